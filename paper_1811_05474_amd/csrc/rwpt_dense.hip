@@ -352,6 +352,7 @@ __global__ __launch_bounds__(kBlock) void k_dense_exchange(
       if (s == react_a) va = (double)v;
       if (s == react_b) vb = (double)v;
     }
+    for (int s = S; s < species_slots(S); ++s) mout[species_slots(S) * (int64_t)i + s] = 0.0f;  // unused slots stay zero
     tot[8] = va - vb;
   }
 #pragma unroll

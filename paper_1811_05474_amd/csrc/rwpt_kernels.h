@@ -129,6 +129,13 @@ hipError_t launch_noalloc_setup(int fp64, int dim, int S, const NoAllocParams& a
 hipError_t launch_noalloc_store(int fp64, int S, int32_t n, const void* mass_sorted, const uint32_t* id,
                                 void* mass, hipStream_t s);
 
+// comps values per particle (stride slots per particle in `in`, cell-sorted) to
+// the caller's order in `out`: out[k n + i] (species_major) or out[comps i + k]
+// for the caller's particle i = id[p].  inv (n entries) is overwritten with the
+// inverse of the id map.
+hipError_t launch_unsort(int fp64, int32_t n, const uint32_t* id, uint32_t* inv, const void* in, void* out, int comps,
+                         int stride, int species_major, hipStream_t s);
+
 // Full-matrix path of one realisation (binary32 state, bf16-split MFMA).
 struct DenseArgs {
   const float* pos;        // [cap][PS] particle-major, sorted

@@ -2467,6 +2467,37 @@ __global__ __launch_bounds__(kBlock) void k_na_store(int32_t n, int32_t S, const
 }
 
 // ---------------------------------------------------------------------------
+// Caller's order for the queries
+// ---------------------------------------------------------------------------
+
+// inv[id[p]] = p.  (id is a permutation of 0..n-1.)
+__global__ __launch_bounds__(kBlock) void k_invert(int32_t n, const uint32_t* __restrict__ id,
+                                                   uint32_t* __restrict__ inv) {
+  const int p = blockIdx.x * kBlock + threadIdx.x;
+  if (p < n) {
+    const uint32_t o = id[p];
+    if (o < (uint32_t)n) inv[o] = (uint32_t)p;
+  }
+}
+
+// The caller's particle i reads its whole record (one line) from its sorted
+// slot, so that the writes are coalesced and only the reads gather.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_unsort(int32_t n, const uint32_t* __restrict__ inv,
+                                                   const T* __restrict__ in, T* __restrict__ out, int32_t comps,
+                                                   int32_t stride, int32_t species_major) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  const int64_t p = inv[i];
+  if (p >= n) return;
+  for (int k = 0; k < comps; ++k) {
+    const T v = in[p * stride + k];
+    if (species_major) out[(int64_t)k * n + i] = v;
+    else out[i * comps + k] = v;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
 
@@ -2841,6 +2872,20 @@ hipError_t launch_noalloc_store(int fp64, int S, int32_t n, const void* mass_sor
   };
   if (fp64) with_s(double{});
   else with_s(float{});
+  return hipGetLastError();
+}
+
+hipError_t launch_unsort(int fp64, int32_t n, const uint32_t* id, uint32_t* inv, const void* in, void* out, int comps,
+                         int stride, int species_major, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  const dim3 g(blocks_for(n)), b(kBlock);
+  hipLaunchKernelGGL(k_invert, g, b, 0, s, n, id, inv);
+  if (fp64)
+    hipLaunchKernelGGL(k_unsort<double>, g, b, 0, s, n, inv, (const double*)in, (double*)out, comps, stride,
+                       species_major);
+  else
+    hipLaunchKernelGGL(k_unsort<float>, g, b, 0, s, n, inv, (const float*)in, (float*)out, comps, stride,
+                       species_major);
   return hipGetLastError();
 }
 

@@ -525,11 +525,10 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
 
   // device copies
   const int64_t ncell = cell_off;
-  const int64_t nscan = (ncell + kScanChunk - 1) / kScanChunk + 1;
   bool regrow = (size_t)(ncell * 4) > c->cell_count.bytes;
   HIPCHK(c, c->cell_count.ensure((size_t)ncell * 4));
   HIPCHK(c, c->cell_start.ensure((size_t)(ncell + 1) * 4));
-  HIPCHK(c, c->scan_part.ensure((size_t)nscan * 4));
+  HIPCHK(c, c->scan_part.ensure(scan_state_words(ncell) * sizeof(uint64_t)));
   HIPCHK(c, c->d_rp.ensure(c->h_rp.size() * sizeof(RealParams)));
   HIPCHK(c, c->d_st.ensure(std::max<size_t>(1, c->h_st.size()) * sizeof(StencilRow)));
   HIPCHK(c, c->d_tiles.ensure(std::max<size_t>(1, c->h_tiles.size()) * sizeof(Tile)));
@@ -636,7 +635,8 @@ static PairArgs pair_args(rwpt_ctx* c) {
 // Leaves positions in pos0, ids in id, keys in skey; the masses move to the
 // other buffer in the new order (mcur flips), or, with move_mass false, stay
 // where they are and src_of records each sorted particle's previous slot.
-static rwpt_status enqueue_sort(rwpt_ctx* c, bool walk, bool move_mass) {
+// The step counter advances by bump after the walk.
+static rwpt_status enqueue_sort(rwpt_ctx* c, bool walk, bool move_mass, int bump) {
   const int fp64 = c->cfg.precision == RWPT_FP64;
   const int32_t n = (int32_t)c->N;
   {
@@ -646,12 +646,12 @@ static rwpt_status enqueue_sort(rwpt_ctx* c, bool walk, bool move_mass) {
                               c->d_blk_real.as<int32_t>(), c->n_real,
                               c->step_ctr.as<uint64_t>(), c->cfg.seed, walk ? 1 : 0,
                               c->cell_count.as<uint32_t>(), c->key.as<uint32_t>(),
-                              c->slot.as<uint32_t>(), c->stream));
+                              c->slot.as<uint32_t>(), c->scan_part.as<uint64_t>(), c->stream));
   }
   {
     PhaseScope ps(c, PH_SCAN);
     HIPCHK(c, launch_cell_scan(c->cell_count.as<uint32_t>(), c->cell_start.as<uint32_t>(), c->ncell_total,
-                               c->scan_part.as<uint32_t>(), c->stream));
+                               c->scan_part.as<uint64_t>(), c->step_ctr.as<uint64_t>(), bump, c->stream));
   }
   {
     PhaseScope ps(c, PH_SCATTER);
@@ -679,7 +679,7 @@ static rwpt_status enqueue_step(rwpt_ctx* c, bool sort, bool walk) {
   const int fp64 = c->cfg.precision == RWPT_FP64;
   const bool stay = sort && masses_stay(c);
   if (sort) {
-    rwpt_status st = enqueue_sort(c, walk, !stay);
+    rwpt_status st = enqueue_sort(c, walk, !stay, 1);
     if (st != RWPT_OK) return st;
   }
   PairArgs a = pair_args(c);
@@ -717,13 +717,19 @@ static rwpt_status enqueue_step(rwpt_ctx* c, bool sort, bool walk) {
     HIPCHK(c, launch_exchange(fp64, c->dim, c->log2l, a, c->stream));
   }
   c->mcur ^= 1;
-  {
-    PhaseScope ps(c, PH_AUDIT);
-    HIPCHK(c, launch_audit_reduce(c->audit_part.as<double>(), c->S + 1, c->d_chunks.as<AuditChunk>(),
-                                  (int32_t)c->h_chunks.size(), c->chunk_part.as<double>(),
-                                  c->d_chunk_start.as<int32_t>(), c->n_real, c->audit_out.as<double>(),
-                                  c->audit_done.as<uint32_t>(), c->step_ctr.as<uint64_t>(), 1, c->stream));
-  }
+  return RWPT_OK;
+}
+
+// Audit of the masses the last step wrote, from its tile partials.  Only the
+// last step of a call can be queried, so it runs once per call and not in
+// every step (4 us of a 50 us step at 3e4 particles, 12 of 650 at 8e6).  The
+// step counter advances by bump: the call's steps without a sort.
+static rwpt_status enqueue_audit(rwpt_ctx* c, int32_t bump) {
+  PhaseScope ps(c, PH_AUDIT);
+  HIPCHK(c, launch_audit_reduce(c->audit_part.as<double>(), c->S + 1, c->d_chunks.as<AuditChunk>(),
+                                (int32_t)c->h_chunks.size(), c->chunk_part.as<double>(),
+                                c->d_chunk_start.as<int32_t>(), c->n_real, c->audit_out.as<double>(),
+                                c->audit_done.as<uint32_t>(), c->step_ctr.as<uint64_t>(), bump, c->stream));
   return RWPT_OK;
 }
 
@@ -734,7 +740,7 @@ static int step_flips(const rwpt_ctx* c, bool sort) { return (sort && !masses_st
 
 static rwpt_status ensure_sorted(rwpt_ctx* c) {
   if (c->sorted_valid) return RWPT_OK;
-  rwpt_status st = enqueue_sort(c, false, true);  // masses follow into the sorted order
+  rwpt_status st = enqueue_sort(c, false, true, 0);  // masses follow into the sorted order
   if (st != RWPT_OK) return st;
   c->sorted_valid = true;
   return RWPT_OK;
@@ -1094,6 +1100,7 @@ rwpt_status rwpt_step(rwpt_ctx* c, double dt, double D, int32_t n_steps) {
   bool advect = false;
   for (int k = 0; k < c->dim; ++k) advect = advect || c->cfg.velocity[k] != 0.0;
   const bool walk = (c->cfg.rw_ratio > 0.0 && D > 0.0) || advect;
+  int32_t unsorted = 0;  // steps without a sort, which do not advance the step counter themselves
   for (int32_t it = 0; it < n_steps; ++it) {
     const bool sort = walk || !c->sorted_valid;
     if (c->cfg.use_graph && !c->prof) {
@@ -1124,8 +1131,9 @@ rwpt_status rwpt_step(rwpt_ctx* c, double dt, double D, int32_t n_steps) {
     }
     c->sorted_valid = true;
     c->steps += 1;
+    if (!sort) ++unsorted;
   }
-  return RWPT_OK;
+  return enqueue_audit(c, unsorted);
 }
 
 rwpt_status rwpt_sync(rwpt_ctx* c) {
@@ -1859,7 +1867,6 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   const int32_t ntiles = (int32_t)((n + G - 1) / G);
   const int64_t cap = (int64_t)(n + 63) / 64 * 64;
   const int PS = dim, Sa = padded_species(S);
-  const int64_t nscan = (ncell + kScanChunk - 1) / kScanChunk + 1;
   // the pieces of the scratch area this call uses
   ScratchLayout L;
   const size_t o_pos0 = L.take(PS * cap * ts), o_pos1 = L.take(PS * cap * ts);
@@ -1867,7 +1874,10 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   const size_t o_id = L.take(cap * 4), o_key = L.take(cap * 4), o_slot = L.take(cap * 4);
   const size_t o_tsrc = L.take(cap * 4), o_tid = L.take(cap * 4), o_tkey = L.take(cap * 4);
   const size_t o_skey = L.take(cap * 4), o_r = L.take(cap * 8), o_q = L.take(cap * ts);
-  const size_t o_cnt = L.take(ncell * 4), o_start = L.take((ncell + 1) * 4), o_scan = L.take(nscan * 4);
+  const size_t o_cnt = L.take(ncell * 4), o_start = L.take((ncell + 1) * 4);
+  // the cell scan's words: the sorted keys' place, which the scatter fills later, where that is large enough
+  const size_t scan_bytes = scan_state_words(ncell) * 8;
+  const size_t o_scan = (size_t)cap * 4 >= scan_bytes ? o_tkey : L.take(scan_bytes);
   const size_t o_rp = L.take(sizeof(RealParams)), o_st = L.take(kNoAllocStencil * sizeof(StencilRow));
   const size_t o_tiles = L.take((size_t)ntiles * sizeof(Tile));
   const size_t o_blk = L.take((size_t)((n + kBlock - 1) / kBlock) * 4), o_ctr = L.take(8);
@@ -1906,8 +1916,9 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   // cell keys (no walk), counting sort, canonical order with the masses moved
   NACHK(launch_walk_key(fp64, dim, at(o_pos0), at(o_pos1), (uint32_t*)at(o_id), n, (RealParams*)at(o_rp),
                         (int64_t*)at(o_rs), (int32_t*)at(o_blk), 1, (uint64_t*)at(o_ctr), c.seed, 0, (uint32_t*)at(o_cnt),
-                        (uint32_t*)at(o_key), (uint32_t*)at(o_slot), s));
-  NACHK(launch_cell_scan((uint32_t*)at(o_cnt), (uint32_t*)at(o_start), ncell, (uint32_t*)at(o_scan), s));
+                        (uint32_t*)at(o_key), (uint32_t*)at(o_slot), (uint64_t*)at(o_scan), s));
+  NACHK(launch_cell_scan((uint32_t*)at(o_cnt), (uint32_t*)at(o_start), ncell, (uint64_t*)at(o_scan),
+                         (uint64_t*)at(o_ctr), 0, s));
   NACHK(launch_scatter(n, (uint32_t*)at(o_key), (uint32_t*)at(o_slot), (uint32_t*)at(o_start), (uint32_t*)at(o_id),
                        (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey), s));
   NACHK(launch_canon(fp64, dim, n, (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey),

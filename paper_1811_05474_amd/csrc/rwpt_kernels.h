@@ -21,22 +21,32 @@ enum Phase {
 constexpr int kBlock = 256;        // threads per block of every kernel
 constexpr int kScanItems = 16;     // counts per thread in the cell-count scan
 constexpr int kScanChunk = kBlock * kScanItems;
-constexpr int64_t kScanDirectMax = 256;  // up to this many scan blocks (one partial per thread), no top-level scan launch
+// Up to this many scan blocks the cell scan is one launch (one block total per
+// thread; beyond, every block would read all the totals before it).
+constexpr int64_t kScanDirectMax = 256;
+// Words of 64 bits the cell scan keeps for ncell cells: kBlock chunk totals
+// and a ticket, or the 32-bit totals of the three-launch form.
+inline size_t scan_state_words(int64_t ncell) {
+  const int64_t nb = (ncell + kScanChunk - 1) / kScanChunk;
+  return (size_t)(nb / 2 + 1 > kBlock + 1 ? nb / 2 + 1 : kBlock + 1);
+}
 
 // Random walk + reflection (optional) and cell key / in-cell slot of every particle.
 // pos_in/pos_out may not alias.  blk_real[b] is the realisation of particle
-// b * kBlock (one entry per block of the launch).
+// b * kBlock (one entry per block of the launch).  Clears scan_state for the
+// cell scan that follows.
 hipError_t launch_walk_key(int fp64, int dim, const void* pos_in, void* pos_out,
                            const uint32_t* id, int32_t n, const RealParams* rp,
                            const int64_t* real_start, const int32_t* blk_real, int32_t n_real,
                            const uint64_t* step_ctr,
                            uint64_t seed, int32_t do_walk, uint32_t* cell_count, uint32_t* key,
-                           uint32_t* slot, hipStream_t s);
+                           uint32_t* slot, uint64_t* scan_state, hipStream_t s);
 
 // Exclusive scan of cell_count[0..ncell) into cell_start[0..ncell]; zeroes cell_count.
-// partials must hold ceil(ncell / kScanChunk) + 1 entries.
-hipError_t launch_cell_scan(uint32_t* cell_count, uint32_t* cell_start, int64_t ncell,
-                            uint32_t* partials, hipStream_t s);
+// scan_state holds scan_state_words(ncell) words, cleared by launch_walk_key.
+// Advances the step counter by bump.
+hipError_t launch_cell_scan(uint32_t* cell_count, uint32_t* cell_start, int64_t ncell, uint64_t* scan_state,
+                            uint64_t* step_ctr, int32_t bump, hipStream_t s);
 
 // Place every particle at cell_start[key] + slot (arrival order inside a cell).
 hipError_t launch_scatter(int32_t n, const uint32_t* key, const uint32_t* slot,
@@ -91,8 +101,8 @@ hipError_t launch_nbr_fill(int fp64, int dim, int log2l, const PairArgs& a, hipS
 // Per-realisation FP64 reduction of the per-tile audit partials in two fixed-
 // order levels (chunks of at most kAuditChunk tiles inside one realisation,
 // then the chunks of each realisation) in one launch; `done` holds n_real
-// zeroed completion counters that the kernel returns to zero.  Optionally
-// advances the step counter.
+// zeroed completion counters that the kernel returns to zero.  Advances the
+// step counter by bump.
 // Few, large chunks: every chunk block of a realisation with more than one
 // chunk ends in a device-scope fence and a completion atomic on a shared
 // counter, which serialise across blocks; a realisation of one chunk needs

@@ -187,8 +187,13 @@ __global__ __launch_bounds__(kBlock) void k_walk_key(
     const uint32_t* __restrict__ id, int32_t n, const RealParams* __restrict__ rp,
     const int64_t* __restrict__ real_start, const int32_t* __restrict__ blk_real, int32_t n_real,
     const uint64_t* __restrict__ step_ctr, uint64_t seed, int32_t do_walk,
-    uint32_t* __restrict__ cell_count, uint32_t* __restrict__ key_out, uint32_t* __restrict__ slot_out) {
+    uint32_t* __restrict__ cell_count, uint32_t* __restrict__ key_out, uint32_t* __restrict__ slot_out,
+    uint64_t* __restrict__ scan_state) {
   const int p = blockIdx.x * kBlock + threadIdx.x;
+  if (blockIdx.x == 0) {  // a zeroed ticket and zeroed block totals for the cell scan that follows
+    scan_state[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) scan_state[kBlock] = 0u;
+  }
   if (p >= n) return;
   // last realisation whose first particle is <= p, from that of the block's
   // first particle (one block rarely spans more than two realisations)
@@ -309,29 +314,42 @@ __global__ __launch_bounds__(kBlock) void k_scan_top(uint32_t* __restrict__ part
 // reading its 16 consecutive elements hits distinct banks.
 __device__ __forceinline__ int scan_pad(int k) { return k + (k >> 4); }
 
-// Final pass: coalesced striped loads into LDS, a sequential scan of 16
-// consecutive elements per thread, a block scan of the thread sums, then
-// coalesced striped stores of the cell starts; the counts are re-zeroed for
-// the next step.  DIRECT: partials holds the block sums themselves and every
-// block adds up those of the blocks before it (no top-level scan launch; the
-// last block writes the grand total start[n]); otherwise partials holds their
-// exclusive scan.
-template <bool DIRECT>
-__global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cnt, int64_t n,
-                                                       const uint32_t* __restrict__ partials,
-                                                       uint32_t* __restrict__ start) {
+// Cell starts of one chunk: coalesced striped loads into LDS, a sequential
+// scan of 16 consecutive elements per thread, a block scan of the thread sums,
+// then coalesced striped stores; the counts are re-zeroed for the next step.
+// ONE (up to kScanDirectMax chunks): the whole scan in this launch.  A block
+// takes the next chunk from a ticket, publishes the chunk's total as soon as
+// it has summed it, and thread t waits for the total of chunk t < its own; a
+// chunk's block has always started before any block that waits for it (the
+// ticket orders them), so every wait ends.  The total and its valid bit
+// travel in one 64-bit word, so a relaxed device-scope load is enough; the
+// walk + key kernel cleared the words.  Otherwise partials holds the exclusive
+// scan of the chunk totals (k_scan_reduce, k_scan_top).
+// Launch-latency bound: at 4.4e5 cells (108 chunks) the two launches took
+// 5.3 + 5.5 us and a gap; a transfer call of 2000 particles went from 40.4 to
+// 37.9 us, fifty 2-D steps of 77777 particles (with one audit per call) from
+// 3.33 to 2.55 ms.
+// step_ctr advances by bump here: the walk that read it has ended and the
+// next one has not started.
+constexpr uint64_t kScanValid = (uint64_t)1 << 32;
+
+template <bool ONE>
+__global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cnt, int64_t n, uint64_t* scan_state,
+                                                       uint32_t* __restrict__ start, uint64_t* __restrict__ step_ctr,
+                                                       int32_t bump) {
   __shared__ uint32_t sh[4];
   __shared__ uint32_t buf[kScanChunk + kScanChunk / 16];
+  __shared__ uint32_t sh_chunk;
   const int t = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * kScanChunk;
-  uint32_t prefix = 0;
-  if constexpr (DIRECT) {
-    uint32_t s = 0;
-    for (int c = t; c < (int)blockIdx.x; c += kBlock) s += partials[c];
-    block_inclusive_scan(s, sh, &prefix);
-  } else {
-    prefix = partials[blockIdx.x];
+  int chunk = blockIdx.x;
+  if constexpr (ONE) {
+    if (t == 0)
+      sh_chunk = __hip_atomic_fetch_add((uint32_t*)(scan_state + kBlock), 1u, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    chunk = (int)__builtin_amdgcn_readfirstlane(sh_chunk);
   }
+  const int64_t base = (int64_t)chunk * kScanChunk;
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i) {
     const int k = t + i * kBlock;
@@ -347,9 +365,23 @@ __global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cn
   }
   uint32_t total;
   const uint32_t incl = block_inclusive_scan(sum, sh, &total);
-  if constexpr (DIRECT) {
-    if (t == 0 && blockIdx.x == gridDim.x - 1) start[n] = prefix + total;
+  uint32_t prefix = 0;
+  if constexpr (ONE) {
+    if (t == 0)
+      __hip_atomic_store(&scan_state[chunk], kScanValid | total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t before = 0;
+    if (t < chunk) {  // chunk < kScanDirectMax = kBlock
+      uint64_t w;
+      while (!((w = __hip_atomic_load(&scan_state[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) & kScanValid))
+        __builtin_amdgcn_s_sleep(1);
+      before = (uint32_t)w;
+    }
+    block_inclusive_scan(before, sh, &prefix);
+    if (t == 0 && chunk == (int)gridDim.x - 1) start[n] = prefix + total;
+  } else {
+    prefix = ((const uint32_t*)scan_state)[chunk];
   }
+  if (bump && chunk == 0 && t == 0) *step_ctr = *step_ctr + (uint64_t)bump;
   uint32_t run = prefix + incl - sum;
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i) {
@@ -1793,7 +1825,7 @@ __device__ __forceinline__ double block_sum_fixed(double (&acc)[NV], double (*sh
 // done[r]) adds the realisation's chunk sums in chunk order with one wave
 // (lanes over chunks, then recursive halving), so realisations are finalised
 // in parallel and the result does not depend on which block finishes last.
-// Block 0 advances the step counter, which no block of this launch reads.
+// Block 0 advances the step counter by `bump`, which no block of this launch reads.
 // The counters are returned to zero for the next launch (no memset node, so
 // the launch can be captured).
 __global__ __launch_bounds__(kBlock) void k_audit(const double* __restrict__ part, int32_t S1,
@@ -1824,7 +1856,7 @@ __global__ __launch_bounds__(kBlock) void k_audit(const double* __restrict__ par
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] += val[u][v];
   const double c = block_sum_fixed<NV>(acc, sh, S1);
-  if (bump && blockIdx.x == 0 && threadIdx.x == 0) *step_ctr = *step_ctr + 1;
+  if (bump && blockIdx.x == 0 && threadIdx.x == 0) *step_ctr = *step_ctr + (uint64_t)bump;
   const int r = ch.real;
   if (ch.n_in_real == 1) {
     if ((int)threadIdx.x < S1) out[(int64_t)r * S1 + threadIdx.x] = c;
@@ -2510,12 +2542,12 @@ hipError_t launch_walk_key(int fp64, int dim, const void* pos_in, void* pos_out,
                            const uint32_t* id, int32_t n, const RealParams* rp,
                            const int64_t* real_start, const int32_t* blk_real, int32_t n_real,
                            const uint64_t* step_ctr, uint64_t seed, int32_t do_walk, uint32_t* cell_count,
-                           uint32_t* key, uint32_t* slot, hipStream_t s) {
+                           uint32_t* key, uint32_t* slot, uint64_t* scan_state, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const dim3 g(blocks_for(n)), b(kBlock);
 #define RWPT_WK(T, D)                                                                             \
   hipLaunchKernelGGL((k_walk_key<T, D>), g, b, 0, s, (const T*)pos_in, (T*)pos_out, id, n, rp, \
-                     real_start, blk_real, n_real, step_ctr, seed, do_walk, cell_count, key, slot)
+                     real_start, blk_real, n_real, step_ctr, seed, do_walk, cell_count, key, slot, scan_state)
   if (fp64) {
     if (dim == 1) RWPT_WK(double, 1);
     else if (dim == 2) RWPT_WK(double, 2);
@@ -2529,18 +2561,18 @@ hipError_t launch_walk_key(int fp64, int dim, const void* pos_in, void* pos_out,
   return hipGetLastError();
 }
 
-hipError_t launch_cell_scan(uint32_t* cell_count, uint32_t* cell_start, int64_t ncell,
-                            uint32_t* partials, hipStream_t s) {
+hipError_t launch_cell_scan(uint32_t* cell_count, uint32_t* cell_start, int64_t ncell, uint64_t* scan_state,
+                            uint64_t* step_ctr, int32_t bump, hipStream_t s) {
+  static_assert(kScanDirectMax <= kBlock, "one chunk total per thread");
   const int64_t nb = (ncell + kScanChunk - 1) / kScanChunk;
-  hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kBlock), 0, s, cell_count, ncell, partials);
+  const dim3 g((unsigned)nb), b(kBlock);
   if (nb <= kScanDirectMax) {
-    // each block sums the block partials before it, at most one per thread
-    hipLaunchKernelGGL(k_scan_final<true>, dim3((unsigned)nb), dim3(kBlock), 0, s, cell_count, ncell, partials,
-                       cell_start);
+    hipLaunchKernelGGL(k_scan_final<true>, g, b, 0, s, cell_count, ncell, scan_state, cell_start, step_ctr, bump);
   } else {
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s, partials, (int32_t)nb, cell_start, ncell);
-    hipLaunchKernelGGL(k_scan_final<false>, dim3((unsigned)nb), dim3(kBlock), 0, s, cell_count, ncell, partials,
-                       cell_start);
+    uint32_t* const partials = (uint32_t*)scan_state;
+    hipLaunchKernelGGL(k_scan_reduce, g, b, 0, s, cell_count, ncell, partials);
+    hipLaunchKernelGGL(k_scan_top, dim3(1), b, 0, s, partials, (int32_t)nb, cell_start, ncell);
+    hipLaunchKernelGGL(k_scan_final<false>, g, b, 0, s, cell_count, ncell, scan_state, cell_start, step_ctr, bump);
   }
   return hipGetLastError();
 }

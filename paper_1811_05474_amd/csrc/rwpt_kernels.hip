@@ -348,6 +348,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cn
                                         __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     chunk = (int)__builtin_amdgcn_readfirstlane(sh_chunk);
+    if (chunk >= (int)gridDim.x) return;  // never in a scan that has its words to itself
   }
   const int64_t base = (int64_t)chunk * kScanChunk;
 #pragma unroll
@@ -371,9 +372,14 @@ __global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cn
       __hip_atomic_store(&scan_state[chunk], kScanValid | total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint32_t before = 0;
     if (t < chunk) {  // chunk < kScanDirectMax = kBlock
-      uint64_t w;
-      while (!((w = __hip_atomic_load(&scan_state[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) & kScanValid))
+      uint64_t w = 0;
+      // bounded, so that calls that overlap on one scratch area (which the
+      // allocation-free entry point does not allow) still end
+      for (int spin = 0; spin < (1 << 20); ++spin) {
+        w = __hip_atomic_load(&scan_state[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (w & kScanValid) break;
         __builtin_amdgcn_s_sleep(1);
+      }
       before = (uint32_t)w;
     }
     block_inclusive_scan(before, sh, &prefix);

@@ -135,7 +135,7 @@ struct rwpt_ctx {
   int64_t steps = 0;
   std::vector<double> audit_init;
 
-  // captured steps: [2 * (sort ? 0 : 1) + mcur at the start of the step]
+  // captured steps: [2 * (walk ? 0 : 1) + mcur at the start of the step]
   hipGraphExec_t gx[4] = {nullptr, nullptr, nullptr, nullptr};
   int32_t n_captures = 0;  // step graphs captured since the context was created
 
@@ -671,59 +671,76 @@ static rwpt_status enqueue_sort(rwpt_ctx* c, bool walk, bool move_mass, int bump
   return RWPT_OK;
 }
 
-// One explicit step.  Positions in pos0; the masses are read from buffer
-// mcur (in the previous sorted order when the sort left them in place) and
-// the updated masses are written, in the current sorted order, to the other
-// buffer, which becomes mcur.
-static rwpt_status enqueue_step(rwpt_ctx* c, bool sort, bool walk) {
-  const int fp64 = c->cfg.precision == RWPT_FP64;
-  const bool stay = sort && masses_stay(c);
-  if (sort) {
-    rwpt_status st = enqueue_sort(c, walk, !stay, 1);
-    if (st != RWPT_OK) return st;
-  }
-  PairArgs a = pair_args(c);
-  a.indirect = stay ? 1 : 0;
+static DenseArgs dense_args(rwpt_ctx* c) {
+  DenseArgs da;
+  memset(&da, 0, sizeof(da));
+  da.pos = c->pos0.as<float>();
+  da.cap = c->cap;
+  da.n = (int32_t)c->N;
+  da.mass_in = mass_buf(c, c->mcur).as<float>();
+  da.mass_out = mass_buf(c, c->mcur ^ 1).as<float>();
+  da.q = c->q.as<float>();
+  da.r = c->r.as<double>();
+  da.bbox = c->bbox.as<float>();
+  da.escale = c->dense_escale;
+  da.skip_s2 = c->dense_skip_s2;
+  da.bparts = c->bparts.as<__bf16>();
+  da.ncb = dense_ncb(c->S, c->cfg.norm);
+  da.S = c->S;
+  da.react_a = c->cfg.react_a;
+  da.react_b = c->cfg.react_b;
+  da.norm = c->cfg.norm;
+  da.audit_part = c->audit_part.as<double>();
+  return da;
+}
+
+// What depends on the positions alone: the row sums (with the neighbour cache
+// or the tile boxes), for every exchange until the positions move.
+static rwpt_status enqueue_rowsums(rwpt_ctx* c, bool indirect) {
   if (c->dense && c->h_rp[0].active) {
-    DenseArgs da;
-    memset(&da, 0, sizeof(da));
-    da.pos = c->pos0.as<float>();
-    da.cap = c->cap;
-    da.n = (int32_t)c->N;
-    da.mass_in = mass_buf(c, c->mcur).as<float>();
-    da.mass_out = mass_buf(c, c->mcur ^ 1).as<float>();
-    da.q = c->q.as<float>();
-    da.r = c->r.as<double>();
-    da.bbox = c->bbox.as<float>();
-    da.escale = c->dense_escale;
-    da.skip_s2 = c->dense_skip_s2;
-    da.bparts = c->bparts.as<__bf16>();
-    da.ncb = dense_ncb(c->S, c->cfg.norm);
-    da.S = c->S;
-    da.react_a = c->cfg.react_a;
-    da.react_b = c->cfg.react_b;
-    da.norm = c->cfg.norm;
-    da.audit_part = c->audit_part.as<double>();
     PhaseScope ps(c, PH_DENSE);
-    HIPCHK(c, launch_dense_step(c->dim, da, c->stream));
-  } else {
+    HIPCHK(c, launch_dense_rowsum(c->dim, dense_args(c), c->stream));
+  } else if (c->cfg.norm == RWPT_NORM_SYM || c->log2l == kPrivateLists || c->log2l == kHalfPairs) {
     // the one-lane-per-particle exchange reads the row-sum pass's neighbour
     // cache, so that pass runs for either normalisation
-    if (c->cfg.norm == RWPT_NORM_SYM || c->log2l == kPrivateLists || c->log2l == kHalfPairs) {
-      PhaseScope ps(c, PH_ROWSUM);
-      HIPCHK(c, launch_rowsum(fp64, c->dim, c->log2l, a, c->stream));
-    }
+    PairArgs a = pair_args(c);
+    a.indirect = indirect ? 1 : 0;
+    PhaseScope ps(c, PH_ROWSUM);
+    HIPCHK(c, launch_rowsum(c->cfg.precision == RWPT_FP64, c->dim, c->log2l, a, c->stream));
+  }
+  return RWPT_OK;
+}
+
+// The transfer and the reaction.  The masses are read from buffer mcur (in
+// the previous sorted order when indirect) and written, in the current sorted
+// order, to the other buffer, which becomes mcur.
+static rwpt_status enqueue_exchange(rwpt_ctx* c, bool indirect) {
+  if (c->dense && c->h_rp[0].active) {
+    PhaseScope ps(c, PH_DENSE);
+    HIPCHK(c, launch_dense_exchange(c->dim, dense_args(c), c->stream));
+  } else {
+    PairArgs a = pair_args(c);
+    a.indirect = indirect ? 1 : 0;
     PhaseScope ps(c, PH_EXCHANGE);
-    HIPCHK(c, launch_exchange(fp64, c->dim, c->log2l, a, c->stream));
+    HIPCHK(c, launch_exchange(c->cfg.precision == RWPT_FP64, c->dim, c->log2l, a, c->stream));
   }
   c->mcur ^= 1;
   return RWPT_OK;
 }
 
+// One explicit step with a walk; positions in pos0.
+static rwpt_status enqueue_step(rwpt_ctx* c) {
+  const bool stay = masses_stay(c);
+  rwpt_status st = enqueue_sort(c, true, !stay, 1);
+  if (st == RWPT_OK) st = enqueue_rowsums(c, stay);
+  if (st == RWPT_OK) st = enqueue_exchange(c, stay);
+  return st;
+}
+
 // Audit of the masses the last step wrote, from its tile partials.  Only the
 // last step of a call can be queried, so it runs once per call and not in
 // every step (4 us of a 50 us step at 3e4 particles, 12 of 650 at 8e6).  The
-// step counter advances by bump: the call's steps without a sort.
+// step counter advances by bump: the call's steps without a walk.
 static rwpt_status enqueue_audit(rwpt_ctx* c, int32_t bump) {
   PhaseScope ps(c, PH_AUDIT);
   HIPCHK(c, launch_audit_reduce(c->audit_part.as<double>(), c->S + 1, c->d_chunks.as<AuditChunk>(),
@@ -735,7 +752,7 @@ static rwpt_status enqueue_audit(rwpt_ctx* c, int32_t bump) {
 
 // Flips of mcur in one step: the exchange always writes the other buffer; a
 // sort that moves the masses flips once more.
-static int step_flips(const rwpt_ctx* c, bool sort) { return (sort && !masses_stay(c)) ? 0 : 1; }
+static int step_flips(const rwpt_ctx* c, bool walk) { return (walk && !masses_stay(c)) ? 0 : 1; }
 
 
 static rwpt_status ensure_sorted(rwpt_ctx* c) {
@@ -1100,17 +1117,23 @@ rwpt_status rwpt_step(rwpt_ctx* c, double dt, double D, int32_t n_steps) {
   bool advect = false;
   for (int k = 0; k < c->dim; ++k) advect = advect || c->cfg.velocity[k] != 0.0;
   const bool walk = (c->cfg.rw_ratio > 0.0 && D > 0.0) || advect;
-  int32_t unsorted = 0;  // steps without a sort, which do not advance the step counter themselves
+  if (!walk) {
+    // fixed positions: sorted once, and the row sums are those of every step
+    // of this call (1-D, 32768 particles: 19 us of a 54 us step; full matrix
+    // 34 of 156)
+    st = ensure_sorted(c);
+    if (st == RWPT_OK) st = enqueue_rowsums(c, false);
+    if (st != RWPT_OK) return st;
+  }
   for (int32_t it = 0; it < n_steps; ++it) {
-    const bool sort = walk || !c->sorted_valid;
     if (c->cfg.use_graph && !c->prof) {
       // a captured step bakes in the buffers of the mass parity it starts from
       const int m0 = c->mcur;
-      hipGraphExec_t& gx = c->gx[2 * (sort ? 0 : 1) + m0];
+      hipGraphExec_t& gx = c->gx[2 * (walk ? 0 : 1) + m0];
       if (!gx) {
         hipGraph_t g = nullptr;
         HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-        rwpt_status s2 = enqueue_step(c, sort, walk);
+        rwpt_status s2 = walk ? enqueue_step(c) : enqueue_exchange(c, false);
         hipError_t ec = hipStreamEndCapture(c->stream, &g);
         c->mcur = m0;  // capture records the step; it runs at the launch below
         if (s2 != RWPT_OK) {
@@ -1124,16 +1147,15 @@ rwpt_status rwpt_step(rwpt_ctx* c, double dt, double D, int32_t n_steps) {
         ++c->n_captures;
       }
       HIPCHK(c, hipGraphLaunch(gx, c->stream));
-      c->mcur = m0 ^ step_flips(c, sort);
+      c->mcur = m0 ^ step_flips(c, walk);
     } else {
-      st = enqueue_step(c, sort, walk);
+      st = walk ? enqueue_step(c) : enqueue_exchange(c, false);
       if (st != RWPT_OK) return st;
     }
     c->sorted_valid = true;
     c->steps += 1;
-    if (!sort) ++unsorted;
   }
-  return enqueue_audit(c, unsorted);
+  return enqueue_audit(c, walk ? 0 : n_steps);
 }
 
 rwpt_status rwpt_sync(rwpt_ctx* c) {

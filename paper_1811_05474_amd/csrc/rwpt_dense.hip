@@ -366,23 +366,41 @@ __global__ __launch_bounds__(kBlock) void k_dense_exchange(
   }
 }
 
-hipError_t launch_dense_step(int dim, const DenseArgs& a, hipStream_t s) {
+// f(IC<dim>) for the supported dimensions.
+template <typename F>
+static hipError_t with_dim(int dim, F&& f) {
+  if (dim == 1) f(std::integral_constant<int, 1>{});
+  else if (dim == 2) f(std::integral_constant<int, 2>{});
+  else if (dim == 3) f(std::integral_constant<int, 3>{});
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_dense_rowsum(int dim, const DenseArgs& a, hipStream_t s) {
   const int32_t n = a.n;
   if (n <= 0) return hipSuccess;
   const int32_t ntile = (n + kColTile - 1) / kColTile;
-  const dim3 b(kBlock);
-  const int NC = 16 * a.ncb;
-  if (a.ncb < 1 || a.ncb > 2 || dim < 1 || dim > 3) return hipErrorInvalidValue;
   const dim3 gbox((unsigned)((ntile + kBlock - 1) / kBlock));
   const dim3 gsum((unsigned)((n + kRowTileSum - 1) / kRowTileSum)), bsum(64 * kSumWaves);
-  const dim3 gex((unsigned)((n + kRowTile - 1) / kRowTile));
-  const dim3 gprep((unsigned)((a.cap + kBlock - 1) / kBlock));
-  auto go = [&](auto d) {
+  return with_dim(dim, [&](auto d) {
     constexpr int D = decltype(d)::value;
-    hipLaunchKernelGGL((k_tile_bbox<D>), gbox, b, 0, s, a.pos, n, a.bbox);
+    hipLaunchKernelGGL((k_tile_bbox<D>), gbox, dim3(kBlock), 0, s, a.pos, n, a.bbox);
     hipLaunchKernelGGL((k_dense_rowsum<D>), gsum, bsum, 0, s, a.pos, n, a.bbox, ntile, a.escale,
                        a.skip_s2, a.r, a.q);
-    hipLaunchKernelGGL(k_dense_prep_b, gprep, b, 0, s, a.mass_in, a.q, a.cap, n, a.S, a.norm, NC, a.bparts);
+  });
+}
+
+hipError_t launch_dense_exchange(int dim, const DenseArgs& a, hipStream_t s) {
+  const int32_t n = a.n;
+  if (n <= 0) return hipSuccess;
+  if (a.ncb < 1 || a.ncb > 2) return hipErrorInvalidValue;
+  const int32_t ntile = (n + kColTile - 1) / kColTile;
+  const dim3 b(kBlock);
+  const dim3 gex((unsigned)((n + kRowTile - 1) / kRowTile));
+  const dim3 gprep((unsigned)((a.cap + kBlock - 1) / kBlock));
+  return with_dim(dim, [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    hipLaunchKernelGGL(k_dense_prep_b, gprep, b, 0, s, a.mass_in, a.q, a.cap, n, a.S, a.norm, 16 * a.ncb, a.bparts);
     if (a.ncb == 1)
       hipLaunchKernelGGL((k_dense_exchange<D, 1>), gex, b, 0, s, a.pos, a.cap, n, a.mass_in, a.mass_out, a.q,
                          a.bbox, ntile, a.escale, a.skip_s2, a.bparts, a.S, a.react_a, a.react_b, a.norm,
@@ -391,11 +409,7 @@ hipError_t launch_dense_step(int dim, const DenseArgs& a, hipStream_t s) {
       hipLaunchKernelGGL((k_dense_exchange<D, 2>), gex, b, 0, s, a.pos, a.cap, n, a.mass_in, a.mass_out, a.q,
                          a.bbox, ntile, a.escale, a.skip_s2, a.bparts, a.S, a.react_a, a.react_b, a.norm,
                          a.audit_part);
-  };
-  if (dim == 1) go(std::integral_constant<int, 1>{});
-  else if (dim == 2) go(std::integral_constant<int, 2>{});
-  else go(std::integral_constant<int, 3>{});
-  return hipGetLastError();
+  });
 }
 
 }  // namespace rwpt

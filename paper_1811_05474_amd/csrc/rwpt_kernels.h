@@ -168,7 +168,9 @@ constexpr int kDenseColTile = 32;
 constexpr int64_t kDenseMaxN = (int64_t)1 << 17;
 // column blocks of 16 the contraction needs: [M_s, q M_s, q, 1] (symmetric) or [M_s, 1] (row)
 inline int dense_ncb(int S, int norm) { return ((norm == 0 ? 2 * S + 2 : S + 1) + 15) / 16; }
-hipError_t launch_dense_step(int dim, const DenseArgs& a, hipStream_t s);
+// Tile boxes and row sums (functions of the positions alone), then the exchange.
+hipError_t launch_dense_rowsum(int dim, const DenseArgs& a, hipStream_t s);
+hipError_t launch_dense_exchange(int dim, const DenseArgs& a, hipStream_t s);
 
 // Instruction-rate probes (register-only kernels of rwpt_probe.hip): binary32
 // FMA, binary32 exp2, and the per-candidate code of the row-broadcast row-sum

@@ -89,6 +89,13 @@ const char* kPhaseNames[PH_N] = {"walk_key", "cell_scan", "scatter", "canon", "r
 
 }  // namespace
 
+// Steps of the longer captured graph: even, so that it ends on the mass buffer
+// it began with.  A graph launch costs about 5 us beside its kernels' gaps: 500
+// 1-D steps of two launches each took 11.6 ms one step a graph, 8.6 ms so; one
+// of 1e6 particles in 2-D 0.419 -> 0.400 ms.  A longer one is paid for in the
+// first call, which captures it (about 0.3 ms).
+constexpr int kGraphSteps = 8;
+
 struct rwpt_ctx {
   rwpt_config cfg;
   std::string err;
@@ -115,6 +122,9 @@ struct rwpt_ctx {
   DevBuf bbox, bparts;  // full-matrix path
   DevBuf half_slots, half_own, d_item_start, d_item_real;  // half-stencil tiling
   int64_t half_nitems = 0;
+  DevBuf d_gauss_items, gauss_tab, gauss_mom;  // 1-D expansions
+  int gauss = 0;                    // their plan (0: the tiles evaluate every pair)
+  int32_t gauss_nitems = 0;
   bool dense = false;   // full-matrix path selected at init
   float dense_escale = 0.0f, dense_skip_s2 = 0.0f;
   int64_t ncell_total = 0;
@@ -136,7 +146,8 @@ struct rwpt_ctx {
   std::vector<double> audit_init;
 
   // captured steps: [2 * (walk ? 0 : 1) + mcur at the start of the step]
-  hipGraphExec_t gx[4] = {nullptr, nullptr, nullptr, nullptr};
+  // and, from index 4, kGraphSteps steps in one graph
+  hipGraphExec_t gx[8] = {};
   int32_t n_captures = 0;  // step graphs captured since the context was created
 
   // read-back of the queries
@@ -226,7 +237,7 @@ static int default_lanes(int dim, int64_t n, bool fp64) {
 }
 
 static void invalidate_graphs(rwpt_ctx* c) {
-  for (int k = 0; k < 4; ++k)
+  for (int k = 0; k < 8; ++k)
     if (c->gx[k]) {
       (void)hipGraphExecDestroy(c->gx[k]);
       c->gx[k] = nullptr;
@@ -412,6 +423,18 @@ static void real_grid(const rwpt_config& cfg, int dim, double dt, double Dr, int
   P.n_stencil = (int32_t)st.size() - P.stencil_off;
 }
 
+// Fixed-capacity list of stencil rows (no host allocation).
+struct RowBuf {
+  StencilRow* rows;
+  int cap;
+  int n;
+  size_t size() const { return (size_t)n; }
+  void push_back(const StencilRow& r) {
+    if (n < cap) rows[n] = r;
+    ++n;
+  }
+};
+
 // Segments of the half-stencil tiling for one realisation: seg_w =
 // ceil(2 * the widest reach along x of its stencil rows / (npar - 1)), so that
 // at most npar consecutive segments of a row (distinct mod npar) reach any
@@ -444,6 +467,64 @@ static void half_segments(RealParams& P, const StencilRow* st, int64_t nr, int64
   P.n_fwd = n_fwd;
 }
 
+// Reaches of the 1-D expansions for a grid of one realisation; false if its
+// cells are too wide or too many for the plan.  Inner cells: all their points
+// within the cutoff of each other, a margin of 1e-5 over the rounding of the
+// predicate (full matrix: out to weights of 2^-44, no outer cells).
+static bool gauss_reach(RealParams& P, const StencilRow* st, bool dense, const GaussPlan& plan) {
+  if (!P.active) return true;
+  const double h = 1.0 / P.inv_h[0], sigma = 1.0 / std::sqrt(-P.escale_d);
+  if (!(h <= plan.width * sigma)) return false;
+  if (dense) {
+    P.g_in = P.g_out = (int32_t)std::ceil(std::sqrt(44.0 * std::log(2.0)) * sigma / h);
+  } else {
+    const double k = std::floor(std::sqrt(P.rc2_d) * (1.0 - 1e-5) / h) - 1.0;
+    if (!(k >= 1.0 && k <= (double)plan.reach)) return false;
+    P.g_in = (int32_t)k;
+    P.g_out = st[P.stencil_off].rx;  // the one row of a 1-D stencil
+  }
+  return P.g_in <= plan.reach;
+}
+
+// Mean particles per cell from which the expansions pay: a cell costs about
+// (2 g_in + 1) P (P + 1) / 2 operations per column, 2200 with 32 cells per
+// cutoff, whatever it holds, and eight particles of 512 neighbours about 8 * 600 * 2
+// per column as pairs.
+constexpr int64_t kGaussPerCell = 8;
+
+// The 1-D expansion plan of an ensemble with `n_real` realisations of
+// real_start, or 0.  Only where the caller left tiling and cells open, in
+// binary32; a call for RWPT_PATH_DENSE gets the matrix-core kernels.
+template <typename ScaleOf>
+static int gauss_plan(const rwpt_config& cfg, int dim, double dt, double D, int32_t n_real, const int64_t* real_start,
+                      ScaleOf&& scale_of, bool dense) {
+  if (dim != 1 || cfg.precision != RWPT_FP32 || cfg.tile_lanes != 0 || cfg.path == RWPT_PATH_DENSE) return 0;
+  for (int k = 0; k < 3; ++k)
+    if (cfg.cell_refine[k] > 0) return 0;
+  if (std::isinf(cfg.kappa) && !dense) return 0;
+  for (int plan = 1; plan <= kGaussPlans; ++plan) {
+    if (dense != (plan == 3)) continue;
+    const double refine[3] = {(double)kGaussPlan[plan].refine, 1.0, 1.0};
+    int64_t n = 0, cells = 0;
+    bool ok = true;
+    for (int32_t r = 0; r < n_real && ok; ++r) {
+      RealParams P;
+      StencilRow row;
+      RowBuf rows{&row, 1, 0};
+      float es = 0.0f, skip = 0.0f;
+      const int64_t nr = real_start[r + 1] - real_start[r];
+      real_grid(cfg, dim, dt, D * scale_of(r), nr, refine, dense, &es, &skip, 0, P, rows);
+      ok = gauss_reach(P, &row, dense, kGaussPlan[plan]);
+      if (P.active) {
+        n += nr;
+        cells += P.nc[0];
+      }
+    }
+    if (ok && cells > 0 && n >= kGaussPerCell * cells) return plan;
+  }
+  return 0;
+}
+
 static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   if (c->grid_valid && c->g_dt == dt && c->g_D == D) return RWPT_OK;
   const rwpt_config& cfg = c->cfg;
@@ -454,6 +535,9 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   double defr[3];
   default_refine(dim, defr);
   for (int k = 0; k < 3; ++k) c->refine[k] = cfg.cell_refine[k] > 0 ? cfg.cell_refine[k] : defr[k];
+  c->gauss = gauss_plan(cfg, dim, dt, D, c->n_real, c->real_start.data(), [&](int32_t r) { return c->d_scale[r]; },
+                        c->dense);
+  if (c->gauss) c->refine[0] = kGaussPlan[c->gauss].refine;
   const int G = (c->log2l == kPrivateLists || c->log2l == kHalfPairs) ? 64 : 64 >> c->log2l;
   const bool half = c->log2l == kHalfPairs;
 
@@ -471,6 +555,8 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
     P.p_end = c->real_start[r + 1];
     cell_off += (int64_t)P.nc[0] * P.nc[1] * P.nc[2];
     if (half) half_segments(P, c->h_st.data() + P.stencil_off, nr, kHalfTarget);
+    if (c->gauss && !gauss_reach(P, c->h_st.data(), c->dense, kGaussPlan[c->gauss]))
+      return fail(c, RWPT_EUNSUPPORTED, "cell grid of the 1-D expansions");  // never: the plan was made for this grid
     c->h_tile_start[r] = (int32_t)c->h_tiles.size();
     for (int64_t b = P.p_begin; b < P.p_end; b += G)
       c->h_tiles.push_back(Tile{(int32_t)b, (int32_t)std::min<int64_t>(b + G, P.p_end), r, 0});
@@ -488,6 +574,13 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   c->h_chunk_start[c->n_real] = (int32_t)c->h_chunks.size();
   if (cell_off >= (int64_t)1 << 31) return fail(c, RWPT_EUNSUPPORTED, "cell grid too large (%lld cells)", (long long)cell_off);
   c->ntiles = (int32_t)c->h_tiles.size();
+  // 1-D expansions: blocks of up to kGaussTiles tiles of one realisation
+  std::vector<GaussItem> gitems;
+  if (c->gauss)
+    for (int r = 0; r < c->n_real; ++r)
+      for (int32_t t = c->h_tile_start[r]; t < c->h_tile_start[r + 1]; t += kGaussTiles)
+        gitems.push_back(GaussItem{t, std::min<int32_t>(kGaussTiles, c->h_tile_start[r + 1] - t), r, 0});
+  c->gauss_nitems = (int32_t)gitems.size();
   // half-stencil tiling: work items (row, segment) of every realisation, and
   // slot planes npar (1 + forward rows) deep
   std::vector<int64_t> item_start(c->n_real + 1, 0);
@@ -576,6 +669,15 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   HIPCHK(c, hipMemcpyAsync(c->d_tile_start.p, c->h_tile_start.data(),
                            c->h_tile_start.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
   (void)regrow;
+  if (c->gauss) {
+    HIPCHK(c, c->d_gauss_items.ensure(std::max<size_t>(1, gitems.size()) * sizeof(GaussItem)));
+    HIPCHK(c, c->gauss_tab.ensure((size_t)c->n_real * gauss_rows(c->gauss) * kGaussPlan[c->gauss].terms * sizeof(double)));
+    HIPCHK(c, c->gauss_mom.ensure(gauss_moment_words(c->gauss, ncell, c->S) * sizeof(double)));
+    if (!gitems.empty())
+      HIPCHK(c, hipMemcpyAsync(c->d_gauss_items.p, gitems.data(), gitems.size() * sizeof(GaussItem),
+                               hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, launch_gauss_table(c->gauss, c->d_rp.as<RealParams>(), c->n_real, c->gauss_tab.as<double>(), c->stream));
+  }
   HIPCHK(c, hipMemsetAsync(c->cell_count.p, 0, (size_t)ncell * 4, c->stream));
   // the host vectors above must stay alive until the copies finish
   HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -628,6 +730,12 @@ static PairArgs pair_args(rwpt_ctx* c) {
   a.half_nitems = c->half_nitems;
   a.half_cap = c->cap;
   a.n_real = c->n_real;
+  a.gauss_items = c->d_gauss_items.as<GaussItem>();
+  a.gauss_nitems = c->gauss_nitems;
+  a.gauss_rows = c->gauss ? gauss_rows(c->gauss) : 0;
+  a.gauss_tab = c->gauss_tab.as<double>();
+  a.gauss_mom = c->gauss_mom.as<double>();
+  a.gauss_ncell = c->ncell_total;
   return a;
 }
 
@@ -697,7 +805,11 @@ static DenseArgs dense_args(rwpt_ctx* c) {
 // What depends on the positions alone: the row sums (with the neighbour cache
 // or the tile boxes), for every exchange until the positions move.
 static rwpt_status enqueue_rowsums(rwpt_ctx* c, bool indirect) {
-  if (c->dense && c->h_rp[0].active) {
+  if (c->gauss) {
+    if (c->cfg.norm != RWPT_NORM_SYM) return RWPT_OK;
+    PhaseScope ps(c, c->dense ? PH_DENSE : PH_ROWSUM);
+    HIPCHK(c, launch_gauss_rowsum(c->gauss, pair_args(c), c->stream));
+  } else if (c->dense && c->h_rp[0].active) {
     PhaseScope ps(c, PH_DENSE);
     HIPCHK(c, launch_dense_rowsum(c->dim, dense_args(c), c->stream));
   } else if (c->cfg.norm == RWPT_NORM_SYM || c->log2l == kPrivateLists || c->log2l == kHalfPairs) {
@@ -715,7 +827,10 @@ static rwpt_status enqueue_rowsums(rwpt_ctx* c, bool indirect) {
 // the previous sorted order when indirect) and written, in the current sorted
 // order, to the other buffer, which becomes mcur.
 static rwpt_status enqueue_exchange(rwpt_ctx* c, bool indirect) {
-  if (c->dense && c->h_rp[0].active) {
+  if (c->gauss) {
+    PhaseScope ps(c, c->dense ? PH_DENSE : PH_EXCHANGE);
+    HIPCHK(c, launch_gauss_exchange(c->gauss, pair_args(c), c->stream));
+  } else if (c->dense && c->h_rp[0].active) {
     PhaseScope ps(c, PH_DENSE);
     HIPCHK(c, launch_dense_exchange(c->dim, dense_args(c), c->stream));
   } else {
@@ -807,18 +922,6 @@ static rwpt_status scratch_on_current_device(void** out) {
   *out = g_scratch_ptr[dev];
   return RWPT_OK;
 }
-
-// Fixed-capacity list of stencil rows (no host allocation).
-struct RowBuf {
-  StencilRow* rows;
-  int cap;
-  int n;
-  size_t size() const { return (size_t)n; }
-  void push_back(const StencilRow& r) {
-    if (n < cap) rows[n] = r;
-    ++n;
-  }
-};
 
 // Bump allocation of 256-byte-aligned pieces of the scratch area.
 struct ScratchLayout {
@@ -1125,17 +1228,20 @@ rwpt_status rwpt_step(rwpt_ctx* c, double dt, double D, int32_t n_steps) {
     if (st == RWPT_OK) st = enqueue_rowsums(c, false);
     if (st != RWPT_OK) return st;
   }
-  for (int32_t it = 0; it < n_steps; ++it) {
+  for (int32_t it = 0; it < n_steps;) {
+    int32_t batch = 1;
     if (c->cfg.use_graph && !c->prof) {
       // a captured step bakes in the buffers of the mass parity it starts from
       const int m0 = c->mcur;
-      hipGraphExec_t& gx = c->gx[2 * (walk ? 0 : 1) + m0];
+      batch = n_steps - it >= kGraphSteps ? kGraphSteps : 1;
+      hipGraphExec_t& gx = c->gx[(batch > 1 ? 4 : 0) + 2 * (walk ? 0 : 1) + m0];
       if (!gx) {
         hipGraph_t g = nullptr;
         HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-        rwpt_status s2 = walk ? enqueue_step(c) : enqueue_exchange(c, false);
+        rwpt_status s2 = RWPT_OK;
+        for (int32_t k = 0; k < batch && s2 == RWPT_OK; ++k) s2 = walk ? enqueue_step(c) : enqueue_exchange(c, false);
         hipError_t ec = hipStreamEndCapture(c->stream, &g);
-        c->mcur = m0;  // capture records the step; it runs at the launch below
+        c->mcur = m0;  // capture records the steps; they run at the launch below
         if (s2 != RWPT_OK) {
           if (g) (void)hipGraphDestroy(g);
           return s2;
@@ -1147,13 +1253,14 @@ rwpt_status rwpt_step(rwpt_ctx* c, double dt, double D, int32_t n_steps) {
         ++c->n_captures;
       }
       HIPCHK(c, hipGraphLaunch(gx, c->stream));
-      c->mcur = m0 ^ step_flips(c, walk);
+      if (batch == 1) c->mcur = m0 ^ step_flips(c, walk);
     } else {
       st = walk ? enqueue_step(c) : enqueue_exchange(c, false);
       if (st != RWPT_OK) return st;
     }
     c->sorted_valid = true;
-    c->steps += 1;
+    c->steps += batch;
+    it += batch;
   }
   return enqueue_audit(c, walk ? 0 : n_steps);
 }
@@ -1463,7 +1570,7 @@ rwpt_status rwpt_debug_rowsums(rwpt_ctx* c, double dt, double D, int32_t unit_we
   if (st != RWPT_OK) return st;
   PairArgs a = pair_args(c);
   a.r_out = c->r.as<double>();
-  DevBuf rp_unit;
+  DevBuf rp_unit, tab_unit;
   rwpt_status result = RWPT_OK;
   do {
     if (unit_weights) {
@@ -1482,8 +1589,18 @@ rwpt_status rwpt_debug_rowsums(rwpt_ctx* c, double dt, double D, int32_t unit_we
         break;
       }
       a.rp = rp_unit.as<RealParams>();
+      if (c->gauss) {
+        e = tab_unit.ensure((size_t)c->n_real * a.gauss_rows * kGaussPlan[c->gauss].terms * sizeof(double));
+        if (e == hipSuccess) e = launch_gauss_table(c->gauss, a.rp, c->n_real, tab_unit.as<double>(), c->stream);
+        if (e != hipSuccess) {
+          result = fail(c, RWPT_EDEVICE, "debug_rowsums table: %s", hipGetErrorString(e));
+          break;
+        }
+        a.gauss_tab = tab_unit.as<double>();
+      }
     }
-    hipError_t e = launch_rowsum(c->cfg.precision == RWPT_FP64, c->dim, c->log2l, a, c->stream);
+    hipError_t e = c->gauss ? launch_gauss_rowsum(c->gauss, a, c->stream)
+                            : launch_rowsum(c->cfg.precision == RWPT_FP64, c->dim, c->log2l, a, c->stream);
     std::vector<double> hr(N);
     std::vector<uint32_t> hid(N);
     if (e == hipSuccess) e = hipMemcpyAsync(hr.data(), c->r.p, N * 8, hipMemcpyDeviceToHost, c->stream);
@@ -1502,6 +1619,7 @@ rwpt_status rwpt_debug_rowsums(rwpt_ctx* c, double dt, double D, int32_t unit_we
     }
   } while (0);
   rp_unit.release();
+  tab_unit.release();
   return result;
 }
 
@@ -1634,6 +1752,7 @@ static std::vector<std::pair<int, std::array<double, 3>>> tuning_candidates(int 
   else if (dim == 2) refs = {{8, 1, 1}, {16, 1, 1}, {4, 2, 1}, {8, 2, 1}, {8, 3, 1}, {16, 3, 1}, {8, 4, 1}};
   else refs = {{0.5, 0.5, 0.5}, {1, 0.5, 0.5}, {2, 1, 1}, {4, 1, 1}, {8, 1, 1}, {4, 2, 2}, {8, 0.5, 0.5}};
   std::vector<std::pair<int, std::array<double, 3>>> out;
+  if (dim == 1 && !fp64) out.push_back({0, {0, 0, 0}});  // the 1-D expansions, where they apply
   for (int lanes : {-2, -1, 1, 4, 8, 16})
     if (lanes != -2 || !fp64)
       for (auto& r : refs) out.push_back({lanes, r});
@@ -1680,7 +1799,7 @@ static bool tuning_cache_lookup(const std::string& key, int* lanes, double ref[3
     if (key == line) {
       int l;
       double r0, r1, r2;
-      if (sscanf(bar + 1, "%d %lf %lf %lf", &l, &r0, &r1, &r2) == 4 && lanes_to_log2(l) != -2) {
+      if (sscanf(bar + 1, "%d %lf %lf %lf", &l, &r0, &r1, &r2) == 4 && (l == 0 || lanes_to_log2(l) != -2)) {
         *lanes = l;
         ref[0] = r0;
         ref[1] = r1;
@@ -1775,9 +1894,11 @@ rwpt_status rwpt_autotune(rwpt_ctx* c, double dt, double D, int32_t trial_steps)
       // A step's graph depends on the mass buffer it starts from, which
       // alternates when the step flips it once (a sort that leaves the masses
       // in place, or a step without a sort); three steps capture every graph
-      // the timed steps replay, so no capture falls inside the timed window.
-      const int warm = c->cfg.use_graph ? 3 : 1;
-      rwpt_status st = rwpt_step(c, dt, D, warm);
+      // the timed steps replay, and kGraphSteps more, which start from the
+      // buffer the timed steps start from, the longer graph; so no capture
+      // falls inside the timed window.
+      rwpt_status st = rwpt_step(c, dt, D, c->cfg.use_graph ? 3 : 1);
+      if (st == RWPT_OK && c->cfg.use_graph && trial_steps >= kGraphSteps) st = rwpt_step(c, dt, D, kGraphSteps);
       if (st == RWPT_EUNSUPPORTED) {
         c->err.clear();  // e.g. a grid too large for this candidate: skip it
         continue;
@@ -1875,22 +1996,41 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   // grid of the realisation for (dt, D): parameters and stencil rows, kept in
   // kernel arguments
   NoAllocParams na;
-  memset(&na, 0, sizeof(na));
-  RowBuf rows{na.st, kNoAllocStencil, 0};
-  float unused_escale = 0.0f, unused_skip = 0.0f;
-  real_grid(c, dim, dt, D, n, refine, false, &unused_escale, &unused_skip, 0, na.P, rows);
-  if (rows.n > kNoAllocStencil)
-    return fail(nullptr, RWPT_EUNSUPPORTED, "the cutoff spans %d stencil rows; the allocation-free path takes at most %d",
-                rows.n, kNoAllocStencil);
-  na.n_st = rows.n;
-  na.P.p_begin = 0;
-  na.P.p_end = n;
-  const int64_t ncell = (int64_t)na.P.nc[0] * na.P.nc[1] * na.P.nc[2];
+  const int64_t n_range[2] = {0, n};
+  int plan = gauss_plan(c, dim, dt, D, 1, n_range, [](int32_t) { return 1.0; }, false);
   const int32_t ntiles = (int32_t)((n + G - 1) / G);
   const int64_t cap = (int64_t)(n + 63) / 64 * 64;
   const int PS = dim, Sa = padded_species(S);
-  // the pieces of the scratch area this call uses
   ScratchLayout L;
+  int64_t ncell = 0;
+  size_t o_gtab = 0, o_gmom = 0;
+  // the pieces of the scratch area this call uses; the 1-D expansions only
+  // where theirs fit too
+  for (;; plan = 0) {
+    memset(&na, 0, sizeof(na));
+    RowBuf rows{na.st, kNoAllocStencil, 0};
+    float unused_escale = 0.0f, unused_skip = 0.0f;
+    if (plan) refine[0] = kGaussPlan[plan].refine;
+    else refine[0] = c.cell_refine[0] > 0 ? c.cell_refine[0] : defr[0];
+    real_grid(c, dim, dt, D, n, refine, false, &unused_escale, &unused_skip, 0, na.P, rows);
+    if (rows.n > kNoAllocStencil)
+      return fail(nullptr, RWPT_EUNSUPPORTED, "the cutoff spans %d stencil rows; the allocation-free path takes at most %d",
+                  rows.n, kNoAllocStencil);
+    na.n_st = rows.n;
+    na.P.p_begin = 0;
+    na.P.p_end = n;
+    ncell = (int64_t)na.P.nc[0] * na.P.nc[1] * na.P.nc[2];
+    if (!plan) break;
+    // room for the pieces below: per particle, per cell and per tile, the walk's
+    // table, parameters and rounding
+    L.used = (size_t)cap * (2 * PS * ts + 2 * Sa * ts + 7 * 4 + 8 + ts) + (size_t)ncell * 8 +
+             (size_t)ntiles * (sizeof(Tile) + (S + 1) * 8) + (size_t)cap / 32 + 16384;
+    o_gtab = L.take((size_t)gauss_rows(plan) * kGaussPlan[plan].terms * 8);
+    o_gmom = L.take(gauss_moment_words(plan, ncell, S) * 8);
+    if (L.used <= kScratchBytes && gauss_reach(na.P, na.st, false, kGaussPlan[plan])) break;
+  }
+  const size_t gauss_from = o_gtab;
+  L.used = 0;
   const size_t o_pos0 = L.take(PS * cap * ts), o_pos1 = L.take(PS * cap * ts);
   const size_t o_m0 = L.take(Sa * cap * ts), o_m1 = L.take(Sa * cap * ts);
   const size_t o_id = L.take(cap * 4), o_key = L.take(cap * 4), o_slot = L.take(cap * 4);
@@ -1917,6 +2057,7 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
                 "%d particles (dim %d, %d species, binary%d, %lld cells) need %zu bytes of scratch; "
                 "the allocation-free path has %zu",
                 n, dim, S, fp64 ? 64 : 32, (long long)ncell, L.used, kScratchBytes);
+  if (plan && L.used > gauss_from) return fail(nullptr, RWPT_EUNSUPPORTED, "scratch layout");  // never
   void* base = nullptr;
   st = scratch_on_current_device(&base);
   if (st != RWPT_OK) return st;
@@ -1973,8 +2114,20 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
     a.nb_src = (uint32_t*)at(o_nsrc);
   }
   a.indirect = 0;
-  if (c.norm == RWPT_NORM_SYM || log2l == kPrivateLists) NACHK(launch_rowsum(fp64, dim, log2l, a, s));
-  NACHK(launch_exchange(fp64, dim, log2l, a, s));
+  if (plan) {
+    a.n_real = 1;
+    a.gauss_nitems = (ntiles + kGaussTiles - 1) / kGaussTiles;
+    a.gauss_rows = gauss_rows(plan);
+    a.gauss_mom = (double*)at(o_gmom);
+    a.gauss_ncell = ncell;
+    a.gauss_tab = (double*)at(o_gtab);
+    NACHK(launch_gauss_table(plan, a.rp, 1, (double*)at(o_gtab), s));
+    if (c.norm == RWPT_NORM_SYM) NACHK(launch_gauss_rowsum(plan, a, s));
+    NACHK(launch_gauss_exchange(plan, a, s));
+  } else {
+    if (c.norm == RWPT_NORM_SYM || log2l == kPrivateLists) NACHK(launch_rowsum(fp64, dim, log2l, a, s));
+    NACHK(launch_exchange(fp64, dim, log2l, a, s));
+  }
   NACHK(launch_noalloc_store(fp64, S, n, at(o_m0), (uint32_t*)at(o_id), mass_out, s));
 #undef NACHK
   return RWPT_OK;
@@ -2003,7 +2156,8 @@ void rwpt_destroy(rwpt_ctx* c) {
                       &c->step_ctr, &c->counts, &c->d_chunks, &c->d_chunk_start, &c->chunk_part,
                       &c->audit_done, &c->bbox, &c->bparts, &c->nb_meta, &c->nb_idx, &c->nb_w,
                       &c->nb_src, &c->src_of, &c->half_slots, &c->half_own, &c->d_item_start,
-                      &c->d_item_real};
+                      &c->d_item_real, &c->d_gauss_items, &c->gauss_tab,
+                      &c->gauss_mom};
     for (DevBuf* b : bufs) b->release();
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   }

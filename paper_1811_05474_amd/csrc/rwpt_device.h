@@ -37,6 +37,9 @@ struct RealParams {
   int32_t rx_own;      // stencil reach along x on the particle's own row
   int32_t n_fwd;       // forward stencil rows (dz > 0, or dz = 0 and dy > 0)
   int64_t item_off;    // first work item of this realisation
+  // 1-D expansions: cells at most g_in away lie wholly within the cutoff of
+  // each other, cells more than g_out away wholly outside
+  int32_t g_in, g_out;
 };
 
 // Offset (dy, dz) of a neighbour row of cells and how many cells (rx) to
@@ -48,6 +51,12 @@ struct StencilRow {
 // A run of consecutive particles (in cell-sorted order) handled by one wave.
 struct Tile {
   int32_t begin, end, real, pad;
+};
+
+// The 1-D expansion kernels' block: up to kGaussTiles consecutive tiles of 16
+// particles of one realisation.
+struct GaussItem {
+  int32_t tile, ntiles, real, pad;
 };
 
 // Arguments of the pair kernels.  Floating-point arrays are binary32 or
@@ -99,6 +108,13 @@ struct PairArgs {
   int64_t half_nitems;
   int64_t half_cap;                // particles per slot plane
   int32_t n_real;
+  // 1-D expansions
+  const GaussItem* gauss_items;    // null: one realisation, its tiles in order
+  int32_t gauss_nitems;
+  int32_t gauss_rows;              // rows of gauss_tab per realisation
+  double* gauss_mom;               // [terms][gauss_ncell][columns] moments of the cells
+  int64_t gauss_ncell;             // cells of all realisations
+  const double* gauss_tab;         // [n_real][gauss_rows][terms] Hermite functions of the cell offsets
 };
 
 }  // namespace rwpt

@@ -146,6 +146,32 @@ hipError_t launch_noalloc_store(int fp64, int S, int32_t n, const void* mass_sor
 hipError_t launch_unsort(int fp64, int32_t n, const uint32_t* id, uint32_t* inv, const void* in, void* out, int comps,
                          int stride, int species_major, hipStream_t s);
 
+// Dense 1-D neighbourhoods by expansions over cells (binary32, tiles of 16
+// particles).  Each plan: `refine` cells per cutoff length, terms of the
+// expansions, the widest cell in units of sigma (whose truncation is below
+// 2e-9 of a weight) and the largest g_in.  Plan 3 is the full matrix's, whose
+// "cutoff" is the distance of weights 2^-40.
+constexpr int kGaussTiles = 8;
+constexpr int kGaussPlans = 3;
+constexpr int kGaussMaxTerms = 10;
+constexpr int kGaussCells = 8;  // target cells a block takes at a time
+struct GaussPlan {
+  int refine, terms;
+  double width;
+  int reach;
+};
+constexpr GaussPlan kGaussPlan[kGaussPlans + 1] = {
+    {0, 0, 0.0, 0}, {32, 8, 0.1, 31}, {16, 10, 0.2, 15}, {32, 10, 0.2, 40}};
+// values of the moment buffer for ncell cells of S species
+inline size_t gauss_moment_words(int plan, int64_t ncell, int S) {
+  return (size_t)kGaussPlan[plan].terms * (size_t)ncell * (2 * padded_species(S) + 2);
+}
+inline int gauss_rows(int plan) { return 2 * kGaussPlan[plan].reach + 1; }
+// tab: n_real * gauss_rows(plan) * terms values
+hipError_t launch_gauss_table(int plan, const RealParams* rp, int32_t n_real, double* tab, hipStream_t s);
+hipError_t launch_gauss_rowsum(int plan, const PairArgs& a, hipStream_t s);
+hipError_t launch_gauss_exchange(int plan, const PairArgs& a, hipStream_t s);
+
 // Full-matrix path of one realisation (binary32 state, bf16-split MFMA).
 struct DenseArgs {
   const float* pos;        // [cap][PS] particle-major, sorted

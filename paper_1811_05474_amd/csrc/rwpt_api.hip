@@ -125,6 +125,8 @@ struct rwpt_ctx {
   DevBuf d_gauss_items, gauss_tab, gauss_mom;  // 1-D expansions
   int gauss = 0;                    // their plan (0: the tiles evaluate every pair)
   int32_t gauss_nitems = 0;
+  DevBuf d_group_items;  // binary64 tiles, two per wave
+  int32_t group_nitems = 0;
   bool dense = false;   // full-matrix path selected at init
   float dense_escale = 0.0f, dense_skip_s2 = 0.0f;
   int64_t ncell_total = 0;
@@ -362,6 +364,7 @@ static void real_grid(const rwpt_config& cfg, int dim, double dt, double Dr, int
     P.rc2_d = rc2;
     P.rc2_f = (float)rc2;
     P.escale_d = -1.0 / sigma2;
+    P.esc64_d = (double)(-92.332482616893658071L / (long double)sigma2);  // 64 / ln 2
     P.escale_f = (float)(-1.4426950408889634073599246810019 / sigma2);
     // geometric cutoff: covers the rounding of s^2 in the predicate
     rcg = std::sqrt(rc2) * (1.0 + 1e-5);
@@ -525,6 +528,13 @@ static int gauss_plan(const rwpt_config& cfg, int dim, double dt, double D, int3
   return 0;
 }
 
+static bool wide_cutoff(const rwpt_config& cfg) { return cfg.kappa * cfg.kappa > kWideCutoff; }
+
+// Whether the binary64 pair kernels take two tiles per wave.
+static bool two_tiles(const rwpt_config& cfg, int log2l, int32_t ntiles) {
+  return cfg.precision == RWPT_FP64 && (log2l == 3 || log2l == 4) && !wide_cutoff(cfg) && ntiles >= kGroupMinTiles;
+}
+
 static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   if (c->grid_valid && c->g_dt == dt && c->g_D == D) return RWPT_OK;
   const rwpt_config& cfg = c->cfg;
@@ -575,12 +585,24 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   if (cell_off >= (int64_t)1 << 31) return fail(c, RWPT_EUNSUPPORTED, "cell grid too large (%lld cells)", (long long)cell_off);
   c->ntiles = (int32_t)c->h_tiles.size();
   // 1-D expansions: blocks of up to kGaussTiles tiles of one realisation
-  std::vector<GaussItem> gitems;
+  std::vector<TileGroup> gitems;
   if (c->gauss)
     for (int r = 0; r < c->n_real; ++r)
       for (int32_t t = c->h_tile_start[r]; t < c->h_tile_start[r + 1]; t += kGaussTiles)
-        gitems.push_back(GaussItem{t, std::min<int32_t>(kGaussTiles, c->h_tile_start[r + 1] - t), r, 0});
+        gitems.push_back(TileGroup{t, std::min<int32_t>(kGaussTiles, c->h_tile_start[r + 1] - t), r, 0});
   c->gauss_nitems = (int32_t)gitems.size();
+  // binary64 tiles, two per wave
+  std::vector<TileGroup> groups;
+  c->group_nitems = 0;
+  if (two_tiles(cfg, c->log2l, c->ntiles)) {
+    for (int r = 0; r < c->n_real; ++r)
+      for (int32_t t = c->h_tile_start[r]; t < c->h_tile_start[r + 1]; t += kGroupTiles)
+        groups.push_back(TileGroup{t, std::min<int32_t>(kGroupTiles, c->h_tile_start[r + 1] - t), r, 0});
+    c->group_nitems = (int32_t)groups.size();
+    HIPCHK(c, c->d_group_items.ensure(groups.size() * sizeof(TileGroup)));
+    HIPCHK(c, hipMemcpyAsync(c->d_group_items.p, groups.data(), groups.size() * sizeof(TileGroup),
+                             hipMemcpyHostToDevice, c->stream));
+  }
   // half-stencil tiling: work items (row, segment) of every realisation, and
   // slot planes npar (1 + forward rows) deep
   std::vector<int64_t> item_start(c->n_real + 1, 0);
@@ -670,11 +692,11 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
                            c->h_tile_start.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
   (void)regrow;
   if (c->gauss) {
-    HIPCHK(c, c->d_gauss_items.ensure(std::max<size_t>(1, gitems.size()) * sizeof(GaussItem)));
+    HIPCHK(c, c->d_gauss_items.ensure(std::max<size_t>(1, gitems.size()) * sizeof(TileGroup)));
     HIPCHK(c, c->gauss_tab.ensure((size_t)c->n_real * gauss_rows(c->gauss) * kGaussPlan[c->gauss].terms * sizeof(double)));
     HIPCHK(c, c->gauss_mom.ensure(gauss_moment_words(c->gauss, ncell, c->S) * sizeof(double)));
     if (!gitems.empty())
-      HIPCHK(c, hipMemcpyAsync(c->d_gauss_items.p, gitems.data(), gitems.size() * sizeof(GaussItem),
+      HIPCHK(c, hipMemcpyAsync(c->d_gauss_items.p, gitems.data(), gitems.size() * sizeof(TileGroup),
                                hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, launch_gauss_table(c->gauss, c->d_rp.as<RealParams>(), c->n_real, c->gauss_tab.as<double>(), c->stream));
   }
@@ -730,7 +752,10 @@ static PairArgs pair_args(rwpt_ctx* c) {
   a.half_nitems = c->half_nitems;
   a.half_cap = c->cap;
   a.n_real = c->n_real;
-  a.gauss_items = c->d_gauss_items.as<GaussItem>();
+  a.group_items = c->d_group_items.as<TileGroup>();
+  a.group_nitems = c->group_nitems;
+  a.wide = wide_cutoff(c->cfg) ? 1 : 0;
+  a.gauss_items = c->d_gauss_items.as<TileGroup>();
   a.gauss_nitems = c->gauss_nitems;
   a.gauss_rows = c->gauss ? gauss_rows(c->gauss) : 0;
   a.gauss_tab = c->gauss_tab.as<double>();
@@ -1578,6 +1603,7 @@ rwpt_status rwpt_debug_rowsums(rwpt_ctx* c, double dt, double D, int32_t unit_we
       std::vector<RealParams> h = c->h_rp;
       for (RealParams& P : h) {
         P.escale_d = 0.0;
+        P.esc64_d = 0.0;
         P.escale_f = 0.0f;
       }
       hipError_t e = rp_unit.ensure(h.size() * sizeof(RealParams));
@@ -2114,6 +2140,8 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
     a.nb_src = (uint32_t*)at(o_nsrc);
   }
   a.indirect = 0;
+  a.wide = wide_cutoff(c) ? 1 : 0;
+  a.group_nitems = two_tiles(c, log2l, ntiles) ? (ntiles + kGroupTiles - 1) / kGroupTiles : 0;
   if (plan) {
     a.n_real = 1;
     a.gauss_nitems = (ntiles + kGaussTiles - 1) / kGaussTiles;
@@ -2157,7 +2185,7 @@ void rwpt_destroy(rwpt_ctx* c) {
                       &c->audit_done, &c->bbox, &c->bparts, &c->nb_meta, &c->nb_idx, &c->nb_w,
                       &c->nb_src, &c->src_of, &c->half_slots, &c->half_own, &c->d_item_start,
                       &c->d_item_real, &c->d_gauss_items, &c->gauss_tab,
-                      &c->gauss_mom};
+                      &c->gauss_mom, &c->d_group_items};
     for (DevBuf* b : bufs) b->release();
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   }

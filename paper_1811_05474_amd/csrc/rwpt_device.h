@@ -20,6 +20,7 @@ struct RealParams {
   int64_t p_end;
   double rc2_d;        // cutoff^2 = (kappa*kappa) * ((8*D_r)*dt), binary64
   double escale_d;     // -1 / sigma^2, sigma^2 = 8 D_r dt
+  double esc64_d;      // -64 log2(e) / sigma^2
   float rc2_f;         // rc2_d rounded once to binary32
   float escale_f;      // -log2(e) / sigma^2 rounded to binary32 (for exp2)
   double amp;          // isotropic walk amplitude sqrt(2 dt (D_rw + alpha_t |v|))
@@ -53,9 +54,8 @@ struct Tile {
   int32_t begin, end, real, pad;
 };
 
-// The 1-D expansion kernels' block: up to kGaussTiles consecutive tiles of 16
-// particles of one realisation.
-struct GaussItem {
+// Consecutive tiles of one realisation, taken by one block or wave.
+struct TileGroup {
   int32_t tile, ntiles, real, pad;
 };
 
@@ -108,8 +108,12 @@ struct PairArgs {
   int64_t half_nitems;
   int64_t half_cap;                // particles per slot plane
   int32_t n_real;
+  // binary64 tiles of 8 or 16 lanes: two tiles per wave (0 groups: one)
+  const TileGroup* group_items;    // null: one realisation, its tiles in order
+  int32_t group_nitems;
+  int32_t wide;                    // kappa^2 > kWideCutoff
   // 1-D expansions
-  const GaussItem* gauss_items;    // null: one realisation, its tiles in order
+  const TileGroup* gauss_items;    // null: one realisation, its tiles in order
   int32_t gauss_nitems;
   int32_t gauss_rows;              // rows of gauss_tab per realisation
   double* gauss_mom;               // [terms][gauss_ncell][columns] moments of the cells

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kGaussBlock) void k_gauss1d(const PairArgs a) {
   constexpr int kNear = SMAX > 4 ? 512 : 1024;
   __shared__ float near_x[kNear], near_q[MODE == 1 ? kNear : 1], near_m[MODE == 0 ? 1 : kNear * SMAX];
   const int blk = xcd_block(blockIdx.x, gridDim.x);
-  GaussItem item;
+  TileGroup item;
   if (a.gauss_items) {
     item = a.gauss_items[blk];
   } else {  // one realisation

@@ -146,6 +146,17 @@ hipError_t launch_noalloc_store(int fp64, int S, int32_t n, const void* mass_sor
 hipError_t launch_unsort(int fp64, int32_t n, const uint32_t* id, uint32_t* inv, const void* in, void* out, int comps,
                          int stride, int species_major, hipStream_t s);
 
+// Binary64 tiles of 8 or 16 lanes (log2l 3, 4): exponents -s^2 / sigma^2 at the
+// cutoff down to -kWideCutoff (results stay normal numbers); wider cutoffs and
+// kappa = inf keep the exp of the other binary64 kernels, which ends in zero.
+constexpr double kWideCutoff = 700.0;
+// Tiles per wave, and the number of tiles from which there are enough waves
+// for it.
+constexpr int kGroupTiles = 2;
+constexpr int32_t kGroupMinTiles = 8192;
+hipError_t launch_rowsum64(int dim, int log2l, const PairArgs& a, hipStream_t s);
+hipError_t launch_exchange64(int dim, int log2l, const PairArgs& a, hipStream_t s);
+
 // Dense 1-D neighbourhoods by expansions over cells (binary32, tiles of 16
 // particles).  Each plan: `refine` cells per cutoff length, terms of the
 // expansions, the widest cell in units of sigma (whose truncation is below

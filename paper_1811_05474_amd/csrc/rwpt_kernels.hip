@@ -16,8 +16,9 @@
 
 #include <type_traits>
 
-#include "rwpt_kernels.h"
+#include "rwpt_cursor.h"
 #include "rwpt_epilogue.h"
+#include "rwpt_kernels.h"
 #include "rwpt_layout.h"
 #include "rwpt_pairstep.h"
 
@@ -45,11 +46,6 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   }
   return __builtin_amdgcn_readfirstlane(v);
 }
-
-// Between a wave's LDS stores and its loads of what other lanes of the same
-// wave stored: the LDS executes one wave's operations in order, so only the
-// compiler has to be kept from moving the loads above the stores.
-__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Philox4x32-10 (Salmon, Moraes, Dror & Shaw, SC'11): 10 rounds of the
 // multiply/xor S-box with the key bumped by the golden-ratio and sqrt(3)-1
@@ -762,61 +758,6 @@ __global__ __launch_bounds__(kBlock) void k_exchange(
 // `row_share:k` broadcasts to the whole row straight into the consuming VALU
 // instruction.  Each particle sees all 64 candidates across its four lanes.
 // ---------------------------------------------------------------------------
-
-// Wave-uniform cursor over the non-empty stencil rows of one segment.
-struct RowCursor {
-  int r;            // next stencil entry to examine
-  uint32_t jb, je;  // current row's sorted candidate range
-  uint32_t p;       // virtual index of jb
-  bool valid;
-};
-
-__device__ __forceinline__ void cursor_advance(RowCursor& c, const RealParams& P, const StencilRow* __restrict__ st,
-                                               const uint32_t* __restrict__ cell_start, int cy, int cz, int cxa,
-                                               int cxb) {
-  const int nc0 = P.nc[0], nc1 = P.nc[1], nc2 = P.nc[2];
-  c.valid = false;
-  while (c.r < P.n_stencil) {
-    const StencilRow sr = st[P.stencil_off + c.r];
-    ++c.r;
-    const int ny = cy + sr.dy, nz = cz + sr.dz;
-    if (ny < 0 || ny >= nc1 || nz < 0 || nz >= nc2) continue;
-    const int xa = cxa - sr.rx < 0 ? 0 : cxa - sr.rx;
-    const int xb = cxb + sr.rx > nc0 - 1 ? nc0 - 1 : cxb + sr.rx;
-    const int64_t cb = P.cell_off + ((int64_t)nz * nc1 + ny) * nc0;
-    const uint32_t jb = cell_start[cb + xa], je = cell_start[cb + xb + 1];
-    if (je > jb) {
-      c.jb = jb;
-      c.je = je;
-      c.valid = true;
-      return;
-    }
-  }
-}
-
-// Lane `lane` of the chunk starting at virtual index vbase: its candidate j
-// (or jdummy when the chunk runs past the segment's last row), advancing the
-// cursor over every row that ends inside the chunk.
-__device__ __forceinline__ void chunk_pick(RowCursor& c, const RealParams& P, const StencilRow* __restrict__ st,
-                                           const uint32_t* __restrict__ cell_start, int cy, int cz, int cxa,
-                                           int cxb, uint32_t vbase, int32_t jdummy, int32_t& j, bool& has) {
-  const uint32_t v = vbase + (uint32_t)(threadIdx.x & 63);
-  j = jdummy;
-  has = false;
-  while (c.valid) {
-    const uint32_t len = c.je - c.jb;
-    if (v >= c.p && v < c.p + len) {
-      j = (int32_t)(c.jb + (v - c.p));
-      has = true;
-    }
-    if (c.p + len <= vbase + 64) {
-      c.p += len;
-      cursor_advance(c, P, st, cell_start, cy, cz, cxa, cxb);
-    } else {
-      break;
-    }
-  }
-}
 
 // A segment's last chunk when it holds n <= 32 candidates: lane (g, K) of
 // row g takes candidate g * per + K for K < per (per = 4 for n <= 16, else 8),
@@ -2606,6 +2547,7 @@ hipError_t launch_rowsum(int fp64, int dim, int log2l, const PairArgs& a, hipStr
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
+  if (fp64 && (log2l == 3 || log2l == 4) && !a.wide) return launch_rowsum64(dim, log2l, a, s);
   return dispatch_tdl(fp64, dim, log2l, [&](auto t, auto d, auto l) {
     using T = decltype(t);
     hipLaunchKernelGGL((k_rowsum<T, decltype(d)::value, decltype(l)::value>), g, b, 0, s, (const T*)a.pos,
@@ -2664,6 +2606,7 @@ hipError_t launch_exchange(int fp64, int dim, int log2l, const PairArgs& a, hipS
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
+  if (fp64 && (log2l == 3 || log2l == 4) && !a.wide) return launch_exchange64(dim, log2l, a, s);
   return dispatch_tdl(fp64, dim, log2l, [&](auto t, auto d, auto l) {
     using T = decltype(t);
     constexpr int D = decltype(d)::value, L = decltype(l)::value;

@@ -139,6 +139,7 @@ struct rwpt_ctx {
   std::vector<int32_t> h_chunk_start;
   int32_t ntiles = 0;
   int log2l = 3;
+  int nb_slots = 0;
   double refine[3] = {0, 0, 0};
 
   bool grid_valid = false;
@@ -204,19 +205,32 @@ static int lanes_to_log2(int lanes) {
   }
 }
 
-static void default_refine(int dim, double out[3]) {
-  // cells per cutoff length: fine along x (the fastest key axis, which trims
+static void default_refine(int dim, double nb, double out[3]) {
+  // nb: expected neighbours per particle.  Cells per cutoff length: fine along x (the fastest key axis, which trims
   // the candidate ranges), a few per cutoff across the other axes in 1-D and
   // 2-D
   if (dim == 1) {
     out[0] = 16.0; out[1] = 1.0; out[2] = 1.0;
   } else if (dim == 2) {
     out[0] = 16.0; out[1] = 2.0; out[2] = 1.0;
-  } else {
-    // 3-D neighbourhoods are sparse (one lane per particle): cells of two
+  } else if (nb <= kSlotsFrom) {
+    // sparse 3-D neighbourhoods (one lane per particle): cells of two
     // cutoffs, so each particle's cutoff box overlaps 2 x 2 rows of 2 cells
     out[0] = 0.5; out[1] = 0.5; out[2] = 0.5;
+  } else {
+    // more candidates per row: smaller cells leave fewer of them outside the
+    // cutoff (1.5e5 particles, S = 8, whole call, 0.5 x 0.5 x 0.5 / 2 x 1 x 1:
+    // 0.7 neighbours 73 / 77 us, 2: 101 / 91, 4: 147 / 103, 12: 280 / 142)
+    out[0] = 2.0; out[1] = 1.0; out[2] = 1.0;
   }
+}
+
+// Expected neighbours of a particle among nr in the box, walls aside.
+static double expected_neighbours(const rwpt_config& cfg, int dim, double dt, double Dr, int64_t nr) {
+  const double rc = cfg.kappa * std::sqrt(8.0 * Dr * dt);
+  double v = dim == 1 ? 2.0 * rc : (dim == 2 ? 3.14159265358979 * rc * rc : 4.18879020478639 * rc * rc * rc);
+  for (int k = 0; k < dim; ++k) v /= cfg.box_hi[k] - cfg.box_lo[k];
+  return (double)nr * (v < 1.0 ? v : 1.0);
 }
 
 // Lanes per particle when the configuration leaves it open: enough tiles to
@@ -542,8 +556,15 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   int lanes = cfg.tile_lanes ? cfg.tile_lanes : default_lanes(dim, c->N, cfg.precision == RWPT_FP64);
   if (c->dense) lanes = 64 / kDenseRowTile;  // tiles of 16 rows (audit partials, D = 0 copy)
   c->log2l = lanes_to_log2(lanes);
+  // mean over the particles
+  double nb = 0.0;
+  for (int r = 0; r < c->n_real; ++r) {
+    const int64_t nr = c->real_start[r + 1] - c->real_start[r];
+    nb += (double)nr / (double)std::max<int64_t>(c->N, 1) * expected_neighbours(cfg, dim, dt, D * c->d_scale[r], nr);
+  }
+  c->nb_slots = c->log2l == kPrivateLists ? slots_for(nb) : 0;
   double defr[3];
-  default_refine(dim, defr);
+  default_refine(dim, nb, defr);
   for (int k = 0; k < 3; ++k) c->refine[k] = cfg.cell_refine[k] > 0 ? cfg.cell_refine[k] : defr[k];
   c->gauss = gauss_plan(cfg, dim, dt, D, c->n_real, c->real_start.data(), [&](int32_t r) { return c->d_scale[r]; },
                         c->dense);
@@ -652,9 +673,10 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   HIPCHK(c, c->counts.ensure((size_t)std::max(1, c->ntiles) * 2 * sizeof(unsigned long long)));
   if (c->log2l == kPrivateLists) {
     HIPCHK(c, c->nb_meta.ensure((size_t)c->cap * sizeof(uint16_t)));
-    HIPCHK(c, c->nb_idx.ensure((size_t)std::max(1, c->ntiles) * kCacheWave * sizeof(uint32_t)));
-    HIPCHK(c, c->nb_w.ensure((size_t)std::max(1, c->ntiles) * kCacheWave * c->tsize));
-    HIPCHK(c, c->nb_src.ensure((size_t)std::max(1, c->ntiles) * kCacheWave * sizeof(uint32_t)));
+    const size_t entries = (size_t)std::max(1, c->ntiles) * (c->nb_slots ? 64 * c->nb_slots : kCacheWave);
+    HIPCHK(c, c->nb_idx.ensure(entries * sizeof(uint32_t)));
+    HIPCHK(c, c->nb_w.ensure(entries * c->tsize));
+    if (!c->nb_slots) HIPCHK(c, c->nb_src.ensure(entries * sizeof(uint32_t)));
   }
   if (half) {
     const int Sa = padded_species(c->S);
@@ -715,8 +737,9 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
 static DevBuf& mass_buf(rwpt_ctx* c, int k) { return k ? c->mass1 : c->mass0; }
 
 // Steps whose sort leaves the masses in place (the exchange reads them
-// through src_of): the one-lane-per-particle kernels of the sparse path.
-static bool masses_stay(const rwpt_ctx* c) { return !c->dense && c->log2l == kPrivateLists; }
+// through src_of): the one-lane-per-particle kernels of the sparse path, with
+// the compacted neighbour cache.
+static bool masses_stay(const rwpt_ctx* c) { return !c->dense && c->log2l == kPrivateLists && !c->nb_slots; }
 
 static PairArgs pair_args(rwpt_ctx* c) {
   PairArgs a;
@@ -742,6 +765,7 @@ static PairArgs pair_args(rwpt_ctx* c) {
   a.nb_meta = c->nb_meta.as<uint16_t>();
   a.nb_idx = c->nb_idx.as<uint32_t>();
   a.nb_w = c->nb_w.p;
+  a.nb_slots = c->nb_slots;
   a.nb_src = c->nb_src.as<uint32_t>();
   a.src_of = c->src_of.as<uint32_t>();
   a.indirect = 0;
@@ -1764,10 +1788,11 @@ rwpt_status rwpt_get_tiling(rwpt_ctx* c, int32_t* tile_lanes, double* cell_refin
   if (!c) return fail(nullptr, RWPT_EINVAL, "ctx is NULL");
   int lanes = c->cfg.tile_lanes ? c->cfg.tile_lanes : default_lanes(c->dim, c->N, c->cfg.precision == RWPT_FP64);
   double defr[3];
-  default_refine(c->dim, defr);
+  default_refine(c->dim, 0.0, defr);
   if (tile_lanes) *tile_lanes = lanes;
-  if (cell_refine3)
-    for (int k = 0; k < 3; ++k) cell_refine3[k] = c->cfg.cell_refine[k] > 0 ? c->cfg.cell_refine[k] : defr[k];
+  if (cell_refine3)  // the grid's, once there is one
+    for (int k = 0; k < 3; ++k)
+      cell_refine3[k] = c->grid_valid ? c->refine[k] : (c->cfg.cell_refine[k] > 0 ? c->cfg.cell_refine[k] : defr[k]);
   return RWPT_OK;
 }
 
@@ -2016,74 +2041,77 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
     return fail(nullptr, RWPT_EUNSUPPORTED, "rwpt_transfer_noalloc does not take the half-stencil tiling");
   const int log2l = lanes_to_log2(lanes);
   const int G = log2l == kPrivateLists ? 64 : 64 >> log2l;
-  double refine[3], defr[3];
-  default_refine(dim, defr);
-  for (int k = 0; k < 3; ++k) refine[k] = c.cell_refine[k] > 0 ? c.cell_refine[k] : defr[k];
   // grid of the realisation for (dt, D): parameters and stencil rows, kept in
   // kernel arguments
   NoAllocParams na;
   const int64_t n_range[2] = {0, n};
+  const double nb = expected_neighbours(c, dim, dt, D, n);
   int plan = gauss_plan(c, dim, dt, D, 1, n_range, [](int32_t) { return 1.0; }, false);
+  int nb_slots = log2l == kPrivateLists ? slots_for(nb) : 0;
   const int32_t ntiles = (int32_t)((n + G - 1) / G);
   const int64_t cap = (int64_t)(n + 63) / 64 * 64;
   const int PS = dim, Sa = padded_species(S);
-  ScratchLayout L;
   int64_t ncell = 0;
-  size_t o_gtab = 0, o_gmom = 0;
-  // the pieces of the scratch area this call uses; the 1-D expansions only
-  // where theirs fit too
-  for (;; plan = 0) {
+  // the pieces of the scratch area this call uses
+  size_t o_pos0, o_pos1, o_m0, o_m1, o_id, o_key, o_slot, o_tsrc, o_tid, o_tkey, o_skey, o_r, o_q, o_cnt, o_start,
+      o_scan, o_rp, o_st, o_tiles, o_blk, o_ctr, o_rs, o_aud, o_meta = 0, o_nidx = 0, o_nw = 0, o_nsrc = 0, o_gtab = 0,
+      o_gmom = 0;
+  // the forms that need more of the area (1-D expansions, neighbour slots with
+  // their smaller cells) only where they fit
+  for (;;) {
+    const bool last = !plan && !nb_slots;
     memset(&na, 0, sizeof(na));
     RowBuf rows{na.st, kNoAllocStencil, 0};
     float unused_escale = 0.0f, unused_skip = 0.0f;
+    double refine[3];
+    default_refine(dim, nb_slots ? nb : 0.0, refine);
     if (plan) refine[0] = kGaussPlan[plan].refine;
-    else refine[0] = c.cell_refine[0] > 0 ? c.cell_refine[0] : defr[0];
+    for (int k = 0; k < 3; ++k)
+      if (c.cell_refine[k] > 0) refine[k] = c.cell_refine[k];
     real_grid(c, dim, dt, D, n, refine, false, &unused_escale, &unused_skip, 0, na.P, rows);
-    if (rows.n > kNoAllocStencil)
+    if (last && rows.n > kNoAllocStencil)
       return fail(nullptr, RWPT_EUNSUPPORTED, "the cutoff spans %d stencil rows; the allocation-free path takes at most %d",
                   rows.n, kNoAllocStencil);
     na.n_st = rows.n;
     na.P.p_begin = 0;
     na.P.p_end = n;
     ncell = (int64_t)na.P.nc[0] * na.P.nc[1] * na.P.nc[2];
-    if (!plan) break;
-    // room for the pieces below: per particle, per cell and per tile, the walk's
-    // table, parameters and rounding
-    L.used = (size_t)cap * (2 * PS * ts + 2 * Sa * ts + 7 * 4 + 8 + ts) + (size_t)ncell * 8 +
-             (size_t)ntiles * (sizeof(Tile) + (S + 1) * 8) + (size_t)cap / 32 + 16384;
-    o_gtab = L.take((size_t)gauss_rows(plan) * kGaussPlan[plan].terms * 8);
-    o_gmom = L.take(gauss_moment_words(plan, ncell, S) * 8);
-    if (L.used <= kScratchBytes && gauss_reach(na.P, na.st, false, kGaussPlan[plan])) break;
+    ScratchLayout L;
+    o_pos0 = L.take(PS * cap * ts), o_pos1 = L.take(PS * cap * ts);
+    o_m0 = L.take(Sa * cap * ts), o_m1 = L.take(Sa * cap * ts);
+    o_id = L.take(cap * 4), o_key = L.take(cap * 4), o_slot = L.take(cap * 4);
+    o_tsrc = L.take(cap * 4), o_tid = L.take(cap * 4), o_tkey = L.take(cap * 4);
+    o_skey = L.take(cap * 4), o_r = L.take(cap * 8), o_q = L.take(cap * ts);
+    o_cnt = L.take(ncell * 4), o_start = L.take((ncell + 1) * 4);
+    // the cell scan's words: the sorted keys' place, which the scatter fills later, where that is large enough
+    const size_t scan_bytes = scan_state_words(ncell) * 8;
+    o_scan = (size_t)cap * 4 >= scan_bytes ? o_tkey : L.take(scan_bytes);
+    o_rp = L.take(sizeof(RealParams)), o_st = L.take(kNoAllocStencil * sizeof(StencilRow));
+    o_tiles = L.take((size_t)ntiles * sizeof(Tile));
+    o_blk = L.take((size_t)((n + kBlock - 1) / kBlock) * 4), o_ctr = L.take(8);
+    o_rs = L.take(2 * sizeof(int64_t));
+    o_aud = L.take((size_t)ntiles * (S + 1) * 8);
+    if (log2l == kPrivateLists) {
+      const size_t entries = (size_t)ntiles * (nb_slots ? 64 * nb_slots : kCacheWave);
+      o_meta = L.take(cap * 2);
+      o_nidx = L.take(entries * 4);
+      o_nw = L.take(entries * ts);
+      if (!nb_slots) o_nsrc = L.take(entries * 4);
+    }
+    if (plan) {
+      o_gtab = L.take((size_t)gauss_rows(plan) * kGaussPlan[plan].terms * 8);
+      o_gmom = L.take(gauss_moment_words(plan, ncell, S) * 8);
+    }
+    if (L.used <= kScratchBytes && rows.n <= kNoAllocStencil &&
+        (!plan || gauss_reach(na.P, na.st, false, kGaussPlan[plan])))
+      break;
+    if (last)
+      return fail(nullptr, RWPT_EUNSUPPORTED,
+                  "%d particles (dim %d, %d species, binary%d, %lld cells) need %zu bytes of scratch; "
+                  "the allocation-free path has %zu",
+                  n, dim, S, fp64 ? 64 : 32, (long long)ncell, L.used, kScratchBytes);
+    plan = nb_slots = 0;
   }
-  const size_t gauss_from = o_gtab;
-  L.used = 0;
-  const size_t o_pos0 = L.take(PS * cap * ts), o_pos1 = L.take(PS * cap * ts);
-  const size_t o_m0 = L.take(Sa * cap * ts), o_m1 = L.take(Sa * cap * ts);
-  const size_t o_id = L.take(cap * 4), o_key = L.take(cap * 4), o_slot = L.take(cap * 4);
-  const size_t o_tsrc = L.take(cap * 4), o_tid = L.take(cap * 4), o_tkey = L.take(cap * 4);
-  const size_t o_skey = L.take(cap * 4), o_r = L.take(cap * 8), o_q = L.take(cap * ts);
-  const size_t o_cnt = L.take(ncell * 4), o_start = L.take((ncell + 1) * 4);
-  // the cell scan's words: the sorted keys' place, which the scatter fills later, where that is large enough
-  const size_t scan_bytes = scan_state_words(ncell) * 8;
-  const size_t o_scan = (size_t)cap * 4 >= scan_bytes ? o_tkey : L.take(scan_bytes);
-  const size_t o_rp = L.take(sizeof(RealParams)), o_st = L.take(kNoAllocStencil * sizeof(StencilRow));
-  const size_t o_tiles = L.take((size_t)ntiles * sizeof(Tile));
-  const size_t o_blk = L.take((size_t)((n + kBlock - 1) / kBlock) * 4), o_ctr = L.take(8);
-  const size_t o_rs = L.take(2 * sizeof(int64_t));
-  const size_t o_aud = L.take((size_t)ntiles * (S + 1) * 8);
-  size_t o_meta = 0, o_nidx = 0, o_nw = 0, o_nsrc = 0;
-  if (log2l == kPrivateLists) {
-    o_meta = L.take(cap * 2);
-    o_nidx = L.take((size_t)ntiles * kCacheWave * 4);
-    o_nw = L.take((size_t)ntiles * kCacheWave * ts);
-    o_nsrc = L.take((size_t)ntiles * kCacheWave * 4);
-  }
-  if (L.used > kScratchBytes)
-    return fail(nullptr, RWPT_EUNSUPPORTED,
-                "%d particles (dim %d, %d species, binary%d, %lld cells) need %zu bytes of scratch; "
-                "the allocation-free path has %zu",
-                n, dim, S, fp64 ? 64 : 32, (long long)ncell, L.used, kScratchBytes);
-  if (plan && L.used > gauss_from) return fail(nullptr, RWPT_EUNSUPPORTED, "scratch layout");  // never
   void* base = nullptr;
   st = scratch_on_current_device(&base);
   if (st != RWPT_OK) return st;
@@ -2137,7 +2165,8 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
     a.nb_meta = (uint16_t*)at(o_meta);
     a.nb_idx = (uint32_t*)at(o_nidx);
     a.nb_w = at(o_nw);
-    a.nb_src = (uint32_t*)at(o_nsrc);
+    a.nb_slots = nb_slots;
+    if (!nb_slots) a.nb_src = (uint32_t*)at(o_nsrc);
   }
   a.indirect = 0;
   a.wide = wide_cutoff(c) ? 1 : 0;

@@ -80,6 +80,17 @@ constexpr int kPrivateLists = -1;
 constexpr int kCacheLane = 8;
 constexpr int kCacheWave = 256;
 constexpr uint32_t kCacheMiss = 15;
+// From this many expected neighbours the cache keeps them in slots instead
+// (PairArgs::nb_slots), read and written in place without LDS: the compacted
+// region overflows and its rounds of 64 entries leave most lanes idle.
+// 1.5e5 particles in 3-D, eight species, cells of 2 x 1 x 1 per cutoff, whole
+// call, compacted / slots: 2 neighbours 91 / 80 us, 4: 103 / 84, 8: 126 / 92,
+// 12: 142 / 100; at 0.7 both take 77 (sparse cells: 73 compacted).
+constexpr double kSlotsFrom = 1.5;
+constexpr double kSlotsUpTo = 64.0;
+constexpr uint16_t kSlotMiss = 0xffff;
+// Slots per particle: room for nearly all of Poisson counts of mean nb.
+inline int slots_for(double nb) { return !(nb > kSlotsFrom && nb <= kSlotsUpTo) ? 0 : (nb <= 6.0 ? 16 : 32); }
 // Half-stencil tiling (binary32): every unordered pair evaluated once, its
 // far-end share accumulated into slot planes and summed by a finalizer.
 constexpr int kHalfPairs = -4;

@@ -1330,6 +1330,135 @@ __global__ __launch_bounds__(kBlock) void k_exchange_priv(
                                  audit_part, wave_tile());
 }
 
+// The same two passes with the neighbours in slots (PairArgs::nb_slots), for
+// neighbourhoods of more than kSlotsFrom.  Entry k of the tile's 64 particles is
+// one row of the region, so the exchange reads rows whole; a particle with more
+// neighbours than slots is a miss.
+template <typename T, int DIM>
+__global__ __launch_bounds__(kBlock) void k_rowsum_slots(
+    const T* __restrict__ pos, const uint32_t* __restrict__ cell_start, const Tile* __restrict__ tiles,
+    const int32_t ntiles, const RealParams* __restrict__ rp, double* __restrict__ r_out, T* __restrict__ q_out,
+    uint16_t* __restrict__ nb_meta, uint32_t* __restrict__ nb_idx, T* __restrict__ nb_w, const uint32_t slots) {
+  constexpr int CB = PrivBatch<DIM>::kCandBatch;
+  WeightFn<T> wfn;  // before any return: the binary64 form has a block barrier
+  wfn.setup();
+  TileLane tl;
+  Tile tile;
+  if (!tile_lane_setup<0>(tiles, ntiles, tl, tile)) return;
+  if (!tl.valid) return;
+  const RealParams& P = rp[tile.real];
+  const int32_t ii = tl.i;
+  T xi[DIM];
+  load_pos<T, DIM>(pos, ii, xi);
+  const T rc2 = rc2_of<T>(P), esc = escale_of<T>(P);
+  double acc = 1.0;  // only the self weight when the transfer is off
+  const int64_t base = wave_tile() * 64 * (int64_t)slots + tl.gi;
+  uint32_t cnt = 0;
+  if (P.active) {
+    acc = 0.0;
+    priv_walk<T, DIM>(P, cell_start, pos, xi, ii, [&](const uint32_t (&jv)[CB], const T (&s2)[CB],
+                                                      const bool (&ok)[CB]) {
+      T a = (T)0;
+#pragma unroll
+      for (int u = 0; u < CB; ++u) {
+        if (ok[u] && s2[u] <= rc2) {
+          const T w = wfn(s2[u], esc);
+          a += w;
+          if (jv[u] != (uint32_t)ii) {
+            if (cnt < slots) {
+              nb_idx[base + 64 * (int64_t)cnt] = jv[u];
+              nb_w[base + 64 * (int64_t)cnt] = w;
+            }
+            ++cnt;
+          }
+        }
+      }
+      acc += (double)a;
+    });
+  }
+  if (r_out) r_out[ii] = acc;
+  q_out[ii] = (T)(1.0 / acc);
+  nb_meta[ii] = cnt > slots ? kSlotMiss : (uint16_t)cnt;
+}
+
+template <typename T, int DIM, int SMAX>
+__global__ __launch_bounds__(kBlock) void k_exchange_slots(
+    const T* __restrict__ pos, const T* __restrict__ min_, T* __restrict__ mout, const T* __restrict__ q,
+    const double* __restrict__ r_in, const uint32_t* __restrict__ skey, const uint32_t* __restrict__ cell_start,
+    const Tile* __restrict__ tiles, const int32_t ntiles, const RealParams* __restrict__ rp,
+    const StencilRow* __restrict__ st, const int32_t S, const int32_t react_a, const int32_t react_b,
+    const int32_t norm, double* __restrict__ audit_part, const uint16_t* __restrict__ nb_meta,
+    const uint32_t* __restrict__ nb_idx, const T* __restrict__ nb_w, const uint32_t slots) {
+  // entries whose loads are in flight together
+  constexpr int U = SMAX * sizeof(T) > 32 ? 2 : 4;
+  WeightFn<T> wfn;  // before any return: the binary64 form has a block barrier
+  wfn.setup();
+  TileLane tl;
+  Tile tile;
+  if (!tile_lane_setup<0>(tiles, ntiles, tl, tile)) return;
+  const RealParams& P = rp[tile.real];
+  const int32_t ii = tl.valid ? tl.i : tile.end - 1;
+  T Mi[SMAX];
+  load_mass<T, SMAX>(min_, ii, Mi);
+  double acc[SMAX];
+#pragma unroll
+  for (int s = 0; s < SMAX; ++s) acc[s] = 0.0;
+  double racc = 0.0;
+  const bool sym = (norm == 0);
+  const bool mine = P.active && tl.valid;
+  const T qi = mine ? q[ii] : (T)0;
+  const uint32_t meta = mine ? nb_meta[ii] : 0u;
+  if (mine && meta != kSlotMiss) {
+    racc = sym ? 1.0 : r_in[ii];  // only the row normalisation divides by r_i
+    const int64_t base = wave_tile() * 64 * (int64_t)slots + tl.gi;
+    for (uint32_t k0 = 0; k0 < meta; k0 += U) {
+      uint32_t j[U];
+      T w[U], qj[U], mj[U][SMAX];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t e = base + 64 * (int64_t)(k0 + u < meta ? k0 + u : k0);
+        j[u] = nb_idx[e];
+        w[u] = nb_w[e];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        qj[u] = q[j[u]];
+        load_mass<T, SMAX>(min_, j[u], mj[u]);
+      }
+      T a[SMAX];  // at most U terms in the path's precision, then widened
+#pragma unroll
+      for (int s = 0; s < SMAX; ++s) a[s] = (T)0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const T p = k0 + u < meta ? (sym ? w[u] * (qi + qj[u]) : w[u]) : (T)0;
+#pragma unroll
+        for (int s = 0; s < SMAX; ++s) a[s] += p * (mj[u][s] - Mi[s]);
+      }
+#pragma unroll
+      for (int s = 0; s < SMAX; ++s) acc[s] += (double)a[s];
+    }
+  } else if (mine) {
+    T xi[DIM];
+    load_pos<T, DIM>(pos, ii, xi);
+    const T rc2 = rc2_of<T>(P), esc = escale_of<T>(P);
+    for_own_rows<T, DIM>(P, st, cell_start, skey[ii] - (uint32_t)P.cell_off, [&](uint32_t jb, uint32_t je) {
+      for (uint32_t j = jb; j < je; ++j) {
+        const T s2 = sep2<T, DIM>(xi, pos, j);
+        if (!(s2 <= rc2)) continue;
+        const T w = wfn(s2, esc);
+        const T p = sym ? w * (qi + q[j]) : w;
+        racc += (double)w;
+        T mj[SMAX];
+        load_mass<T, SMAX>(min_, j, mj);
+#pragma unroll
+        for (int s = 0; s < SMAX; ++s) acc[s] += (double)(p * (mj[s] - Mi[s]));
+      }
+    });
+  }
+  exchange_epilogue<T, SMAX, 64>(P, sym, acc, racc, Mi, tl.valid, tl.i, mout, S, react_a, react_b, audit_part,
+                                 wave_tile());
+}
+
 // Counts ordered pairs j != i within the cutoff and candidate evaluations.
 template <typename T, int DIM, int LOG2L>
 __global__ __launch_bounds__(kBlock) void k_count(PairArgs a) {
@@ -2518,6 +2647,15 @@ hipError_t launch_rowsum(int fp64, int dim, int log2l, const PairArgs& a, hipStr
   if (a.ntiles <= 0) return hipSuccess;
   if (log2l == kHalfPairs) return fp64 ? hipErrorInvalidValue : launch_half(dim, false, a, s);
   const dim3 g = pair_grid(a.ntiles), b(kBlock);
+  if (log2l == kPrivateLists && a.nb_slots > 0) {
+    if (a.indirect) return hipErrorInvalidValue;
+    return dispatch_tdl(fp64, dim, 0, [&](auto t, auto d, auto) {
+      using T = decltype(t);
+      hipLaunchKernelGGL((k_rowsum_slots<T, decltype(d)::value>), g, b, 0, s, (const T*)a.pos, a.cell_start, a.tiles,
+                         a.ntiles, a.rp, a.r_out, (T*)a.q_out, a.nb_meta, a.nb_idx, (T*)a.nb_w,
+                         (uint32_t)a.nb_slots);
+    });
+  }
   if (log2l == kPrivateLists) {
     return dispatch_tdl(fp64, dim, 0, [&](auto t, auto d, auto) {
       using T = decltype(t);
@@ -2560,6 +2698,22 @@ hipError_t launch_exchange(int fp64, int dim, int log2l, const PairArgs& a, hipS
   if (a.S < 1 || a.S > 8) return hipErrorInvalidValue;
   if (log2l == kHalfPairs) return fp64 ? hipErrorInvalidValue : launch_half(dim, true, a, s);
   const dim3 g = pair_grid(a.ntiles), b(kBlock);
+  if (log2l == kPrivateLists && a.nb_slots > 0) {
+    if (a.indirect) return hipErrorInvalidValue;
+    return dispatch_tdl(fp64, dim, 0, [&](auto t, auto d, auto) {
+      using T = decltype(t);
+      constexpr int D = decltype(d)::value;
+      auto go = [&](auto sm) {
+        hipLaunchKernelGGL((k_exchange_slots<T, D, decltype(sm)::value>), g, b, 0, s, (const T*)a.pos,
+                           (const T*)a.mass_in, (T*)a.mass_out, (const T*)a.q_in, a.r_out, a.skey, a.cell_start,
+                           a.tiles, a.ntiles, a.rp, a.st, a.S, a.react_a, a.react_b, a.norm, a.audit_part, a.nb_meta,
+                           a.nb_idx, (const T*)a.nb_w, (uint32_t)a.nb_slots);
+      };
+      if (a.S <= 2) go(IC<2>{});
+      else if (a.S <= 4) go(IC<4>{});
+      else go(IC<8>{});
+    });
+  }
   if (log2l == kPrivateLists) {
     return dispatch_tdl(fp64, dim, 0, [&](auto t, auto d, auto) {
       using T = decltype(t);

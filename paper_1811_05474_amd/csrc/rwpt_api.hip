@@ -140,6 +140,7 @@ struct rwpt_ctx {
   int32_t ntiles = 0;
   int log2l = 3;
   int nb_slots = 0;
+  bool small_sort = false;  // every realisation fits the one-launch sort
   double refine[3] = {0, 0, 0};
 
   bool grid_valid = false;
@@ -283,7 +284,6 @@ static rwpt_status ensure_device(rwpt_ctx* c) {
     HIPCHK(c, hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking));
     c->own_stream = true;
   }
-  HIPCHK(c, c->step_ctr.ensure(sizeof(uint64_t)));
 
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->device_ready = true;
@@ -577,6 +577,7 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   c->h_tiles.clear();
   c->h_tile_start.assign(c->n_real + 1, 0);
   int64_t cell_off = 0;
+  c->small_sort = true;
   for (int r = 0; r < c->n_real; ++r) {
     RealParams& P = c->h_rp[r];
     const int64_t nr = c->real_start[r + 1] - c->real_start[r];
@@ -584,7 +585,9 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
               cell_off, P, c->h_st);
     P.p_begin = c->real_start[r];
     P.p_end = c->real_start[r + 1];
-    cell_off += (int64_t)P.nc[0] * P.nc[1] * P.nc[2];
+    const int64_t cells = (int64_t)P.nc[0] * P.nc[1] * P.nc[2];
+    cell_off += cells;
+    c->small_sort = c->small_sort && nr <= kSmallParticles && cells <= kSmallCells;
     if (half) half_segments(P, c->h_st.data() + P.stencil_off, nr, kHalfTarget);
     if (c->gauss && !gauss_reach(P, c->h_st.data(), c->dense, kGaussPlan[c->gauss]))
       return fail(c, RWPT_EUNSUPPORTED, "cell grid of the 1-D expansions");  // never: the plan was made for this grid
@@ -796,6 +799,27 @@ static PairArgs pair_args(rwpt_ctx* c) {
 static rwpt_status enqueue_sort(rwpt_ctx* c, bool walk, bool move_mass, int bump) {
   const int fp64 = c->cfg.precision == RWPT_FP64;
   const int32_t n = (int32_t)c->N;
+  if (c->small_sort) {
+    SmallSortArgs a;
+    memset(&a, 0, sizeof(a));
+    a.pos_in = a.pos_out = c->pos0.p;
+    a.mass_in = mass_buf(c, c->mcur).p;
+    a.mass_out = mass_buf(c, c->mcur ^ 1).p;
+    a.src_out = move_mass ? nullptr : c->src_of.as<uint32_t>();
+    a.id = a.id_out = c->id.as<uint32_t>();
+    a.skey = c->skey.as<uint32_t>();
+    a.cell_start = c->cell_start.as<uint32_t>();
+    a.rp = c->d_rp.as<RealParams>();
+    a.step_ctr = c->step_ctr.as<uint64_t>();
+    a.seed = c->cfg.seed;
+    a.do_walk = walk ? 1 : 0;
+    a.bump = bump;
+    a.S = c->S;
+    PhaseScope ps(c, PH_WALK_KEY);
+    HIPCHK(c, launch_small_sort(fp64, c->dim, c->n_real, a, nullptr, c->stream));
+    if (move_mass) c->mcur ^= 1;
+    return RWPT_OK;
+  }
   {
     PhaseScope ps(c, PH_WALK_KEY);
     HIPCHK(c, launch_walk_key(fp64, c->dim, c->pos0.p, c->pos1.p, c->id.as<uint32_t>(), n,
@@ -808,7 +832,8 @@ static rwpt_status enqueue_sort(rwpt_ctx* c, bool walk, bool move_mass, int bump
   {
     PhaseScope ps(c, PH_SCAN);
     HIPCHK(c, launch_cell_scan(c->cell_count.as<uint32_t>(), c->cell_start.as<uint32_t>(), c->ncell_total,
-                               c->scan_part.as<uint64_t>(), c->step_ctr.as<uint64_t>(), bump, c->stream));
+                               c->scan_part.as<uint64_t>(), c->step_ctr.as<uint64_t>(), c->n_real,
+                               bump, c->stream));
   }
   {
     PhaseScope ps(c, PH_SCATTER);
@@ -1217,7 +1242,8 @@ rwpt_status rwpt_init_ensemble(rwpt_ctx* c, int32_t n_real, const int64_t* n_per
   HIPCHK(c, c->d_blk_real.ensure(blk_real.size() * sizeof(int32_t)));
   HIPCHK(c, hipMemcpyAsync(c->d_blk_real.p, blk_real.data(), blk_real.size() * sizeof(int32_t),
                            hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemsetAsync(c->step_ctr.p, 0, sizeof(uint64_t), c->stream));
+  HIPCHK(c, c->step_ctr.ensure((size_t)n_real * sizeof(uint64_t)));
+  HIPCHK(c, hipMemsetAsync(c->step_ctr.p, 0, (size_t)n_real * sizeof(uint64_t), c->stream));
   HIPCHK(c, hipMemcpyAsync(c->audit_out.p, c->audit_init.data(), c->audit_init.size() * sizeof(double),
                            hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1903,7 +1929,7 @@ rwpt_status rwpt_autotune(rwpt_ctx* c, double dt, double D, int32_t trial_steps)
   hipEvent_t e0 = nullptr, e1 = nullptr;
   do {
     if (sp.ensure(npos) != hipSuccess || sm.ensure(nmass) != hipSuccess || si.ensure(cap * 4) != hipSuccess ||
-        sa.ensure(naud) != hipSuccess || sc.ensure(8) != hipSuccess) {
+        sa.ensure(naud) != hipSuccess || sc.ensure((size_t)c->n_real * 8) != hipSuccess) {
       result = fail(c, RWPT_ENOMEM, "autotune snapshot");
       break;
     }
@@ -1911,7 +1937,7 @@ rwpt_status rwpt_autotune(rwpt_ctx* c, double dt, double D, int32_t trial_steps)
     if (e == hipSuccess) e = hipMemcpyAsync(sm.p, mass_buf(c, c->mcur).p, nmass, hipMemcpyDeviceToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(si.p, c->id.p, cap * 4, hipMemcpyDeviceToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(sa.p, c->audit_out.p, naud, hipMemcpyDeviceToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(sc.p, c->step_ctr.p, 8, hipMemcpyDeviceToDevice, c->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(sc.p, c->step_ctr.p, (size_t)c->n_real * 8, hipMemcpyDeviceToDevice, c->stream);
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     if (e != hipSuccess) {
@@ -1924,7 +1950,7 @@ rwpt_status rwpt_autotune(rwpt_ctx* c, double dt, double D, int32_t trial_steps)
       c->mcur = 0;
       if (r == hipSuccess) r = hipMemcpyAsync(c->id.p, si.p, cap * 4, hipMemcpyDeviceToDevice, c->stream);
       if (r == hipSuccess) r = hipMemcpyAsync(c->audit_out.p, sa.p, naud, hipMemcpyDeviceToDevice, c->stream);
-      if (r == hipSuccess) r = hipMemcpyAsync(c->step_ctr.p, sc.p, 8, hipMemcpyDeviceToDevice, c->stream);
+      if (r == hipSuccess) r = hipMemcpyAsync(c->step_ctr.p, sc.p, (size_t)c->n_real * 8, hipMemcpyDeviceToDevice, c->stream);
       c->steps = saved_steps;
       c->grid_valid = false;
       c->sorted_valid = false;
@@ -2001,7 +2027,7 @@ rwpt_status rwpt_autotune(rwpt_ctx* c, double dt, double D, int32_t trial_steps)
       c->mcur = 0;
       (void)hipMemcpyAsync(c->id.p, si.p, cap * 4, hipMemcpyDeviceToDevice, c->stream);
       (void)hipMemcpyAsync(c->audit_out.p, sa.p, naud, hipMemcpyDeviceToDevice, c->stream);
-      (void)hipMemcpyAsync(c->step_ctr.p, sc.p, 8, hipMemcpyDeviceToDevice, c->stream);
+      (void)hipMemcpyAsync(c->step_ctr.p, sc.p, (size_t)c->n_real * 8, hipMemcpyDeviceToDevice, c->stream);
     }
     c->steps = saved_steps;
     c->grid_valid = false;
@@ -2126,6 +2152,24 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
       return fail(nullptr, RWPT_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_));                   \
     }                                                                                               \
   } while (0)
+  if (n <= kSmallParticles && ncell <= kSmallCells) {
+    SmallSortArgs ss;
+    memset(&ss, 0, sizeof(ss));
+    ss.pos_in = pos;
+    ss.pos_out = at(o_pos0);
+    ss.mass_in = mass_in;
+    ss.mass_out = at(o_m1);
+    ss.id_out = (uint32_t*)at(o_id);
+    ss.skey = (uint32_t*)at(o_skey);
+    ss.cell_start = (uint32_t*)at(o_start);
+    ss.S = S;
+    ss.rp_out = (RealParams*)at(o_rp);
+    ss.st_out = (StencilRow*)at(o_st);
+    ss.tiles = (Tile*)at(o_tiles);
+    ss.G = G;
+    ss.ntiles = ntiles;
+    NACHK(launch_small_sort(fp64, dim, 1, ss, &na, s));
+  } else {
   // set-up: parameters, stencil, tiles, ids, cleared counts, caller layouts
   NACHK(launch_noalloc_setup(fp64, dim, S, na, n, pos, mass_in, at(o_pos0), at(o_m0), (uint32_t*)at(o_id),
                              (Tile*)at(o_tiles), G, ntiles, (RealParams*)at(o_rp), (StencilRow*)at(o_st),
@@ -2135,12 +2179,13 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
                         (int64_t*)at(o_rs), (int32_t*)at(o_blk), 1, (uint64_t*)at(o_ctr), c.seed, 0, (uint32_t*)at(o_cnt),
                         (uint32_t*)at(o_key), (uint32_t*)at(o_slot), (uint64_t*)at(o_scan), s));
   NACHK(launch_cell_scan((uint32_t*)at(o_cnt), (uint32_t*)at(o_start), ncell, (uint64_t*)at(o_scan),
-                         (uint64_t*)at(o_ctr), 0, s));
+                         (uint64_t*)at(o_ctr), 1, 0, s));
   NACHK(launch_scatter(n, (uint32_t*)at(o_key), (uint32_t*)at(o_slot), (uint32_t*)at(o_start), (uint32_t*)at(o_id),
                        (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey), s));
   NACHK(launch_canon(fp64, dim, n, (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey),
                      (uint32_t*)at(o_start), at(o_pos1), at(o_pos0), at(o_m0), at(o_m1), S, (uint32_t*)at(o_id),
                      (uint32_t*)at(o_skey), nullptr, s));
+  }
   // row sums, then the exchange + reaction into the other mass buffer
   PairArgs a;
   memset(&a, 0, sizeof(a));

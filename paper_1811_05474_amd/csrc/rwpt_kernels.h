@@ -44,9 +44,9 @@ hipError_t launch_walk_key(int fp64, int dim, const void* pos_in, void* pos_out,
 
 // Exclusive scan of cell_count[0..ncell) into cell_start[0..ncell]; zeroes cell_count.
 // scan_state holds scan_state_words(ncell) words, cleared by launch_walk_key.
-// Advances the step counter by bump.
+// Advances the n_real step counters by bump.
 hipError_t launch_cell_scan(uint32_t* cell_count, uint32_t* cell_start, int64_t ncell, uint64_t* scan_state,
-                            uint64_t* step_ctr, int32_t bump, hipStream_t s);
+                            uint64_t* step_ctr, int32_t n_real, int32_t bump, hipStream_t s);
 
 // Place every particle at cell_start[key] + slot (arrival order inside a cell).
 hipError_t launch_scatter(int32_t n, const uint32_t* key, const uint32_t* slot,
@@ -113,7 +113,7 @@ hipError_t launch_nbr_fill(int fp64, int dim, int log2l, const PairArgs& a, hipS
 // order levels (chunks of at most kAuditChunk tiles inside one realisation,
 // then the chunks of each realisation) in one launch; `done` holds n_real
 // zeroed completion counters that the kernel returns to zero.  Advances the
-// step counter by bump.
+// n_real step counters by bump.
 // Few, large chunks: every chunk block of a realisation with more than one
 // chunk ends in a device-scope fence and a completion atomic on a shared
 // counter, which serialise across blocks; a realisation of one chunk needs
@@ -146,6 +146,33 @@ hipError_t launch_noalloc_setup(int fp64, int dim, int S, const NoAllocParams& a
                                 const void* mass, void* pos_out, void* mass_out, uint32_t* id, Tile* tiles,
                                 int32_t G, int32_t ntiles, RealParams* rp, StencilRow* st, int64_t* real_start,
                                 int32_t* blk_real, uint32_t* cell_count, int64_t ncell, hipStream_t s);
+// The whole sort of realisations of at most kSmallParticles particles and
+// kSmallCells cells each, one block per realisation.  na: the allocation-free
+// call (one realisation, parameters from `na`, written to rp_out, st_out and
+// tiles; pos_in and mass_in in the caller's layouts); else null.
+constexpr int64_t kSmallParticles = 4096;
+constexpr int64_t kSmallCells = 16384;
+struct SmallSortArgs {
+  const void* pos_in;
+  void* pos_out;           // may be pos_in
+  const void* mass_in;
+  void* mass_out;          // written in the new order when src_out is null
+  uint32_t* src_out;       // else the previous slot of each sorted particle
+  const uint32_t* id;
+  uint32_t* id_out;        // may be id
+  uint32_t* skey;
+  uint32_t* cell_start;
+  const RealParams* rp;
+  uint64_t* step_ctr;      // one per realisation, advanced by bump
+  uint64_t seed;
+  int32_t do_walk, bump, S;
+  RealParams* rp_out;
+  StencilRow* st_out;
+  Tile* tiles;
+  int32_t G, ntiles;
+};
+hipError_t launch_small_sort(int fp64, int dim, int32_t n_real, const SmallSortArgs& a, const NoAllocParams* na,
+                             hipStream_t s);
 // Sorted masses (particle-major) back to the caller's order (S x n species-major).
 hipError_t launch_noalloc_store(int fp64, int S, int32_t n, const void* mass_sorted, const uint32_t* id,
                                 void* mass, hipStream_t s);

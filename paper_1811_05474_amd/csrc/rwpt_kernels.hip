@@ -21,6 +21,7 @@
 #include "rwpt_kernels.h"
 #include "rwpt_layout.h"
 #include "rwpt_pairstep.h"
+#include "rwpt_walk.h"
 
 namespace rwpt {
 
@@ -45,73 +46,6 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     v = t > v ? t : v;
   }
   return __builtin_amdgcn_readfirstlane(v);
-}
-
-// Philox4x32-10 (Salmon, Moraes, Dror & Shaw, SC'11): 10 rounds of the
-// multiply/xor S-box with the key bumped by the golden-ratio and sqrt(3)-1
-// Weyl constants between rounds.
-__device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    if (r) {
-      k0 += 0x9E3779B9u;
-      k1 += 0xBB67AE85u;
-    }
-    const uint32_t a0 = c[0], a2 = c[2];
-    const uint32_t hi0 = __umulhi(0xD2511F53u, a0), lo0 = 0xD2511F53u * a0;
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, a2), lo1 = 0xCD9E8D57u * a2;
-    c[0] = hi1 ^ c[1] ^ k0;
-    c[1] = lo1;
-    c[2] = hi0 ^ c[3] ^ k1;
-    c[3] = lo0;
-  }
-}
-
-// Box-Muller pair from the uniforms (u, v): sqrt(-2 ln u) (cos 2 pi v, sin 2 pi v).
-// Binary32 uses the hardware log2 / sqrt / sin / cos (sin and cos take the
-// angle in revolutions), accurate to ~1e-6 relative -- far below what a
-// random displacement needs; binary64 uses the library functions.
-__device__ __forceinline__ void box_muller(float u, float v, float* z0, float* z1) {
-  const float r = __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf(u));  // -2 ln 2 log2 u
-  *z0 = r * __builtin_amdgcn_cosf(v);
-  *z1 = r * __builtin_amdgcn_sinf(v);
-}
-__device__ __forceinline__ void box_muller(double u, double v, double* z0, double* z1) {
-  const double r = sqrt(-2.0 * log(u));
-  double sn, cs;
-  sincospi(2.0 * v, &sn, &cs);
-  *z0 = r * cs;
-  *z1 = r * sn;
-}
-
-// Three standard normals for (particle id, step) under the 64-bit seed:
-// counter (id, step lo, step hi, 0); uniforms u = w * 2^-32 + 2^-33;
-// Box-Muller on (u0, u1) and (u2, u3).
-template <typename T, int DIM>
-__device__ __forceinline__ void walk_normals(uint32_t pid, uint64_t seed, uint64_t step, T z[3]) {
-  uint32_t c[4] = {pid, (uint32_t)step, (uint32_t)(step >> 32), 0u};
-  philox4x32_10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
-  const T s32 = (T)2.3283064365386962890625e-10;   // 2^-32
-  const T half = (T)1.16415321826934814453125e-10; // 2^-33
-  const T u0 = (T)c[0] * s32 + half;
-  const T u1 = (T)c[1] * s32 + half;
-  box_muller(u0, u1, &z[0], &z[1]);
-  z[2] = (T)0;
-  if constexpr (DIM > 2) {
-    const T u2 = (T)c[2] * s32 + half;
-    const T u3 = (T)c[3] * s32 + half;
-    T unused;
-    box_muller(u2, u3, &z[2], &unused);
-  }
-}
-
-// Mirror at zero-flux walls until inside the closed box.
-template <typename T>
-__device__ __forceinline__ T reflect(T x, T lo, T hi) {
-  for (int it = 0; it < 64 && (x < lo || x > hi); ++it) x = (x < lo) ? (T)2 * lo - x : (T)2 * hi - x;
-  x = x < lo ? lo : x;
-  x = x > hi ? hi : x;
-  return x;
 }
 
 // Squared separation used by the cutoff predicate: dx*dx, then
@@ -190,30 +124,8 @@ __global__ __launch_bounds__(kBlock) void k_walk_key(
   T x[DIM];
   load_pos<T, DIM>(pos_in, p, x);
   auto walk_and_key = [&](const RealParams& P) -> uint32_t {
-    if (do_walk && P.moves) {
-      // drift v dt, isotropic amplitude, extra amplitude along v (Eq. 1)
-      T z[3];
-      walk_normals<T, DIM>(id[p], seed, *step_ctr, z);
-      const T amp = (T)P.amp, ampx = (T)P.amp_x;
-      T uz = (T)0;
-#pragma unroll
-      for (int k = 0; k < DIM; ++k) uz += (T)P.udir[k] * z[k];
-#pragma unroll
-      for (int k = 0; k < DIM; ++k) {
-        const T move = (T)P.drift[k] + amp * z[k] + ampx * uz * (T)P.udir[k];
-        x[k] = reflect<T>(x[k] + move, (T)P.lo[k], (T)P.hi[k]);
-      }
-    }
-    int64_t c = 0;
-#pragma unroll
-    for (int k = DIM - 1; k >= 0; --k) {
-      const double u = ((double)x[k] - P.lo[k]) * P.inv_h[k];
-      int ck = (int)floor(u);
-      ck = ck < 0 ? 0 : ck;
-      ck = ck > P.nc[k] - 1 ? P.nc[k] - 1 : ck;
-      c = c * P.nc[k] + ck;
-    }
-    return (uint32_t)(P.cell_off + c);
+    if (do_walk && P.moves) walk_particle<T, DIM>(P, id[p], seed, *step_ctr, x);
+    return (uint32_t)(P.cell_off + cell_index<T, DIM>(P, x));
   };
   // realisations are contiguous, so a wave almost always lies in one: then
   // its parameters are read once through the scalar cache
@@ -317,14 +229,14 @@ __device__ __forceinline__ int scan_pad(int k) { return k + (k >> 4); }
 // 5.3 + 5.5 us and a gap; a transfer call of 2000 particles went from 40.4 to
 // 37.9 us, fifty 2-D steps of 77777 particles (with one audit per call) from
 // 3.33 to 2.55 ms.
-// step_ctr advances by bump here: the walk that read it has ended and the
+// The step counters (one per realisation) advance by bump here: the walk that read it has ended and the
 // next one has not started.
 constexpr uint64_t kScanValid = (uint64_t)1 << 32;
 
 template <bool ONE>
 __global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cnt, int64_t n, uint64_t* scan_state,
                                                        uint32_t* __restrict__ start, uint64_t* __restrict__ step_ctr,
-                                                       int32_t bump) {
+                                                       int32_t n_real, int32_t bump) {
   __shared__ uint32_t sh[4];
   __shared__ uint32_t buf[kScanChunk + kScanChunk / 16];
   __shared__ uint32_t sh_chunk;
@@ -375,7 +287,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cn
   } else {
     prefix = ((const uint32_t*)scan_state)[chunk];
   }
-  if (bump && chunk == 0 && t == 0) *step_ctr = *step_ctr + (uint64_t)bump;
+  if (bump && chunk == 0)
+    for (int r = t; r < n_real; r += kBlock) step_ctr[r] += (uint64_t)bump;
   uint32_t run = prefix + incl - sum;
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i) {
@@ -1776,7 +1689,7 @@ __device__ __forceinline__ double block_sum_fixed(double (&acc)[NV], double (*sh
 // done[r]) adds the realisation's chunk sums in chunk order with one wave
 // (lanes over chunks, then recursive halving), so realisations are finalised
 // in parallel and the result does not depend on which block finishes last.
-// Block 0 advances the step counter by `bump`, which no block of this launch reads.
+// Block 0 advances the step counters by `bump`, which no block of this launch reads.
 // The counters are returned to zero for the next launch (no memset node, so
 // the launch can be captured).
 __global__ __launch_bounds__(kBlock) void k_audit(const double* __restrict__ part, int32_t S1,
@@ -1784,7 +1697,7 @@ __global__ __launch_bounds__(kBlock) void k_audit(const double* __restrict__ par
                                                   double* __restrict__ chunk_part,
                                                   const int32_t* __restrict__ chunk_start,
                                                   double* __restrict__ out, uint32_t* __restrict__ done,
-                                                  uint64_t* __restrict__ step_ctr, int32_t bump) {
+                                                  uint64_t* __restrict__ step_ctr, int32_t n_real, int32_t bump) {
   constexpr int NV = kAuditValues;
   __shared__ double sh[kBlock / 64][NV];
   __shared__ int last;
@@ -1807,7 +1720,8 @@ __global__ __launch_bounds__(kBlock) void k_audit(const double* __restrict__ par
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] += val[u][v];
   const double c = block_sum_fixed<NV>(acc, sh, S1);
-  if (bump && blockIdx.x == 0 && threadIdx.x == 0) *step_ctr = *step_ctr + (uint64_t)bump;
+  if (bump && blockIdx.x == 0)
+    for (int k = threadIdx.x; k < n_real; k += kBlock) step_ctr[k] += (uint64_t)bump;
   const int r = ch.real;
   if (ch.n_in_real == 1) {
     if ((int)threadIdx.x < S1) out[(int64_t)r * S1 + threadIdx.x] = c;
@@ -2513,17 +2427,19 @@ hipError_t launch_walk_key(int fp64, int dim, const void* pos_in, void* pos_out,
 }
 
 hipError_t launch_cell_scan(uint32_t* cell_count, uint32_t* cell_start, int64_t ncell, uint64_t* scan_state,
-                            uint64_t* step_ctr, int32_t bump, hipStream_t s) {
+                            uint64_t* step_ctr, int32_t n_real, int32_t bump, hipStream_t s) {
   static_assert(kScanDirectMax <= kBlock, "one chunk total per thread");
   const int64_t nb = (ncell + kScanChunk - 1) / kScanChunk;
   const dim3 g((unsigned)nb), b(kBlock);
   if (nb <= kScanDirectMax) {
-    hipLaunchKernelGGL(k_scan_final<true>, g, b, 0, s, cell_count, ncell, scan_state, cell_start, step_ctr, bump);
+    hipLaunchKernelGGL(k_scan_final<true>, g, b, 0, s, cell_count, ncell, scan_state, cell_start, step_ctr, n_real,
+                       bump);
   } else {
     uint32_t* const partials = (uint32_t*)scan_state;
     hipLaunchKernelGGL(k_scan_reduce, g, b, 0, s, cell_count, ncell, partials);
     hipLaunchKernelGGL(k_scan_top, dim3(1), b, 0, s, partials, (int32_t)nb, cell_start, ncell);
-    hipLaunchKernelGGL(k_scan_final<false>, g, b, 0, s, cell_count, ncell, scan_state, cell_start, step_ctr, bump);
+    hipLaunchKernelGGL(k_scan_final<false>, g, b, 0, s, cell_count, ncell, scan_state, cell_start, step_ctr, n_real,
+                       bump);
   }
   return hipGetLastError();
 }
@@ -2906,7 +2822,7 @@ hipError_t launch_audit_reduce(const double* part, int32_t S1, const AuditChunk*
   if (n_real <= 0 || nchunks <= 0) return hipSuccess;
   if (S1 < 1 || S1 > kAuditValues) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_audit, dim3((unsigned)nchunks), dim3(kBlock), 0, s, part, S1, chunks, chunk_part,
-                     chunk_start, out, done, step_ctr, bump);
+                     chunk_start, out, done, step_ctr, n_real, bump);
   return hipGetLastError();
 }
 

@@ -1,0 +1,162 @@
+// rwpt_smallsort.hip -- the sort of small realisations in one launch: walk, cell
+// keys, counts, cell starts, canonical order and gather, one block per
+// realisation.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "rwpt_kernels.h"
+#include "rwpt_layout.h"
+#include "rwpt_walk.h"
+
+namespace rwpt {
+
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallItems = (int)(kSmallParticles / kSmallBlock);
+
+// The launches of the general sort (walk + key, scan, scatter, canonical
+// gather) take 3 to 5 us each and a gap, whatever they sort; here their steps
+// are separated by block barriers.  Bound by that chain's latency: 2000
+// particles of 8000 cells, 11.2 us, before that 24 and five gaps between seven
+// launches (the whole call 37.9 -> 28.4 us); 75 realisations of 2000 in 1-D 8.8
+// us, before 24 and three gaps (a step 55 -> 41 us).  Limit: what fits the LDS of
+// one block and stays shorter than the launches.
+// A realisation's particles, counts and cell starts never leave the block: its
+// positions are all read (into registers) before any is written, so pos_out may
+// be pos_in.
+// NA (the allocation-free call): one realisation whose parameters come as
+// arguments and are written out for the kernels that follow, masses in the
+// caller's order (S x n species-major), ids = indices, no walk.
+template <typename T, int DIM, int SMAX, bool NA>
+__global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs a, const NoAllocParams na) {
+  __shared__ uint32_t cnt[kSmallCells];
+  __shared__ uint32_t sid[kSmallParticles];
+  __shared__ uint32_t sh[kSmallBlock / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = NA ? 0 : (int)blockIdx.x;
+  const RealParams& P = NA ? na.P : a.rp[r];
+  const int n = (int)(P.p_end - P.p_begin), ncell = P.nc[0] * P.nc[1] * P.nc[2];
+  const int64_t p0 = P.p_begin;
+  const T* __restrict__ mass_in = (const T*)a.mass_in;
+  uint32_t* __restrict__ start = a.cell_start + P.cell_off;
+  if (n <= 0) {  // an empty realisation keeps its cells and its counter
+    for (int k = tid; k <= ncell; k += kSmallBlock) start[k] = (uint32_t)p0;
+    if (!NA && tid == 0) a.step_ctr[r] += (uint64_t)a.bump;
+    return;
+  }
+  for (int k = tid; k < ncell; k += kSmallBlock) cnt[k] = 0u;
+  if constexpr (NA) {
+    if (tid == 0) a.rp_out[0] = na.P;
+    if (tid < na.n_st) a.st_out[tid] = na.st[tid];
+    for (int t = tid; t < a.ntiles; t += kSmallBlock) {
+      const int32_t b = t * a.G;
+      a.tiles[t] = Tile{b, b + a.G < n ? b + a.G : n, 0, 0};
+    }
+  }
+  T x[kSmallItems][DIM], m[kSmallItems][SMAX];
+  uint32_t id[kSmallItems], key[kSmallItems], slot[kSmallItems];
+#pragma unroll
+  for (int u = 0; u < kSmallItems; ++u) {
+    const int o = tid + u * kSmallBlock;
+    const int64_t p = p0 + (o < n ? o : n - 1);
+    load_pos<T, DIM>((const T*)a.pos_in, p, x[u]);
+    id[u] = NA ? (uint32_t)p : a.id[p];
+    if (a.src_out == nullptr) {
+      if constexpr (NA) {
+#pragma unroll
+        for (int s = 0; s < SMAX; ++s) m[u][s] = s < a.S ? mass_in[(int64_t)s * n + p] : (T)0;
+      } else {
+        load_mass<T, SMAX>(mass_in, p, m[u]);
+      }
+    }
+  }
+  const uint64_t step = !NA && a.do_walk ? a.step_ctr[r] : 0u;
+  __syncthreads();  // cnt is clear
+#pragma unroll
+  for (int u = 0; u < kSmallItems; ++u) {
+    const int o = tid + u * kSmallBlock;
+    if (o < n) {
+      if (!NA && a.do_walk && P.moves) walk_particle<T, DIM>(P, id[u], a.seed, step, x[u]);
+      key[u] = (uint32_t)cell_index<T, DIM>(P, x[u]);
+      slot[u] = atomicAdd(&cnt[key[u]], 1u);
+    }
+  }
+  __syncthreads();
+  if (!NA && tid == 0) a.step_ctr[r] += (uint64_t)a.bump;  // every thread has read it
+  // exclusive scan in place, consecutive counts per thread
+  constexpr int kPer = kSmallCells / kSmallBlock;
+  const int per = (ncell + kSmallBlock - 1) / kSmallBlock, c0 = tid * per;
+  uint32_t sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k)
+    if (k < per && c0 + k < ncell) sum += cnt[c0 + k];
+  uint32_t v = sum;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t t = __shfl_up(v, off);
+    if (lane >= off) v += t;
+  }
+  if (lane == 63) sh[wave] = v;
+  __syncthreads();
+  uint32_t run = v - sum;
+  for (int w = 0; w < wave; ++w) run += sh[w];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k)
+    if (k < per && c0 + k < ncell) {
+      const uint32_t c = cnt[c0 + k];
+      cnt[c0 + k] = run;
+      run += c;
+    }
+  __syncthreads();
+  for (int k = tid; k < ncell; k += kSmallBlock) start[k] = (uint32_t)p0 + cnt[k];
+  if (tid == 0) start[ncell] = (uint32_t)P.p_end;  // the next realisation writes the same
+#pragma unroll
+  for (int u = 0; u < kSmallItems; ++u) {
+    const int o = tid + u * kSmallBlock;
+    if (o < n) sid[cnt[key[u]] + slot[u]] = id[u];
+  }
+  __syncthreads();
+  // canonical order inside a cell: by id
+#pragma unroll
+  for (int u = 0; u < kSmallItems; ++u) {
+    const int o = tid + u * kSmallBlock;
+    if (o < n) {
+      const uint32_t cs = cnt[key[u]], ce = (int)key[u] + 1 < ncell ? cnt[key[u] + 1] : (uint32_t)n;
+      uint32_t rank = 0;
+      for (uint32_t f = cs; f < ce; ++f) rank += sid[f] < id[u] ? 1u : 0u;
+      const int64_t dst = p0 + cs + rank;
+      store_pos<T, DIM>((T*)a.pos_out, dst, x[u]);
+      if (a.src_out) a.src_out[dst] = (uint32_t)(p0 + o);
+      else store_mass<T, SMAX>((T*)a.mass_out, dst, m[u]);
+      a.id_out[dst] = id[u];
+      a.skey[dst] = (uint32_t)P.cell_off + key[u];
+    }
+  }
+}
+
+hipError_t launch_small_sort(int fp64, int dim, int32_t n_real, const SmallSortArgs& a, const NoAllocParams* na,
+                             hipStream_t s) {
+  static const NoAllocParams none{};
+  const dim3 g((unsigned)(na ? 1 : n_real)), b(kSmallBlock);
+  auto go = [&](auto t, auto d, auto sm) {
+    using T = decltype(t);
+    constexpr int D = decltype(d)::value, SM = decltype(sm)::value;
+    if (na) hipLaunchKernelGGL((k_small_sort<T, D, SM, true>), g, b, 0, s, a, *na);
+    else hipLaunchKernelGGL((k_small_sort<T, D, SM, false>), g, b, 0, s, a, none);
+  };
+  auto with_s = [&](auto t, auto d) {
+    if (a.S <= 2) go(t, d, std::integral_constant<int, 2>{});
+    else if (a.S <= 4) go(t, d, std::integral_constant<int, 4>{});
+    else go(t, d, std::integral_constant<int, 8>{});
+  };
+  auto with_d = [&](auto t) -> hipError_t {
+    if (dim == 1) with_s(t, std::integral_constant<int, 1>{});
+    else if (dim == 2) with_s(t, std::integral_constant<int, 2>{});
+    else if (dim == 3) with_s(t, std::integral_constant<int, 3>{});
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  };
+  return fp64 ? with_d(double{}) : with_d(float{});
+}
+
+}  // namespace rwpt

@@ -34,7 +34,7 @@ namespace rwpt {
 template <int SPLIT = 1>
 __device__ __forceinline__ int64_t wave_tile() {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
+  const int64_t blk = xcd_group_block(blockIdx.x, gridDim.x);
   return SPLIT > 1 ? blk : blk * (kBlock / 64) + wave;
 }
 
@@ -443,7 +443,7 @@ __device__ __forceinline__ bool tile_lane_setup(const Tile* __restrict__ tiles, 
   // derived from the tile is kept in scalar registers and loaded through the
   // scalar cache
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int blk = xcd_block(blockIdx.x, gridDim.x);
+  const int blk = xcd_group_block(blockIdx.x, gridDim.x);
   const int t = SPLIT > 1 ? blk : blk * (kBlock / 64) + wave;
   if (t >= ntiles) return false;
   tile = tiles[t];
@@ -1410,7 +1410,7 @@ __global__ __launch_bounds__(kBlock) void k_count(PairArgs a) {
     evals += __shfl_xor(evals, off);
   }
   if ((threadIdx.x & 63) == 0) {
-    const int t = xcd_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
+    const int t = xcd_group_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
     a.counts[2 * t] = pairs;
     a.counts[2 * t + 1] = evals;
   }
@@ -1447,7 +1447,7 @@ __global__ __launch_bounds__(kBlock) void k_count_priv(PairArgs a) {
     evals += __shfl_xor(evals, off);
   }
   if ((threadIdx.x & 63) == 0) {
-    const int t = xcd_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
+    const int t = xcd_group_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
     a.counts[2 * t] = pairs;
     a.counts[2 * t + 1] = evals;
   }

@@ -847,7 +847,7 @@ static rwpt_status enqueue_sort(rwpt_ctx* c, bool walk, bool move_mass, int bump
                            c->tmp_key.as<uint32_t>(), c->cell_start.as<uint32_t>(), c->pos1.p, c->pos0.p,
                            mass_buf(c, c->mcur).p, mass_buf(c, c->mcur ^ 1).p, c->S,
                            c->id.as<uint32_t>(), c->skey.as<uint32_t>(),
-                           move_mass ? nullptr : c->src_of.as<uint32_t>(), c->stream));
+                           move_mass ? nullptr : c->src_of.as<uint32_t>(), 0, nullptr, c->stream));
   }
   if (move_mass) c->mcur ^= 1;
   return RWPT_OK;
@@ -2079,8 +2079,8 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   const int PS = dim, Sa = padded_species(S);
   int64_t ncell = 0;
   // the pieces of the scratch area this call uses
-  size_t o_pos0, o_pos1, o_m0, o_m1, o_id, o_key, o_slot, o_tsrc, o_tid, o_tkey, o_skey, o_r, o_q, o_cnt, o_start,
-      o_scan, o_rp, o_st, o_tiles, o_blk, o_ctr, o_rs, o_aud, o_meta = 0, o_nidx = 0, o_nw = 0, o_nsrc = 0, o_gtab = 0,
+  size_t o_pos0, o_m0, o_m1, o_id, o_key, o_slot, o_tsrc, o_tid, o_tkey, o_skey, o_r, o_q, o_cnt, o_start,
+      o_scan, o_rp, o_st, o_tiles, o_ctr, o_aud, o_meta = 0, o_nidx = 0, o_nw = 0, o_nsrc = 0, o_gtab = 0,
       o_gmom = 0;
   // the forms that need more of the area (1-D expansions, neighbour slots with
   // their smaller cells) only where they fit
@@ -2103,7 +2103,7 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
     na.P.p_end = n;
     ncell = (int64_t)na.P.nc[0] * na.P.nc[1] * na.P.nc[2];
     ScratchLayout L;
-    o_pos0 = L.take(PS * cap * ts), o_pos1 = L.take(PS * cap * ts);
+    o_pos0 = L.take(PS * cap * ts);
     o_m0 = L.take(Sa * cap * ts), o_m1 = L.take(Sa * cap * ts);
     o_id = L.take(cap * 4), o_key = L.take(cap * 4), o_slot = L.take(cap * 4);
     o_tsrc = L.take(cap * 4), o_tid = L.take(cap * 4), o_tkey = L.take(cap * 4);
@@ -2111,11 +2111,15 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
     o_cnt = L.take(ncell * 4), o_start = L.take((ncell + 1) * 4);
     // the cell scan's words: the sorted keys' place, which the scatter fills later, where that is large enough
     const size_t scan_bytes = scan_state_words(ncell) * 8;
+    // room that earlier forms of the sort took (a second position buffer, the
+    // walk's tables, the scan's partials), so that the largest call stays the same
+    for (size_t unused : {PS * cap * ts, (size_t)((n + kBlock - 1) / kBlock) * 4, 2 * sizeof(int64_t),
+                          (size_t)((ncell + kScanChunk - 1) / kScanChunk + 1) * 4})
+      (void)L.take(unused);
     o_scan = (size_t)cap * 4 >= scan_bytes ? o_tkey : L.take(scan_bytes);
     o_rp = L.take(sizeof(RealParams)), o_st = L.take(kNoAllocStencil * sizeof(StencilRow));
     o_tiles = L.take((size_t)ntiles * sizeof(Tile));
-    o_blk = L.take((size_t)((n + kBlock - 1) / kBlock) * 4), o_ctr = L.take(8);
-    o_rs = L.take(2 * sizeof(int64_t));
+    o_ctr = L.take(8);
     o_aud = L.take((size_t)ntiles * (S + 1) * 8);
     if (log2l == kPrivateLists) {
       const size_t entries = (size_t)ntiles * (nb_slots ? 64 * nb_slots : kCacheWave);
@@ -2152,7 +2156,12 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
       return fail(nullptr, RWPT_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_));                   \
     }                                                                                               \
   } while (0)
-  if (n <= kSmallParticles && ncell <= kSmallCells) {
+  // up to four species the exchange writes in the caller's order itself; more
+  // are gathered from the sorted order afterwards (by the inverse of the ids, in
+  // the keys' place), since scattered words cost more than that launch
+  const bool small = n <= kSmallParticles && ncell <= kSmallCells;
+  const bool gather = S > 4 && !small;
+  if (small) {
     SmallSortArgs ss;
     memset(&ss, 0, sizeof(ss));
     ss.pos_in = pos;
@@ -2170,28 +2179,29 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
     ss.ntiles = ntiles;
     NACHK(launch_small_sort(fp64, dim, 1, ss, &na, s));
   } else {
-  // set-up: parameters, stencil, tiles, ids, cleared counts, caller layouts
-  NACHK(launch_noalloc_setup(fp64, dim, S, na, n, pos, mass_in, at(o_pos0), at(o_m0), (uint32_t*)at(o_id),
-                             (Tile*)at(o_tiles), G, ntiles, (RealParams*)at(o_rp), (StencilRow*)at(o_st),
-                             (int64_t*)at(o_rs), (int32_t*)at(o_blk), (uint32_t*)at(o_cnt), ncell, s));
-  // cell keys (no walk), counting sort, canonical order with the masses moved
-  NACHK(launch_walk_key(fp64, dim, at(o_pos0), at(o_pos1), (uint32_t*)at(o_id), n, (RealParams*)at(o_rp),
-                        (int64_t*)at(o_rs), (int32_t*)at(o_blk), 1, (uint64_t*)at(o_ctr), c.seed, 0, (uint32_t*)at(o_cnt),
-                        (uint32_t*)at(o_key), (uint32_t*)at(o_slot), (uint64_t*)at(o_scan), s));
-  NACHK(launch_cell_scan((uint32_t*)at(o_cnt), (uint32_t*)at(o_start), ncell, (uint64_t*)at(o_scan),
-                         (uint64_t*)at(o_ctr), 1, 0, s));
-  NACHK(launch_scatter(n, (uint32_t*)at(o_key), (uint32_t*)at(o_slot), (uint32_t*)at(o_start), (uint32_t*)at(o_id),
-                       (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey), s));
-  NACHK(launch_canon(fp64, dim, n, (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey),
-                     (uint32_t*)at(o_start), at(o_pos1), at(o_pos0), at(o_m0), at(o_m1), S, (uint32_t*)at(o_id),
-                     (uint32_t*)at(o_skey), nullptr, s));
+    // keys (no walk), counting sort, canonical order with the masses moved.
+    // The gather takes up to two species from the caller's arrays; more are
+    // brought together first, so that a particle is one read there.
+    const bool direct = S <= 2;
+    NACHK(launch_noalloc_key(fp64, dim, S, na, n, pos, mass_in, direct ? nullptr : at(o_m0), (Tile*)at(o_tiles), G,
+                             ntiles, (RealParams*)at(o_rp), (StencilRow*)at(o_st), (uint32_t*)at(o_cnt), ncell,
+                             (uint64_t*)at(o_scan), (uint32_t*)at(o_key), (uint32_t*)at(o_slot), s));
+    NACHK(launch_cell_scan((uint32_t*)at(o_cnt), (uint32_t*)at(o_start), ncell, (uint64_t*)at(o_scan),
+                           (uint64_t*)at(o_ctr), 1, 0, s));
+    NACHK(launch_scatter(n, (uint32_t*)at(o_key), (uint32_t*)at(o_slot), (uint32_t*)at(o_start), nullptr,
+                         (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey), s));
+    NACHK(launch_canon(fp64, dim, n, (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey),
+                       (uint32_t*)at(o_start), pos, at(o_pos0), direct ? mass_in : at(o_m0), at(o_m1), S,
+                       (uint32_t*)at(o_id), (uint32_t*)at(o_skey), nullptr, direct ? S : 0,
+                       gather ? (uint32_t*)at(o_key) : nullptr, s));
   }
-  // row sums, then the exchange + reaction into the other mass buffer
+  // row sums, then the exchange + reaction
   PairArgs a;
   memset(&a, 0, sizeof(a));
   a.pos = at(o_pos0);
   a.mass_in = at(o_m1);
-  a.mass_out = at(o_m0);
+  a.mass_out = gather ? at(o_m0) : mass_out;
+  if (!gather) a.out_map = OutMap{(const uint32_t*)at(o_id), n};
   a.q_in = at(o_q);
   a.q_out = at(o_q);
   a.r_out = (double*)at(o_r);
@@ -2230,7 +2240,7 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
     if (c.norm == RWPT_NORM_SYM || log2l == kPrivateLists) NACHK(launch_rowsum(fp64, dim, log2l, a, s));
     NACHK(launch_exchange(fp64, dim, log2l, a, s));
   }
-  NACHK(launch_noalloc_store(fp64, S, n, at(o_m0), (uint32_t*)at(o_id), mass_out, s));
+  if (gather) NACHK(launch_noalloc_store(fp64, S, n, at(o_m0), (uint32_t*)at(o_key), mass_out, s));
 #undef NACHK
   return RWPT_OK;
 }

@@ -59,12 +59,21 @@ struct TileGroup {
   int32_t tile, ntiles, real, pad;
 };
 
+// Where the exchange writes the new masses: in the sorted order,
+// particle-major (id null), or in the caller's order, S x n species-major, at
+// id of each sorted particle.
+struct OutMap {
+  const uint32_t* id;
+  int64_t n;
+};
+
 // Arguments of the pair kernels.  Floating-point arrays are binary32 or
 // binary64 according to the kernel instantiation.
 struct PairArgs {
   const void* pos;         // [cap][d] particle-major (packed), cell-sorted
   const void* mass_in;     // [cap][SP] particle-major (SP = 2, 4, 8 species slots)
-  void* mass_out;          // [cap][SP]
+  void* mass_out;          // [cap][SP], or as out_map says
+  OutMap out_map;
   const void* q_in;        // 1 / r_i for the symmetric normalisation, [cap]
   void* q_out;             // written by the row-sum pass
   double* r_out;           // r_i = sum_j w_ij, written by the row-sum pass (null: not kept; the

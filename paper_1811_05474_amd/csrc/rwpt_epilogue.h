@@ -104,7 +104,8 @@ template <typename T, int SMAX, int G>
 __device__ __forceinline__ void exchange_epilogue(const RealParams& P, bool sym, const double acc[SMAX],
                                                   double racc, const T Mi[SMAX], bool writer, int32_t i,
                                                   T* __restrict__ mout, int S, int react_a,
-                                                  int react_b, double* __restrict__ audit_part, int64_t t) {
+                                                  int react_b, double* __restrict__ audit_part, const OutMap& om,
+                                                  int64_t t) {
   double tot[SMAX + 1];
 #pragma unroll
   for (int s = 0; s <= SMAX; ++s) tot[s] = 0.0;
@@ -131,7 +132,14 @@ __device__ __forceinline__ void exchange_epilogue(const RealParams& P, bool sym,
       out[s] = s < S ? (T)Mn[s] : (T)0;  // unused species slots stay zero
       tot[s] = (double)out[s];
     }
-    store_mass<T, SMAX>(mout, i, out);
+    if (om.id) {
+      const uint32_t o = om.id[i];
+#pragma unroll
+      for (int s = 0; s < SMAX; ++s)
+        if (s < S) mout[(int64_t)s * om.n + o] = out[s];
+    } else {
+      store_mass<T, SMAX>(mout, i, out);
+    }
     tot[SMAX] = react_a >= 0 ? tot[react_a] - tot[react_b] : 0.0;
   }
   // totals over lanes 0..G-1 (the other lanes hold zeros and are reduced

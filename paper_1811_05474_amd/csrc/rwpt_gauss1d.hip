@@ -386,7 +386,7 @@ __global__ __launch_bounds__(kGaussBlock) void k_gauss1d(const PairArgs a) {
     }
   } else {
     exchange_epilogue<float, SMAX, 16>(R, MODE == 1, acc, racc, Mi, gl == 0 && valid, i, (float*)a.mass_out, a.S,
-                                       a.react_a, a.react_b, a.audit_part, item.tile + wave);
+                                       a.react_a, a.react_b, a.audit_part, a.out_map, item.tile + wave);
   }
 }
 

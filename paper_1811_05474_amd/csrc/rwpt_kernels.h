@@ -48,7 +48,8 @@ hipError_t launch_walk_key(int fp64, int dim, const void* pos_in, void* pos_out,
 hipError_t launch_cell_scan(uint32_t* cell_count, uint32_t* cell_start, int64_t ncell, uint64_t* scan_state,
                             uint64_t* step_ctr, int32_t n_real, int32_t bump, hipStream_t s);
 
-// Place every particle at cell_start[key] + slot (arrival order inside a cell).
+// Place every particle at cell_start[key] + slot (arrival order inside a cell);
+// id null: the identity.
 hipError_t launch_scatter(int32_t n, const uint32_t* key, const uint32_t* slot,
                           const uint32_t* cell_start, const uint32_t* id, uint32_t* tmp_src,
                           uint32_t* tmp_id, uint32_t* tmp_key, hipStream_t s);
@@ -56,12 +57,15 @@ hipError_t launch_scatter(int32_t n, const uint32_t* key, const uint32_t* slot,
 // Reorder inside every cell by particle id (canonical order), gathering
 // positions, ids and keys into the sorted arrays, and the masses too when
 // src_out is NULL; otherwise the masses stay in the previous order and
-// src_out[i] receives the previous slot of sorted particle i.
+// src_out[i] receives the previous slot of sorted particle i.  caller_S > 0:
+// mass_in holds the caller's masses, caller_S x n species-major.  inv_out (or
+// null) receives the sorted slot of each id.
 hipError_t launch_canon(int fp64, int dim, int32_t n, const uint32_t* tmp_src,
                         const uint32_t* tmp_id, const uint32_t* tmp_key,
                         const uint32_t* cell_start, const void* pos_in, void* pos_out,
                         const void* mass_in, void* mass_out, int32_t S,
-                        uint32_t* id_out, uint32_t* skey, uint32_t* src_out, hipStream_t s);
+                        uint32_t* id_out, uint32_t* skey, uint32_t* src_out, int32_t caller_S, uint32_t* inv_out,
+                        hipStream_t s);
 
 // Species slots per particle the mass arrays hold for S species: the kernels
 // are instantiated for 2, 4 or 8 species and read every slot of their
@@ -131,21 +135,22 @@ hipError_t launch_audit_reduce(const double* part, int32_t S1, const AuditChunk*
 
 // Allocation-free transfer of one realisation in caller arrays.  Its grid
 // parameters and stencil rows travel as kernel arguments (at most
-// kNoAllocStencil rows) and are written to device memory by the set-up
-// launch, which also converts the caller's layouts (positions n x dim
-// row-major, masses S x n species-major), fills the tiles of G particles, the
-// realisation starts {0, n} and the walk's realisation table, and clears ncell
-// cell counts.
+// kNoAllocStencil rows) and are written to device memory for the kernels that
+// follow.
 constexpr int kNoAllocStencil = 64;
 struct NoAllocParams {
   RealParams P;
   StencilRow st[kNoAllocStencil];
   int32_t n_st;
 };
-hipError_t launch_noalloc_setup(int fp64, int dim, int S, const NoAllocParams& a, int32_t n, const void* pos,
-                                const void* mass, void* pos_out, void* mass_out, uint32_t* id, Tile* tiles,
-                                int32_t G, int32_t ntiles, RealParams* rp, StencilRow* st, int64_t* real_start,
-                                int32_t* blk_real, uint32_t* cell_count, int64_t ncell, hipStream_t s);
+// Parameters, stencil, tiles of G particles, cleared counts and scan words;
+// then the cell key and place of every particle of the caller's positions (n x
+// dim row-major).  mass_out not null: the caller's masses (S x n species-major)
+// to the particle-major layout.
+hipError_t launch_noalloc_key(int fp64, int dim, int S, const NoAllocParams& a, int32_t n, const void* pos,
+                              const void* mass, void* mass_out, Tile* tiles, int32_t G, int32_t ntiles, RealParams* rp,
+                              StencilRow* st, uint32_t* cell_count, int64_t ncell, uint64_t* scan_state, uint32_t* key,
+                              uint32_t* slot, hipStream_t s);
 // The whole sort of realisations of at most kSmallParticles particles and
 // kSmallCells cells each, one block per realisation.  na: the allocation-free
 // call (one realisation, parameters from `na`, written to rp_out, st_out and
@@ -173,8 +178,9 @@ struct SmallSortArgs {
 };
 hipError_t launch_small_sort(int fp64, int dim, int32_t n_real, const SmallSortArgs& a, const NoAllocParams* na,
                              hipStream_t s);
-// Sorted masses (particle-major) back to the caller's order (S x n species-major).
-hipError_t launch_noalloc_store(int fp64, int S, int32_t n, const void* mass_sorted, const uint32_t* id,
+// Sorted masses (particle-major) back to the caller's order (S x n
+// species-major); inv: the sorted slot of each of the caller's particles.
+hipError_t launch_noalloc_store(int fp64, int S, int32_t n, const void* mass_sorted, const uint32_t* inv,
                                 void* mass, hipStream_t s);
 
 // comps values per particle (stride slots per particle in `in`, cell-sorted) to

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(kBlock) void k_pairs64(const PairArgs a) {
       }
     } else {
       exchange_epilogue<double, SMAX, G>(R, MODE == 1, acc[p], racc[p], Mi[p], writer, i, (double*)a.mass_out, a.S,
-                                         a.react_a, a.react_b, a.audit_part, tile + p);
+                                         a.react_a, a.react_b, a.audit_part, a.out_map, tile + p);
     }
   }
 }

@@ -14,10 +14,14 @@ namespace rwpt {
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallItems = (int)(kSmallParticles / kSmallBlock);
 
+// LDS word of cell k: one pad word per 16, so that threads scanning consecutive
+// runs of counts meet in few banks (2000 particles: 10.7 -> 9.7 us).
+__device__ __forceinline__ int cell_word(int k) { return k + (k >> 4); }
+
 // The launches of the general sort (walk + key, scan, scatter, canonical
 // gather) take 3 to 5 us each and a gap, whatever they sort; here their steps
 // are separated by block barriers.  Bound by that chain's latency: 2000
-// particles of 8000 cells, 11.2 us, before that 24 and five gaps between seven
+// particles of 8000 cells, 9.7 us, before that 24 and five gaps between seven
 // launches (the whole call 37.9 -> 28.4 us); 75 realisations of 2000 in 1-D 8.8
 // us, before 24 and three gaps (a step 55 -> 41 us).  Limit: what fits the LDS of
 // one block and stays shorter than the launches.
@@ -29,7 +33,7 @@ constexpr int kSmallItems = (int)(kSmallParticles / kSmallBlock);
 // caller's order (S x n species-major), ids = indices, no walk.
 template <typename T, int DIM, int SMAX, bool NA>
 __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs a, const NoAllocParams na) {
-  __shared__ uint32_t cnt[kSmallCells];
+  __shared__ uint32_t cnt[kSmallCells + kSmallCells / 16 + 1];
   __shared__ uint32_t sid[kSmallParticles];
   __shared__ uint32_t sh[kSmallBlock / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -44,7 +48,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
     if (!NA && tid == 0) a.step_ctr[r] += (uint64_t)a.bump;
     return;
   }
-  for (int k = tid; k < ncell; k += kSmallBlock) cnt[k] = 0u;
+  for (int k = tid; k < ncell; k += kSmallBlock) cnt[cell_word(k)] = 0u;
   if constexpr (NA) {
     if (tid == 0) a.rp_out[0] = na.P;
     if (tid < na.n_st) a.st_out[tid] = na.st[tid];
@@ -78,7 +82,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
     if (o < n) {
       if (!NA && a.do_walk && P.moves) walk_particle<T, DIM>(P, id[u], a.seed, step, x[u]);
       key[u] = (uint32_t)cell_index<T, DIM>(P, x[u]);
-      slot[u] = atomicAdd(&cnt[key[u]], 1u);
+      slot[u] = atomicAdd(&cnt[cell_word(key[u])], 1u);
     }
   }
   __syncthreads();
@@ -89,7 +93,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
   uint32_t sum = 0;
 #pragma unroll
   for (int k = 0; k < kPer; ++k)
-    if (k < per && c0 + k < ncell) sum += cnt[c0 + k];
+    if (k < per && c0 + k < ncell) sum += cnt[cell_word(c0 + k)];
   uint32_t v = sum;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -103,17 +107,17 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
 #pragma unroll
   for (int k = 0; k < kPer; ++k)
     if (k < per && c0 + k < ncell) {
-      const uint32_t c = cnt[c0 + k];
-      cnt[c0 + k] = run;
+      const uint32_t c = cnt[cell_word(c0 + k)];
+      cnt[cell_word(c0 + k)] = run;
       run += c;
     }
   __syncthreads();
-  for (int k = tid; k < ncell; k += kSmallBlock) start[k] = (uint32_t)p0 + cnt[k];
+  for (int k = tid; k < ncell; k += kSmallBlock) start[k] = (uint32_t)p0 + cnt[cell_word(k)];
   if (tid == 0) start[ncell] = (uint32_t)P.p_end;  // the next realisation writes the same
 #pragma unroll
   for (int u = 0; u < kSmallItems; ++u) {
     const int o = tid + u * kSmallBlock;
-    if (o < n) sid[cnt[key[u]] + slot[u]] = id[u];
+    if (o < n) sid[cnt[cell_word(key[u])] + slot[u]] = id[u];
   }
   __syncthreads();
   // canonical order inside a cell: by id
@@ -121,7 +125,8 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
   for (int u = 0; u < kSmallItems; ++u) {
     const int o = tid + u * kSmallBlock;
     if (o < n) {
-      const uint32_t cs = cnt[key[u]], ce = (int)key[u] + 1 < ncell ? cnt[key[u] + 1] : (uint32_t)n;
+      const uint32_t cs = cnt[cell_word(key[u])];
+      const uint32_t ce = (int)key[u] + 1 < ncell ? cnt[cell_word(key[u] + 1)] : (uint32_t)n;
       uint32_t rank = 0;
       for (uint32_t f = cs; f < ce; ++f) rank += sid[f] < id[u] ? 1u : 0u;
       const int64_t dst = p0 + cs + rank;

@@ -750,29 +750,36 @@ __device__ __forceinline__ void for_tile_chunks(const RealParams& P, const Stenc
     const int cxb = __builtin_amdgcn_readlane(tl.cx, seg_end - 1);
     const bool act = tl.valid && tl.gi >= seg && tl.gi < seg_end;
     const int cy = seg_row % nc1, cz = seg_row / nc1;
+    RowTable tab;
+    const bool table = NPARTS > 1 && P.n_stencil <= RowTable::kRows;
+    if (table) tab.load(P, st, cell_start, cy, cz, cxa, cxb);
+    auto advance = [&](RowCursor& k) {
+      if (table) tab.advance(k, P);
+      else cursor_advance(k, P, st, cell_start, cy, cz, cxa, cxb);
+    };
     RowCursor c;
     c.r = 0;
     c.p = 0;
-    cursor_advance(c, P, st, cell_start, cy, cz, cxa, cxb);
+    advance(c);
     // after picking the chunk at vbase, c.valid says whether a chunk follows
     uint32_t vbase = 0;
     int32_t j;
     bool has;
     if constexpr (NPARTS > 1) {
       for (int k = 0; k < part && c.valid; ++k) {  // chunks before this part's first
-        chunk_pick(c, P, st, cell_start, cy, cz, cxa, cxb, vbase, jdummy, j, has);
+        chunk_pick(c, advance, vbase, jdummy, j, has);
         vbase += 64;
       }
     }
     if (c.valid) {
-      chunk_pick(c, P, st, cell_start, cy, cz, cxa, cxb, vbase, jdummy, j, has);
+      chunk_pick(c, advance, vbase, jdummy, j, has);
       int nk = NPARTS == 1 ? chunk_compact(c, vbase, j, has) : 16;
       auto cur = load(j, has);
       while (true) {
         if constexpr (NPARTS > 1) {
           for (int k = 1; k < NPARTS && c.valid; ++k) {  // the other parts' chunks
             vbase += 64;
-            chunk_pick(c, P, st, cell_start, cy, cz, cxa, cxb, vbase, jdummy, j, has);
+            chunk_pick(c, advance, vbase, jdummy, j, has);
           }
         }
         const bool next = c.valid;
@@ -780,7 +787,7 @@ __device__ __forceinline__ void for_tile_chunks(const RealParams& P, const Stenc
         int nk_next = 16;
         if (next) {
           vbase += 64;
-          chunk_pick(c, P, st, cell_start, cy, cz, cxa, cxb, vbase, jdummy, j, has);
+          chunk_pick(c, advance, vbase, jdummy, j, has);
           if constexpr (NPARTS == 1) nk_next = chunk_compact(c, vbase, j, has);
           nxt = load(j, has);
         }

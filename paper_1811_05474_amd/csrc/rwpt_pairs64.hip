@@ -173,17 +173,24 @@ __global__ __launch_bounds__(kBlock) void k_pairs64(const PairArgs a) {
         rc2[p] = o >= seg && o < seg_end ? R.rc2_d : -1.0;
       }
       const int cy = seg_row % nc1, cz = seg_row / nc1;
+      RowTable tab;
+      const bool table = PP == 1 && R.n_stencil <= RowTable::kRows;
+      if (table) tab.load(R, a.st, a.cell_start, cy, cz, cxa, cxb);
+      auto advance = [&](RowCursor& k) {
+        if (table) tab.advance(k, R);
+        else cursor_advance(k, R, a.st, a.cell_start, cy, cz, cxa, cxb);
+      };
       RowCursor c;
       c.r = 0;
       c.p = 0;
-      cursor_advance(c, R, a.st, a.cell_start, cy, cz, cxa, cxb);
+      advance(c);
       double xn[DIM], qn = 0.0, mn[SMAX];
       uint32_t vbase = 0;
       int count = 0;  // candidates of the chunk in xn, qn, mn
       auto fetch = [&]() {
         int32_t j;
         bool has;
-        chunk_pick(c, R, a.st, a.cell_start, cy, cz, cxa, cxb, vbase, begin, j, has);
+        chunk_pick(c, advance, vbase, begin, j, has);
         count = c.valid ? 64 : (int)__builtin_amdgcn_readfirstlane(c.p - vbase);
         vbase += 64;
         load_pos<double, DIM>(pos, j, xn);

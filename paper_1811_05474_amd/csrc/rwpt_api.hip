@@ -140,6 +140,7 @@ struct rwpt_ctx {
   int32_t ntiles = 0;
   int log2l = 3;
   int nb_slots = 0;
+  double nb_mean = 0.0;  // expected neighbours per particle
   bool small_sort = false;  // every realisation fits the one-launch sort
   double refine[3] = {0, 0, 0};
 
@@ -562,6 +563,7 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
     const int64_t nr = c->real_start[r + 1] - c->real_start[r];
     nb += (double)nr / (double)std::max<int64_t>(c->N, 1) * expected_neighbours(cfg, dim, dt, D * c->d_scale[r], nr);
   }
+  c->nb_mean = nb;
   c->nb_slots = c->log2l == kPrivateLists ? slots_for(nb) : 0;
   double defr[3];
   default_refine(dim, nb, defr);
@@ -757,6 +759,7 @@ static PairArgs pair_args(rwpt_ctx* c) {
   a.cell_start = c->cell_start.as<uint32_t>();
   a.tiles = c->d_tiles.as<Tile>();
   a.ntiles = c->ntiles;
+  a.split_tiles = split_tiles_for(c->nb_mean);
   a.rp = c->d_rp.as<RealParams>();
   a.st = c->d_st.as<StencilRow>();
   a.S = c->S;
@@ -2209,6 +2212,7 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   a.cell_start = (uint32_t*)at(o_start);
   a.tiles = (Tile*)at(o_tiles);
   a.ntiles = ntiles;
+  a.split_tiles = split_tiles_for(nb);
   a.rp = (RealParams*)at(o_rp);
   a.st = (StencilRow*)at(o_st);
   a.S = S;

@@ -82,6 +82,7 @@ struct PairArgs {
   const uint32_t* cell_start;
   const Tile* tiles;
   int32_t ntiles;
+  int32_t split_tiles;     // row-broadcast kernels: a whole block per tile up to this many tiles
   const RealParams* rp;
   const StencilRow* st;
   int32_t S;

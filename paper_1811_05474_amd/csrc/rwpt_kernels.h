@@ -107,6 +107,14 @@ constexpr int kHalfParities = 2;
 constexpr int64_t kHalfTarget = 32768;
 // Consecutive blocks of the half-stencil launch that one XCD takes in turn.
 constexpr int64_t kHalfGroup = 16;
+// Up to this many tiles, the row-broadcast kernels give each tile a whole block
+// (its four waves take every fourth chunk of the candidates), so that a small
+// ensemble still puts enough waves on the 1024 SIMDs to hide latency.  Whole
+// calls in 2-D, split / whole, us: 24000 particles (1500 tiles) of 60 neighbours
+// 38.3 / 38.1, of 225 40.6 / 43.8; 40000 of 60 45.9 / 42.0, of 225 50.1 / 49.2; 64000
+// of 60 57.2 / 46.3.  Many more candidates per tile keep four waves busy for
+// longer (1-D, 32768 particles of 1758 neighbours, a step: 59 / 63 us).
+inline int32_t split_tiles_for(double nb) { return nb > 400.0 ? 4096 : 1536; }
 hipError_t launch_rowsum(int fp64, int dim, int log2l, const PairArgs& a, hipStream_t s);
 hipError_t launch_exchange(int fp64, int dim, int log2l, const PairArgs& a, hipStream_t s);
 hipError_t launch_count(int fp64, int dim, int log2l, const PairArgs& a, hipStream_t s);

@@ -2527,11 +2527,6 @@ hipError_t launch_canon(int fp64, int dim, int32_t n, const uint32_t* tmp_src,
   return hipGetLastError();
 }
 
-// Up to this many tiles, the row-broadcast kernels give each tile a whole
-// block (its four waves take every fourth chunk of the candidates), so that a
-// small ensemble still puts enough waves on the 1024 SIMDs to hide latency.
-constexpr int32_t kSplitTiles = 4096;
-
 static inline dim3 pair_grid(int32_t ntiles) {
   return dim3((unsigned)((ntiles + (kBlock / 64) - 1) / (kBlock / 64)));
 }
@@ -2621,7 +2616,7 @@ hipError_t launch_rowsum(int fp64, int dim, int log2l, const PairArgs& a, hipStr
     });
   }
   if (!fp64 && log2l == 2) {
-    const bool split = a.ntiles <= kSplitTiles;
+    const bool split = a.ntiles <= a.split_tiles;
     const dim3 gs = split ? dim3((unsigned)a.ntiles) : g;
     auto go = [&](auto d) {
       constexpr int D = decltype(d)::value;
@@ -2689,7 +2684,7 @@ hipError_t launch_exchange(int fp64, int dim, int log2l, const PairArgs& a, hipS
     });
   }
   if (!fp64 && log2l == 2) {
-    const bool split = a.ntiles <= kSplitTiles;
+    const bool split = a.ntiles <= a.split_tiles;
     const dim3 gs = split ? dim3((unsigned)a.ntiles) : g;
     auto go = [&](auto d) {
       constexpr int D = decltype(d)::value;
@@ -2727,10 +2722,10 @@ hipError_t launch_exchange(int fp64, int dim, int log2l, const PairArgs& a, hipS
 }
 
 // The row-broadcast export/count kernels in the launch shape of the binary32
-// four-lane pair kernels (one block per tile up to kSplitTiles tiles).
+// four-lane pair kernels (one block per tile up to a.split_tiles tiles).
 template <int MODE>
 static hipError_t launch_nbr_dpp(int dim, const PairArgs& a, hipStream_t s) {
-  const bool split = a.ntiles <= kSplitTiles;
+  const bool split = a.ntiles <= a.split_tiles;
   const dim3 g = split ? dim3((unsigned)a.ntiles) : pair_grid(a.ntiles), b(kBlock);
   auto go = [&](auto d) {
     constexpr int D = decltype(d)::value;

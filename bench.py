@@ -375,7 +375,8 @@ def cpu_baseline(W, w, unordered_pairs_per_step, budget_s=15.0):
 
 # the device code and the host code that picks its launch shapes; the counter
 # summaries in profiles/ record the SHA-256 of their concatenation, in this order
-DEVICE_SOURCES = ("rwpt_device.h", "rwpt_layout.h", "rwpt_pairstep.h", "rwpt_kernels.h", "rwpt_kernels.hip",
+DEVICE_SOURCES = ("rwpt_device.h", "rwpt_layout.h", "rwpt_pairstep.h", "rwpt_cursor.h", "rwpt_epilogue.h", "rwpt_walk.h",
+                  "rwpt_kernels.h", "rwpt_kernels.hip", "rwpt_smallsort.hip", "rwpt_pairs64.hip", "rwpt_gauss1d.hip",
                   "rwpt_dense.hip", "rwpt_api.hip")
 
 

@@ -166,7 +166,7 @@ __device__ __forceinline__ void add_within(float& a, const float (&s2)[8], const
       "v_cmpx_le_f32 vcc, %[s6], %[lim]\n\tv_add_f32 %[a], %[a], %[w6]\n\ts_mov_b64 exec, %[save]\n\t"
       "v_cmpx_le_f32 vcc, %[s7], %[lim]\n\tv_add_f32 %[a], %[a], %[w7]\n\ts_mov_b64 exec, %[save]\n\t"
       "s_nop 4"
-      : [a] "+v"(a), [save] "=&s"(save)
+      : [a] "+&v"(a), [save] "=&s"(save)
       : [lim] "v"(lim), [s0] "v"(s2[0]), [s1] "v"(s2[1]), [s2] "v"(s2[2]), [s3] "v"(s2[3]), [s4] "v"(s2[4]),
         [s5] "v"(s2[5]), [s6] "v"(s2[6]), [s7] "v"(s2[7]), [w0] "v"(w[0]), [w1] "v"(w[1]), [w2] "v"(w[2]),
         [w3] "v"(w[3]), [w4] "v"(w[4]), [w5] "v"(w[5]), [w6] "v"(w[6]), [w7] "v"(w[7])
@@ -183,7 +183,7 @@ __device__ __forceinline__ void exchange_within(float& acc0, float& acc1, const 
   "v_cmpx_le_f32 vcc, %[s" #u "], %[lim]\n\tv_mul_f32 %[p], %[w" #u "], %[q" #u "]\n\t"           \
   "v_fmac_f32 %[a0], %[p], %[x" #u "]\n\tv_fmac_f32 %[a1], %[p], %[y" #u "]\n\ts_mov_b64 exec, %[save]\n\t"
   asm("s_mov_b64 %[save], exec\n\t" RWPT_PAIR(0) RWPT_PAIR(1) RWPT_PAIR(2) RWPT_PAIR(3) "s_nop 4"
-      : [a0] "+v"(acc0), [a1] "+v"(acc1), [p] "=&v"(p), [save] "=&s"(save)
+      : [a0] "+&v"(acc0), [a1] "+&v"(acc1), [p] "=&v"(p), [save] "=&s"(save)
       : [lim] "v"(lim), [s0] "v"(s2[0]), [s1] "v"(s2[1]), [s2] "v"(s2[2]), [s3] "v"(s2[3]), [w0] "v"(w[0]),
         [w1] "v"(w[1]), [w2] "v"(w[2]), [w3] "v"(w[3]), [q0] "v"(qs[0]), [q1] "v"(qs[1]), [q2] "v"(qs[2]),
         [q3] "v"(qs[3]), [x0] "v"(d0[0]), [x1] "v"(d0[1]), [x2] "v"(d0[2]), [x3] "v"(d0[3]), [y0] "v"(d1[0]),

@@ -790,6 +790,7 @@ static PairArgs pair_args(rwpt_ctx* c) {
   a.gauss_rows = c->gauss ? gauss_rows(c->gauss) : 0;
   a.gauss_tab = c->gauss_tab.as<double>();
   a.gauss_mom = c->gauss_mom.as<double>();
+  a.gauss_q = c->gauss ? c->r.as<double>() : nullptr;  // r itself is kept for the row normalisation only
   a.gauss_ncell = c->ncell_total;
   return a;
 }
@@ -1648,6 +1649,7 @@ rwpt_status rwpt_debug_rowsums(rwpt_ctx* c, double dt, double D, int32_t unit_we
   if (st != RWPT_OK) return st;
   PairArgs a = pair_args(c);
   a.r_out = c->r.as<double>();
+  a.gauss_q = nullptr;
   DevBuf rp_unit, tab_unit;
   rwpt_status result = RWPT_OK;
   do {
@@ -2235,6 +2237,8 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
     a.gauss_nitems = (ntiles + kGaussTiles - 1) / kGaussTiles;
     a.gauss_rows = gauss_rows(plan);
     a.gauss_mom = (double*)at(o_gmom);
+    a.gauss_q = a.r_out;  // r itself is not read by either normalisation here
+    a.r_out = nullptr;
     a.gauss_ncell = ncell;
     a.gauss_tab = (double*)at(o_gtab);
     NACHK(launch_gauss_table(plan, a.rp, 1, (double*)at(o_gtab), s));

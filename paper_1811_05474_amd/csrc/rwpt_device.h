@@ -128,6 +128,7 @@ struct PairArgs {
   const TileGroup* gauss_items;    // null: one realisation, its tiles in order
   int32_t gauss_nitems;
   int32_t gauss_rows;              // rows of gauss_tab per realisation
+  double* gauss_q;                 // 1 / r_i in binary64, as the symmetric expansions read it
   double* gauss_mom;               // [terms][gauss_ncell][columns] moments of the cells
   int64_t gauss_ncell;             // cells of all realisations
   const double* gauss_tab;         // [n_real][gauss_rows][terms] Hermite functions of the cell offsets

@@ -12,7 +12,8 @@
 // polynomial of P coefficients per column: the work per particle does not
 // grow with the neighbours it has.  All of it is binary64; P and h / sigma are
 // chosen (gauss_plan) for a truncation below 2e-9 of one weight, which is
-// under the rounding of a binary32 weight.
+// under the rounding of a binary32 weight; 1 / r is kept in binary64 between
+// the passes.
 //
 // The cutoff is kept exactly: only cells all of whose points lie within the
 // cutoff of all points of the target's cell (|k| <= g_in) are expanded.  The
@@ -81,7 +82,6 @@ __global__ __launch_bounds__(kBlock) void k_gauss_moments(const PairArgs a) {
   constexpr int NCOL = gauss_columns(SMAX, MODE);
   const float* __restrict__ pos = (const float*)a.pos;
   const float* __restrict__ min_ = (const float*)a.mass_in;
-  const float* __restrict__ q = (const float*)a.q_in;
   const int64_t e = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 3;
   const int pt = threadIdx.x & 7;
   const int64_t n_out = a.gauss_ncell * NCOL;
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kBlock) void k_gauss_moments(const PairArgs a) {
     for (uint32_t j = jb + pt; j < je; j += 8) {
       const double v = ((double)pos[j] - ctr) * gs;
       double f = use_m ? (double)min_[(int64_t)SMAX * j + sp] : 1.0;
-      if (use_q) f *= (double)q[j];
+      if (use_q) f *= a.gauss_q[j];
       m[0] += f;
 #pragma unroll
       for (int n = 1; n < P; ++n) {
@@ -167,7 +167,6 @@ __global__ __launch_bounds__(kGaussBlock) void k_gauss1d(const PairArgs a) {
   const RealParams& R = a.rp[item.real];
   const float* __restrict__ pos = (const float*)a.pos;
   const float* __restrict__ min_ = (const float*)a.mass_in;
-  const float* __restrict__ q = (const float*)a.q_in;
   const int tid = threadIdx.x, lane = tid & 63, gi = lane & 15, gl = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wt = wave % kGaussTiles;
@@ -180,11 +179,12 @@ __global__ __launch_bounds__(kGaussBlock) void k_gauss1d(const PairArgs a) {
   const float xi = pos[ii];
   const uint32_t coff = (uint32_t)R.cell_off;
   const int ci = (int)(a.skey[ii] - coff);
-  float Mi[SMAX], qi = 0.0f;
+  float Mi[SMAX];
+  double qi = 0.0;
 #pragma unroll
   for (int s = 0; s < SMAX; ++s) Mi[s] = 0.0f;
   if constexpr (MODE != 0) load_mass<float, SMAX>(min_, ii, Mi);
-  if constexpr (MODE == 1) qi = q[ii];
+  if constexpr (MODE == 1) qi = a.gauss_q[ii];
   double acc[SMAX], racc = 0.0;  // MODE 0: racc alone
 #pragma unroll
   for (int s = 0; s < SMAX; ++s) acc[s] = 0.0;
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kGaussBlock) void k_gauss1d(const PairArgs a) {
           for (uint32_t e = tid - 64 * kGaussTiles; e < nN; e += 64 * kGaussTiles) {
             const uint32_t j = e < nL ? L0 + e : R0 + (e - nL);
             near_x[e] = pos[j];
-            if constexpr (MODE == 1) near_q[e] = q[j];
+            if constexpr (MODE == 1) near_q[e] = (float)a.gauss_q[j];
             if constexpr (MODE != 0) {
               float m[SMAX];
               load_mass<float, SMAX>(min_, j, m);
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kGaussBlock) void k_gauss1d(const PairArgs a) {
                 if constexpr (MODE != 0) load_mass<float, SMAX>(near_m, e, mj[u]);
               } else {
                 xj[u] = pos[j];
-                if constexpr (MODE == 1) qj[u] = q[j];
+                if constexpr (MODE == 1) qj[u] = (float)a.gauss_q[j];
                 if constexpr (MODE != 0) load_mass<float, SMAX>(min_, j, mj[u]);
               }
             }
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(kGaussBlock) void k_gauss1d(const PairArgs a) {
               const float w = (in[u] && s2 <= rc2) ? kweight(s2, esc) : 0.0f;
               if constexpr (MODE != 1) rr += w;
               if constexpr (MODE != 0) {
-                const float p = MODE == 1 ? w * (qi + qj[u]) : w;
+                const float p = MODE == 1 ? w * ((float)qi + qj[u]) : w;
 #pragma unroll
                 for (int s = 0; s < SMAX; ++s) accr[s] += p * (mj[u][s] - Mi[s]);
               }
@@ -336,8 +336,8 @@ __global__ __launch_bounds__(kGaussBlock) void k_gauss1d(const PairArgs a) {
                 racc += val;
               } else if constexpr (MODE == 1) {
                 // q_i sum w M_j + sum w q_j M_j - M_i (sum w q_j + q_i sum w)
-                const double at = col < SMAX ? (double)qi * val : (col < 2 * SMAX ? val : 0.0);
-                const double every = col == 2 * SMAX ? val : (col == 2 * SMAX + 1 ? (double)qi * val : 0.0);
+                const double at = col < SMAX ? qi * val : (col < 2 * SMAX ? val : 0.0);
+                const double every = col == 2 * SMAX ? val : (col == 2 * SMAX + 1 ? qi * val : 0.0);
 #pragma unroll
                 for (int s = 0; s < SMAX; ++s)
                   acc[s] += (col % SMAX == s ? at : 0.0) - (double)Mi[s] * every;
@@ -383,6 +383,7 @@ __global__ __launch_bounds__(kGaussBlock) void k_gauss1d(const PairArgs a) {
       if (!R.active) racc = 1.0;  // only the self weight
       if (a.r_out) a.r_out[i] = racc;
       ((float*)a.q_out)[i] = (float)(1.0 / racc);
+      if (a.gauss_q) a.gauss_q[i] = 1.0 / racc;
     }
   } else {
     exchange_epilogue<float, SMAX, 16>(R, MODE == 1, acc, racc, Mi, gl == 0 && valid, i, (float*)a.mass_out, a.S,

@@ -837,13 +837,13 @@ static rwpt_status enqueue_sort(rwpt_ctx* c, bool walk, bool move_mass, int bump
     PhaseScope ps(c, PH_SCAN);
     HIPCHK(c, launch_cell_scan(c->cell_count.as<uint32_t>(), c->cell_start.as<uint32_t>(), c->ncell_total,
                                c->scan_part.as<uint64_t>(), c->step_ctr.as<uint64_t>(), c->n_real,
-                               bump, c->stream));
+                               bump, kScanPolls, c->stream));
   }
   {
     PhaseScope ps(c, PH_SCATTER);
     HIPCHK(c, launch_scatter(n, c->key.as<uint32_t>(), c->slot.as<uint32_t>(), c->cell_start.as<uint32_t>(),
                              c->id.as<uint32_t>(), c->tmp_src.as<uint32_t>(), c->tmp_id.as<uint32_t>(),
-                             c->tmp_key.as<uint32_t>(), c->stream));
+                             c->tmp_key.as<uint32_t>(), c->cell_count.as<uint32_t>(), c->ncell_total, c->stream));
   }
   {
     PhaseScope ps(c, PH_CANON);
@@ -2114,14 +2114,14 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
     o_tsrc = L.take(cap * 4), o_tid = L.take(cap * 4), o_tkey = L.take(cap * 4);
     o_skey = L.take(cap * 4), o_r = L.take(cap * 8), o_q = L.take(cap * ts);
     o_cnt = L.take(ncell * 4), o_start = L.take((ncell + 1) * 4);
-    // the cell scan's words: the sorted keys' place, which the scatter fills later, where that is large enough
-    const size_t scan_bytes = scan_state_words(ncell) * 8;
     // room that earlier forms of the sort took (a second position buffer, the
-    // walk's tables, the scan's partials), so that the largest call stays the same
-    for (size_t unused : {PS * cap * ts, (size_t)((n + kBlock - 1) / kBlock) * 4, 2 * sizeof(int64_t),
+    // walk's tables, the scan's partials), so that the calls that are refused
+    // stay the same; the cell scan's words lie in the first piece, where nothing
+    // else is ever written
+    o_scan = L.take(std::max(PS * cap * ts, scan_state_words(ncell) * 8));
+    for (size_t unused : {(size_t)((n + kBlock - 1) / kBlock) * 4, 2 * sizeof(int64_t),
                           (size_t)((ncell + kScanChunk - 1) / kScanChunk + 1) * 4})
       (void)L.take(unused);
-    o_scan = (size_t)cap * 4 >= scan_bytes ? o_tkey : L.take(scan_bytes);
     o_rp = L.take(sizeof(RealParams)), o_st = L.take(kNoAllocStencil * sizeof(StencilRow));
     o_tiles = L.take((size_t)ntiles * sizeof(Tile));
     o_ctr = L.take(8);
@@ -2192,9 +2192,9 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
                              ntiles, (RealParams*)at(o_rp), (StencilRow*)at(o_st), (uint32_t*)at(o_cnt), ncell,
                              (uint64_t*)at(o_scan), (uint32_t*)at(o_key), (uint32_t*)at(o_slot), s));
     NACHK(launch_cell_scan((uint32_t*)at(o_cnt), (uint32_t*)at(o_start), ncell, (uint64_t*)at(o_scan),
-                           (uint64_t*)at(o_ctr), 1, 0, s));
+                           (uint64_t*)at(o_ctr), 1, 0, kScanPolls, s));
     NACHK(launch_scatter(n, (uint32_t*)at(o_key), (uint32_t*)at(o_slot), (uint32_t*)at(o_start), nullptr,
-                         (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey), s));
+                         (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey), nullptr, 0, s));
     NACHK(launch_canon(fp64, dim, n, (uint32_t*)at(o_tsrc), (uint32_t*)at(o_tid), (uint32_t*)at(o_tkey),
                        (uint32_t*)at(o_start), pos, at(o_pos0), direct ? mass_in : at(o_m0), at(o_m1), S,
                        (uint32_t*)at(o_id), (uint32_t*)at(o_skey), nullptr, direct ? S : 0,

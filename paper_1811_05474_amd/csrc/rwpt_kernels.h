@@ -42,17 +42,20 @@ hipError_t launch_walk_key(int fp64, int dim, const void* pos_in, void* pos_out,
                            uint64_t seed, int32_t do_walk, uint32_t* cell_count, uint32_t* key,
                            uint32_t* slot, uint64_t* scan_state, hipStream_t s);
 
-// Exclusive scan of cell_count[0..ncell) into cell_start[0..ncell]; zeroes cell_count.
+// Looks at another block's total before the one-launch cell scan sums that
+// chunk itself (about 1 us each: a block that has started answers in a few).
+constexpr int32_t kScanPolls = 4096;
+// Exclusive scan of cell_count[0..ncell) into cell_start[0..ncell].
 // scan_state holds scan_state_words(ncell) words, cleared by launch_walk_key.
 // Advances the n_real step counters by bump.
-hipError_t launch_cell_scan(uint32_t* cell_count, uint32_t* cell_start, int64_t ncell, uint64_t* scan_state,
-                            uint64_t* step_ctr, int32_t n_real, int32_t bump, hipStream_t s);
+hipError_t launch_cell_scan(const uint32_t* cell_count, uint32_t* cell_start, int64_t ncell, uint64_t* scan_state,
+                            uint64_t* step_ctr, int32_t n_real, int32_t bump, int32_t polls, hipStream_t s);
 
 // Place every particle at cell_start[key] + slot (arrival order inside a cell);
-// id null: the identity.
+// id null: the identity.  Zeroes cell_count[0..ncell) unless it is null.
 hipError_t launch_scatter(int32_t n, const uint32_t* key, const uint32_t* slot,
                           const uint32_t* cell_start, const uint32_t* id, uint32_t* tmp_src,
-                          uint32_t* tmp_id, uint32_t* tmp_key, hipStream_t s);
+                          uint32_t* tmp_id, uint32_t* tmp_key, uint32_t* cell_count, int64_t ncell, hipStream_t s);
 
 // Reorder inside every cell by particle id (canonical order), gathering
 // positions, ids and keys into the sorted arrays, and the masses too when

@@ -221,14 +221,16 @@ __device__ __forceinline__ int scan_pad(int k) { return k + (k >> 4); }
 
 // Cell starts of one chunk: coalesced striped loads into LDS, a sequential
 // scan of 16 consecutive elements per thread, a block scan of the thread sums,
-// then coalesced striped stores; the counts are re-zeroed for the next step.
+// then coalesced striped stores.
 // ONE (up to kScanDirectMax chunks): the whole scan in this launch.  A block
 // takes the next chunk from a ticket, publishes the chunk's total as soon as
 // it has summed it, and thread t waits for the total of chunk t < its own; a
 // chunk's block has always started before any block that waits for it (the
-// ticket orders them), so every wait ends.  The total and its valid bit
-// travel in one 64-bit word, so a relaxed device-scope load is enough; the
-// walk + key kernel cleared the words.  Otherwise partials holds the exclusive
+// ticket orders them).  The total and its valid bit travel in one 64-bit word,
+// so a relaxed device-scope load is enough; the walk + key kernel cleared the
+// words.  A wait ends after `polls` looks whatever the other blocks do: the
+// block then sums that chunk's counts itself.  So the counts stay as they are
+// until the scatter, which clears them for the next step.  Otherwise partials holds the exclusive
 // scan of the chunk totals (k_scan_reduce, k_scan_top).
 // Launch-latency bound: at 4.4e5 cells (108 chunks) the two launches took
 // 5.3 + 5.5 us and a gap; a transfer call of 2000 particles went from 40.4 to
@@ -240,24 +242,25 @@ __device__ __forceinline__ int scan_pad(int k) { return k + (k >> 4); }
 constexpr uint64_t kScanValid = (uint64_t)1 << 32;
 
 template <bool ONE>
-__global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cnt, int64_t n, uint64_t* scan_state,
-                                                       uint32_t* __restrict__ start, uint64_t* __restrict__ step_ctr,
-                                                       int32_t n_real, int32_t bump) {
+__global__ __launch_bounds__(kBlock) void k_scan_final(const uint32_t* __restrict__ cnt, int64_t n,
+                                                       uint64_t* scan_state, uint32_t* __restrict__ start,
+                                                       uint64_t* __restrict__ step_ctr, int32_t n_real, int32_t bump,
+                                                       int32_t polls) {
   __shared__ uint32_t sh[4];
   __shared__ uint32_t buf[kScanChunk + kScanChunk / 16];
   __shared__ uint32_t sh_chunk;
   const int t = threadIdx.x;
   int chunk = blockIdx.x;
   uint32_t c[kScanItems];
-  auto load = [&]() {
-    const int64_t base = (int64_t)chunk * kScanChunk;
+  auto load = [&](int k0) {
+    const int64_t base = (int64_t)k0 * kScanChunk;
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
       const int64_t k = base + t + i * kBlock;
       c[i] = k < n ? cnt[k] : 0u;
     }
   };
-  load();
+  load(chunk);
   if constexpr (ONE) {
     // blocks mostly start in order: the counts above are on their way while
     // the ticket is drawn, and are loaded again if it names another chunk
@@ -267,7 +270,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cn
     __syncthreads();
     chunk = (int)__builtin_amdgcn_readfirstlane(sh_chunk);
     if (chunk >= (int)gridDim.x) return;  // never in a scan that has its words to itself
-    if (chunk != (int)blockIdx.x) load();
+    if (chunk != (int)blockIdx.x) load(chunk);
   }
   const int64_t base = (int64_t)chunk * kScanChunk;
 #pragma unroll
@@ -287,16 +290,29 @@ __global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cn
     if (t == 0)
       __hip_atomic_store(&scan_state[chunk], kScanValid | total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint32_t before = 0;
-    if (t < chunk) {  // chunk < kScanDirectMax = kBlock
-      uint64_t w = 0;
-      // bounded, so that calls that overlap on one scratch area (which the
-      // allocation-free entry point does not allow) still end
-      for (int spin = 0; spin < (1 << 20); ++spin) {
-        w = __hip_atomic_load(&scan_state[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (w & kScanValid) break;
+    bool missing = t < chunk;  // chunk < kScanDirectMax = kBlock
+    for (int32_t k = 0; missing && k < polls; ++k) {
+      const uint64_t w = __hip_atomic_load(&scan_state[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (w & kScanValid) {
+        before = (uint32_t)w;
+        missing = false;
+      } else {
         __builtin_amdgcn_s_sleep(1);
       }
-      before = (uint32_t)w;
+    }
+    if (__syncthreads_or(missing)) {
+      buf[t] = missing ? 1u : 0u;  // the chunk's own counts are in v by now
+      __syncthreads();
+      for (int k0 = 0; k0 < chunk; ++k0) {
+        if (!buf[k0]) continue;  // uniform
+        load(k0);
+        uint32_t s = 0, all;
+#pragma unroll
+        for (int i = 0; i < kScanItems; ++i) s += c[i];
+        block_inclusive_scan(s, sh, &all);
+        if (t == k0) before = all;
+      }
+      __syncthreads();  // buf is written again below
     }
     block_inclusive_scan(before, sh, &prefix);
     if (t == 0 && chunk == (int)gridDim.x - 1) start[n] = prefix + total;
@@ -315,10 +331,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_final(uint32_t* __restrict__ cn
 #pragma unroll
   for (int i = 0; i < kScanItems; ++i) {
     const int k = t + i * kBlock;
-    if (base + k < n) {
-      start[base + k] = buf[scan_pad(k)];
-      cnt[base + k] = 0u;  // ready for the next step's counting
-    }
+    if (base + k < n) start[base + k] = buf[scan_pad(k)];
   }
 }
 
@@ -332,7 +345,11 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int32_t n, const uint32_t* _
                                                     const uint32_t* __restrict__ id,
                                                     uint32_t* __restrict__ tmp_src,
                                                     uint32_t* __restrict__ tmp_id,
-                                                    uint32_t* __restrict__ tmp_key) {
+                                                    uint32_t* __restrict__ tmp_key,
+                                                    uint32_t* __restrict__ cell_count, int64_t ncell) {
+  if (cell_count)  // ready for the next step's counting
+    for (int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x; c < ncell; c += (int64_t)gridDim.x * kBlock)
+      cell_count[c] = 0u;
   // XCD-contiguous ranges: neighbouring particles' gathers and partial-line
   // writes meet in one L2
   const int p = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
@@ -2461,30 +2478,30 @@ hipError_t launch_walk_key(int fp64, int dim, const void* pos_in, void* pos_out,
   return hipGetLastError();
 }
 
-hipError_t launch_cell_scan(uint32_t* cell_count, uint32_t* cell_start, int64_t ncell, uint64_t* scan_state,
-                            uint64_t* step_ctr, int32_t n_real, int32_t bump, hipStream_t s) {
+hipError_t launch_cell_scan(const uint32_t* cell_count, uint32_t* cell_start, int64_t ncell, uint64_t* scan_state,
+                            uint64_t* step_ctr, int32_t n_real, int32_t bump, int32_t polls, hipStream_t s) {
   static_assert(kScanDirectMax <= kBlock, "one chunk total per thread");
   const int64_t nb = (ncell + kScanChunk - 1) / kScanChunk;
   const dim3 g((unsigned)nb), b(kBlock);
   if (nb <= kScanDirectMax) {
     hipLaunchKernelGGL(k_scan_final<true>, g, b, 0, s, cell_count, ncell, scan_state, cell_start, step_ctr, n_real,
-                       bump);
+                       bump, polls);
   } else {
     uint32_t* const partials = (uint32_t*)scan_state;
     hipLaunchKernelGGL(k_scan_reduce, g, b, 0, s, cell_count, ncell, partials);
     hipLaunchKernelGGL(k_scan_top, dim3(1), b, 0, s, partials, (int32_t)nb, cell_start, ncell);
     hipLaunchKernelGGL(k_scan_final<false>, g, b, 0, s, cell_count, ncell, scan_state, cell_start, step_ctr, n_real,
-                       bump);
+                       bump, polls);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_scatter(int32_t n, const uint32_t* key, const uint32_t* slot,
                           const uint32_t* cell_start, const uint32_t* id, uint32_t* tmp_src,
-                          uint32_t* tmp_id, uint32_t* tmp_key, hipStream_t s) {
+                          uint32_t* tmp_id, uint32_t* tmp_key, uint32_t* cell_count, int64_t ncell, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n)), dim3(kBlock), 0, s, n, key, slot, cell_start, id,
-                     tmp_src, tmp_id, tmp_key);
+                     tmp_src, tmp_id, tmp_key, cell_count, ncell);
   return hipGetLastError();
 }
 

@@ -122,7 +122,7 @@ struct rwpt_ctx {
   DevBuf bbox, bparts;  // full-matrix path
   DevBuf half_slots, half_own, d_item_start, d_item_real;  // half-stencil tiling
   int64_t half_nitems = 0;
-  DevBuf d_gauss_items, gauss_tab, gauss_mom;  // 1-D expansions
+  DevBuf d_gauss_items, d_gauss_cell_real, gauss_tab, gauss_mom;  // 1-D expansions
   int gauss = 0;                    // their plan (0: the tiles evaluate every pair)
   int32_t gauss_nitems = 0;
   DevBuf d_group_items;  // binary64 tiles, two per wave
@@ -612,10 +612,16 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   c->ntiles = (int32_t)c->h_tiles.size();
   // 1-D expansions: blocks of up to kGaussTiles tiles of one realisation
   std::vector<TileGroup> gitems;
-  if (c->gauss)
+  std::vector<int32_t> gcell_real;
+  if (c->gauss) {
+    for (int64_t k = 0, r = 0; k < cell_off; k += kGaussCellGroup) {
+      while (r + 1 < c->n_real && c->h_rp[r + 1].cell_off <= k) ++r;
+      gcell_real.push_back((int32_t)r);
+    }
     for (int r = 0; r < c->n_real; ++r)
       for (int32_t t = c->h_tile_start[r]; t < c->h_tile_start[r + 1]; t += kGaussTiles)
         gitems.push_back(TileGroup{t, std::min<int32_t>(kGaussTiles, c->h_tile_start[r + 1] - t), r, 0});
+  }
   c->gauss_nitems = (int32_t)gitems.size();
   // binary64 tiles, two per wave
   std::vector<TileGroup> groups;
@@ -725,6 +731,9 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
     if (!gitems.empty())
       HIPCHK(c, hipMemcpyAsync(c->d_gauss_items.p, gitems.data(), gitems.size() * sizeof(TileGroup),
                                hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, c->d_gauss_cell_real.ensure(gcell_real.size() * sizeof(int32_t)));
+    HIPCHK(c, hipMemcpyAsync(c->d_gauss_cell_real.p, gcell_real.data(), gcell_real.size() * sizeof(int32_t),
+                             hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, launch_gauss_table(c->gauss, c->d_rp.as<RealParams>(), c->n_real, c->gauss_tab.as<double>(), c->stream));
   }
   HIPCHK(c, hipMemsetAsync(c->cell_count.p, 0, (size_t)ncell * 4, c->stream));
@@ -792,6 +801,7 @@ static PairArgs pair_args(rwpt_ctx* c) {
   a.gauss_mom = c->gauss_mom.as<double>();
   a.gauss_q = c->gauss ? c->r.as<double>() : nullptr;  // r itself is kept for the row normalisation only
   a.gauss_ncell = c->ncell_total;
+  a.gauss_cell_real = c->d_gauss_cell_real.as<int32_t>();
   return a;
 }
 
@@ -2276,7 +2286,7 @@ void rwpt_destroy(rwpt_ctx* c) {
                       &c->step_ctr, &c->counts, &c->d_chunks, &c->d_chunk_start, &c->chunk_part,
                       &c->audit_done, &c->bbox, &c->bparts, &c->nb_meta, &c->nb_idx, &c->nb_w,
                       &c->nb_src, &c->src_of, &c->half_slots, &c->half_own, &c->d_item_start,
-                      &c->d_item_real, &c->d_gauss_items, &c->gauss_tab,
+                      &c->d_item_real, &c->d_gauss_items, &c->d_gauss_cell_real, &c->gauss_tab,
                       &c->gauss_mom, &c->d_group_items};
     for (DevBuf* b : bufs) b->release();
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);

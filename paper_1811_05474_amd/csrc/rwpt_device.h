@@ -131,6 +131,7 @@ struct PairArgs {
   double* gauss_q;                 // 1 / r_i in binary64, as the symmetric expansions read it
   double* gauss_mom;               // [terms][gauss_ncell][columns] moments of the cells
   int64_t gauss_ncell;             // cells of all realisations
+  const int32_t* gauss_cell_real;  // realisation of cell k * kGaussCellGroup, in entry k (null: one realisation)
   const double* gauss_tab;         // [n_real][gauss_rows][terms] Hermite functions of the cell offsets
 };
 

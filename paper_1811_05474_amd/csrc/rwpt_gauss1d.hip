@@ -92,7 +92,10 @@ __global__ __launch_bounds__(kBlock) void k_gauss_moments(const PairArgs a) {
     const int64_t cell = e / NCOL;
     const int col = (int)(e - cell * NCOL);
     const uint32_t jb = a.cell_start[cell], je = a.cell_start[cell + 1];
-    int real = 0;
+    // from the group's first cell, whose realisation is this cell's or, near a
+    // boundary, one a few before it (searched from realisation 0: a step of 1000
+    // realisations of 4000 particles 6450 us, 1710 so)
+    int real = a.gauss_cell_real ? a.gauss_cell_real[cell / kGaussCellGroup] : 0;
     while (real + 1 < a.n_real && a.rp[real + 1].cell_off <= cell) ++real;
     const RealParams& R = a.rp[real];
     const double ctr = R.lo[0] + ((double)(cell - R.cell_off) + 0.5) / R.inv_h[0], gs = sqrt(-R.escale_d);

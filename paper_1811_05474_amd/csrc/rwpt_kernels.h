@@ -221,6 +221,7 @@ constexpr int kGaussTiles = 8;
 constexpr int kGaussPlans = 3;
 constexpr int kGaussMaxTerms = 10;
 constexpr int kGaussCells = 8;  // target cells a block takes at a time
+constexpr int kGaussCellGroup = 32;  // cells per entry of PairArgs::gauss_cell_real
 struct GaussPlan {
   int refine, terms;
   double width;

@@ -504,15 +504,16 @@ static bool gauss_reach(RealParams& P, const StencilRow* st, bool dense, const G
   return P.g_in <= plan.reach;
 }
 
-// Mean particles per cell from which the expansions pay: a cell costs about
-// (2 g_in + 1) P (P + 1) / 2 operations per column, 2200 with 32 cells per
-// cutoff, whatever it holds, and eight particles of 512 neighbours about 8 * 600 * 2
-// per column as pairs.
-constexpr int64_t kGaussPerCell = 8;
-
 // The 1-D expansion plan of an ensemble with `n_real` realisations of
 // real_start, or 0.  Only where the caller left tiling and cells open, in
 // binary32; a call for RWPT_PATH_DENSE gets the matrix-core kernels.
+// Particles per cell: a block takes 128 particles and eight target cells at a
+// time, so with a cutoff and fewer than about 18 it goes round twice, and the
+// tiles, whose work a cutoff bounds, are faster (steps of fixed positions,
+// expansions / tiles, us: 64000 particles of 700 neighbours 33 / 27, 900 33 / 32, 1200
+// 34 / 38, 1800 29 / 51; 1e6 of 900 400 / 329, 1200 326 / 427; eight species, 64000
+// of 900 75 / 58, 1800 56 / 98).  Against the matrix cores' full matrix eight are
+// enough (8192 particles, D = 1e-4: 20 / 25; 64000, 1e-6: 43 / 80).
 template <typename ScaleOf>
 static int gauss_plan(const rwpt_config& cfg, int dim, double dt, double D, int32_t n_real, const int64_t* real_start,
                       ScaleOf&& scale_of, bool dense) {
@@ -521,9 +522,10 @@ static int gauss_plan(const rwpt_config& cfg, int dim, double dt, double D, int3
     if (cfg.cell_refine[k] > 0) return 0;
   if (std::isinf(cfg.kappa) && !dense) return 0;
   for (int plan = 1; plan <= kGaussPlans; ++plan) {
-    if (dense != (plan == 3)) continue;
+    if (dense != (plan == kGaussFull)) continue;
     const double refine[3] = {(double)kGaussPlan[plan].refine, 1.0, 1.0};
     int64_t n = 0, cells = 0;
+    double pairs = 0.0;
     bool ok = true;
     for (int32_t r = 0; r < n_real && ok; ++r) {
       RealParams P;
@@ -536,9 +538,10 @@ static int gauss_plan(const rwpt_config& cfg, int dim, double dt, double D, int3
       if (P.active) {
         n += nr;
         cells += P.nc[0];
+        pairs += (double)nr * expected_neighbours(cfg, dim, dt, D * scale_of(r), nr);
       }
     }
-    if (ok && cells > 0 && n >= kGaussPerCell * cells) return plan;
+    if (ok && cells > 0 && n >= kGaussPlan[plan].per_cell * cells && (dense || pairs >= kGaussPairs)) return plan;
   }
   return 0;
 }

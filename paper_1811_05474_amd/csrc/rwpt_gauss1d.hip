@@ -133,8 +133,8 @@ __global__ __launch_bounds__(kBlock) void k_gauss_moments(const PairArgs a) {
 // reads was just written by another XCD, so the pass is a chain of a few long
 // latencies: everything a block needs is loaded in one round.  Waves 0-7 load
 // the moments and Hermite rows of the cells around CM target cells (a tile's
-// particles span few: the plan asks for at least eight particles per cell) and
-// transfer them, the cell offset split over the waves; waves 8-15 load the
+// particles span few: the plan asks for 18 particles per cell, the full matrix's
+// for eight) and transfer them, the cell offset split over the waves; waves 8-15 load the
 // particles of the cells that the cutoff may cut and evaluate those pairs,
 // four lanes per particle.  Then the offsets' shares are summed and the
 // polynomials evaluated at the block's particles, whose columns are shared by
@@ -413,7 +413,6 @@ static hipError_t launch_plan(int plan, const PairArgs& a, hipStream_t s) {
   };
   if (plan == 1) go(std::integral_constant<int, 1>{});
   else if (plan == 2) go(std::integral_constant<int, 2>{});
-  else if (plan == 3) go(std::integral_constant<int, 3>{});
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

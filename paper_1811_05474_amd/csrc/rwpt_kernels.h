@@ -215,10 +215,12 @@ hipError_t launch_exchange64(int dim, int log2l, const PairArgs& a, hipStream_t 
 // Dense 1-D neighbourhoods by expansions over cells (binary32, tiles of 16
 // particles).  Each plan: `refine` cells per cutoff length, terms of the
 // expansions, the widest cell in units of sigma (whose truncation is below
-// 2e-9 of a weight) and the largest g_in.  Plan 3 is the full matrix's, whose
-// "cutoff" is the distance of weights 2^-40.
+// 2e-9 of a weight), the largest g_in, and the mean particles per cell from
+// which it is taken.  Plan 2 is the full matrix's, whose "cutoff" is the distance
+// of weights 2^-40.
 constexpr int kGaussTiles = 8;
-constexpr int kGaussPlans = 3;
+constexpr int kGaussPlans = 2;
+constexpr int kGaussFull = 2;
 constexpr int kGaussMaxTerms = 10;
 constexpr int kGaussCells = 8;  // target cells a block takes at a time
 constexpr int kGaussCellGroup = 32;  // cells per entry of PairArgs::gauss_cell_real
@@ -226,9 +228,14 @@ struct GaussPlan {
   int refine, terms;
   double width;
   int reach;
+  int per_cell;
 };
-constexpr GaussPlan kGaussPlan[kGaussPlans + 1] = {
-    {0, 0, 0.0, 0}, {32, 8, 0.1, 31}, {16, 10, 0.2, 15}, {32, 10, 0.2, 40}};
+constexpr GaussPlan kGaussPlan[kGaussPlans + 1] = {{0, 0, 0.0, 0, 0}, {32, 8, 0.1, 31, 18}, {32, 10, 0.2, 40, 8}};
+// Pairs of a step, all realisations, from which a cutoff's expansions pay: up to
+// 32768 particles a launch of them is one round of blocks and takes 18 to 22 us
+// whatever it holds; the pair tiles' time grows with the pairs (exchange of 16000
+// particles of 1800 neighbours 20 us, of 1200 15 us; 32000 of 900 19 us).
+constexpr double kGaussPairs = 3e7;
 // values of the moment buffer for ncell cells of S species
 inline size_t gauss_moment_words(int plan, int64_t ncell, int S) {
   return (size_t)kGaussPlan[plan].terms * (size_t)ncell * (2 * padded_species(S) + 2);

@@ -567,7 +567,7 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
     nb += (double)nr / (double)std::max<int64_t>(c->N, 1) * expected_neighbours(cfg, dim, dt, D * c->d_scale[r], nr);
   }
   c->nb_mean = nb;
-  c->nb_slots = c->log2l == kPrivateLists ? slots_for(nb) : 0;
+  c->nb_slots = c->log2l == kPrivateLists ? slots_for(nb, dim, cfg.precision == RWPT_FP64, c->S) : 0;
   double defr[3];
   default_refine(dim, nb, defr);
   for (int k = 0; k < 3; ++k) c->refine[k] = cfg.cell_refine[k] > 0 ? cfg.cell_refine[k] : defr[k];
@@ -2091,7 +2091,8 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   const int64_t n_range[2] = {0, n};
   const double nb = expected_neighbours(c, dim, dt, D, n);
   int plan = gauss_plan(c, dim, dt, D, 1, n_range, [](int32_t) { return 1.0; }, false);
-  int nb_slots = log2l == kPrivateLists ? slots_for(nb) : 0;
+  int nb_slots = log2l == kPrivateLists ? slots_for(nb, dim, fp64, S) : 0;
+  double refine_nb = nb;
   const int32_t ntiles = (int32_t)((n + G - 1) / G);
   const int64_t cap = (int64_t)(n + 63) / 64 * 64;
   const int PS = dim, Sa = padded_species(S);
@@ -2100,15 +2101,15 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   size_t o_pos0, o_m0, o_m1, o_id, o_key, o_slot, o_tsrc, o_tid, o_tkey, o_skey, o_r, o_q, o_cnt, o_start,
       o_scan, o_rp, o_st, o_tiles, o_ctr, o_aud, o_meta = 0, o_nidx = 0, o_nw = 0, o_nsrc = 0, o_gtab = 0,
       o_gmom = 0;
-  // the forms that need more of the area (1-D expansions, neighbour slots with
-  // their smaller cells) only where they fit
+  // the forms that need more of the area (1-D expansions, neighbour slots,
+  // smaller cells) only where they fit
   for (;;) {
-    const bool last = !plan && !nb_slots;
+    const bool last = !plan && !nb_slots && refine_nb == 0.0;
     memset(&na, 0, sizeof(na));
     RowBuf rows{na.st, kNoAllocStencil, 0};
     float unused_escale = 0.0f, unused_skip = 0.0f;
     double refine[3];
-    default_refine(dim, nb_slots ? nb : 0.0, refine);
+    default_refine(dim, refine_nb, refine);
     if (plan) refine[0] = kGaussPlan[plan].refine;
     for (int k = 0; k < 3; ++k)
       if (c.cell_refine[k] > 0) refine[k] = c.cell_refine[k];
@@ -2159,6 +2160,7 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
                   "the allocation-free path has %zu",
                   n, dim, S, fp64 ? 64 : 32, (long long)ncell, L.used, kScratchBytes);
     plan = nb_slots = 0;
+    refine_nb = 0.0;
   }
   void* base = nullptr;
   st = scratch_on_current_device(&base);

@@ -94,10 +94,17 @@ constexpr uint32_t kCacheMiss = 15;
 // call, compacted / slots: 2 neighbours 91 / 80 us, 4: 103 / 84, 8: 126 / 92,
 // 12: 142 / 100; at 0.7 both take 77 (sparse cells: 73 compacted).
 constexpr double kSlotsFrom = 1.5;
-constexpr double kSlotsUpTo = 64.0;
 constexpr uint16_t kSlotMiss = 0xffff;
-// Slots per particle: room for nearly all of Poisson counts of mean nb.
-inline int slots_for(double nb) { return !(nb > kSlotsFrom && nb <= kSlotsUpTo) ? 0 : (nb <= 6.0 ? 16 : 32); }
+// Slots per particle, 0 for the compacted cache.  16 hold nearly all of Poisson
+// counts up to a mean of 6, 32 up to 16; beyond, more and more particles fill
+// their slots in vain and search again (2e5 particles, a step, compacted / slots in
+// us: 3-D 18 neighbours 146 / 127, 20 152 / 144, 24 167 / 181, 40 224 / 264; 3-D with
+// eight species 24 215 / 208, 28 228 / 239; 2-D 16 82 / 80, 18 86 / 84, 20 87 / 95, 32
+// 102 / 130; 2-D in binary64 14 97 / 95, 16 99 / 104).
+inline int slots_for(double nb, int dim, bool fp64, int S) {
+  const double up_to = dim == 3 ? (S > 4 ? 24.0 : 20.0) : (fp64 ? 14.0 : 18.0);
+  return !(nb > kSlotsFrom && nb <= up_to) ? 0 : (nb <= 6.0 ? 16 : 32);
+}
 // Half-stencil tiling (binary32): every unordered pair evaluated once, its
 // far-end share accumulated into slot planes and summed by a finalizer.
 constexpr int kHalfPairs = -4;

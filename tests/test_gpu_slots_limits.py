@@ -1,0 +1,55 @@
+"""Neighbour slots against the compacted cache on either side of the densities
+where the one gives way to the other (3-D 20 expected neighbours, 24 with more
+than four species; below, 18 in binary32 and 14 in binary64), against the oracle, and the allocation-free call
+at densities beyond, whose cells are the step's."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1811_05474_amd import rwpt, workloads as W
+
+pytestmark = pytest.mark.gpu
+
+F32, F64 = rwpt.RWPT_FP32, rwpt.RWPT_FP64
+# normwise bars of these kernels in binary32 / binary64 (see test_gpu_parity)
+BAR = {F32: 1e-5, F64: 1e-12}
+
+
+def D_for(n, nb, dim, dt=0.1):
+    unit = {1: 2.0, 2: math.pi, 3: 4.0 * math.pi / 3.0}[dim]
+    rc = (nb / (n * unit)) ** (1.0 / dim)
+    return rc * rc / (72.0 * dt)
+
+
+@pytest.mark.parametrize("dim,prec,nb,S", [
+    (3, F32, 23.9, 8), (3, F32, 24.1, 5), (3, F64, 19.9, 2), (3, F64, 20.1, 2), (2, F32, 17.9, 2), (2, F32, 18.1, 2),
+    (2, F64, 13.9, 3), (2, F64, 14.1, 3), (1, F32, 17.9, 2), (3, F32, 63.0, 2), (3, F32, 120.0, 2)])
+def test_step_and_allocation_free_call(dim, prec, nb, S):
+    import torch
+
+    n, dt = 7003, 0.1
+    D = D_for(n, nb, dim)
+    x, M = W.positions(n, dim, n + S), W.masses(n, S, n)
+    if prec == F32:
+        x, M = (a.astype(np.float32).astype(np.float64) for a in (x, M))
+    bits = 32 if prec == F32 else 64
+    ens = rwpt.Ensemble(dim=dim, n_species=S, react=(0, 1), kappa=3.0, rw_ratio=0.0, precision=prec, tile_lanes=-1)
+    ens.init([n], x, M)
+    rp, _ = oracle.neighbors(x, 3.0, D, dt, bits)
+    assert np.array_equal(ens.rowsums(dt, D, unit_weights=True), np.diff(rp))
+    ens.step(dt, D, 1)
+    got = ens.masses()
+    ref = oracle.transfer(x, M, D, dt, kappa=3.0, prec=bits, react=(0, 1))
+    assert np.abs(got - ref).max() <= BAR[prec] * np.abs(ref).max()
+    cfg = rwpt.rwpt_config_default()
+    cfg.dim, cfg.n_species, cfg.precision, cfg.tile_lanes = dim, S, prec, -1
+    t = torch.float32 if prec == F32 else torch.float64
+    xd, md = torch.from_numpy(x).to("cuda", t), torch.from_numpy(M).to("cuda", t)
+    out = torch.empty_like(md)
+    for _ in range(2):
+        rwpt.rwpt_transfer_noalloc(cfg, n, xd.data_ptr(), md.data_ptr(), out.data_ptr(), dt, D)
+    # the same cells and kernels as the step's: the same bits
+    assert np.array_equal(out.double().cpu().numpy(), got)
+    ens.close()

@@ -582,7 +582,7 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   c->h_tiles.clear();
   c->h_tile_start.assign(c->n_real + 1, 0);
   int64_t cell_off = 0;
-  c->small_sort = true;
+  c->small_sort = small_sort_pays(c->n_real, c->N);
   for (int r = 0; r < c->n_real; ++r) {
     RealParams& P = c->h_rp[r];
     const int64_t nr = c->real_start[r + 1] - c->real_start[r];
@@ -592,7 +592,7 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
     P.p_end = c->real_start[r + 1];
     const int64_t cells = (int64_t)P.nc[0] * P.nc[1] * P.nc[2];
     cell_off += cells;
-    c->small_sort = c->small_sort && nr <= kSmallParticles && cells <= kSmallCells;
+    c->small_sort = c->small_sort && small_sort_fits(nr, cells, cfg.precision == RWPT_FP64, c->S);
     if (half) half_segments(P, c->h_st.data() + P.stencil_off, nr, kHalfTarget);
     if (c->gauss && !gauss_reach(P, c->h_st.data(), c->dense, kGaussPlan[c->gauss]))
       return fail(c, RWPT_EUNSUPPORTED, "cell grid of the 1-D expansions");  // never: the plan was made for this grid
@@ -2179,7 +2179,7 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   // up to four species the exchange writes in the caller's order itself; more
   // are gathered from the sorted order afterwards (by the inverse of the ids, in
   // the keys' place), since scattered words cost more than that launch
-  const bool small = n <= kSmallParticles && ncell <= kSmallCells;
+  const bool small = small_sort_fits(n, ncell, fp64, S);
   const bool gather = S > 4 && !small;
   if (small) {
     SmallSortArgs ss;

@@ -1,5 +1,5 @@
 """Cells of many particles in the one-launch sort, whose in-cell order comes from
-bitmaps of the ids beyond 64 particles: the order is the general sort's, bit for
+bitmaps of the ids beyond 128 particles: the order is the general sort's, bit for
 bit, after steps that leave the particles where they are and after walked ones."""
 import numpy as np
 import pytest
@@ -13,18 +13,18 @@ def positions(kind, n, g):
     x = g.random((n, 2))
     if kind == "one point":
         x[:] = 0.4
-    elif kind == "edges":  # cells of 63 to 66 particles, one of 1000
+    elif kind == "edges":  # cells of 127 to 130 particles, one of 1000
         at = 0
-        for k, c in enumerate((63, 64, 65, 66, 1000)):
+        for k, c in enumerate((127, 128, 129, 130, 1000)):
             x[at:at + c] = 0.1 + 0.15 * k
             at += c
-    elif kind == "many":  # 62 cells of 66
-        x = 0.05 + 0.9 * np.stack([np.arange(n) // 66 % 8, np.arange(n) // 66 // 8], 1) / 8.0
+    elif kind == "many":  # 31 cells of 132
+        x = 0.05 + 0.9 * np.stack([np.arange(n) // 132 % 8, np.arange(n) // 132 // 8], 1) / 8.0
     return x[g.permutation(n)]
 
 
 @pytest.mark.parametrize("rw", [0.0, 0.05])
-@pytest.mark.parametrize("kind,n", [("one point", 4096), ("one point", 65), ("edges", 2000), ("many", 4092),
+@pytest.mark.parametrize("kind,n", [("one point", 4096), ("one point", 129), ("edges", 2000), ("many", 4092),
                                     ("spread", 4096)])
 def test_order_is_the_general_sorts(kind, n, rw):
     g = np.random.default_rng(n)
@@ -47,7 +47,7 @@ def test_order_is_the_general_sorts(kind, n, rw):
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("n", [64, 4095])
+@pytest.mark.parametrize("n", [128, 4095])
 def test_allocation_free_call_in_one_cell(n):
     import torch
 
@@ -63,4 +63,33 @@ def test_allocation_free_call_in_one_cell(n):
     ens.init([n, 5000], np.concatenate([x, W.positions(5000, 2, 1)]), np.concatenate([M, W.masses(5000, 2, 1)], 1))
     ens.step(0.1, 1e-3, 1)
     assert np.array_equal(out.cpu().numpy(), ens.masses()[:, :n])
+    ens.close()
+
+
+# (realisations, particles each, species): either side of 512 realisations, of 700 particles on
+# average beyond, and of 2048 particles with eight species slots in binary64
+@pytest.mark.parametrize("n_real,n,S", [(512, 20, 2), (513, 20, 2), (600, 699, 2), (600, 700, 2), (3, 2048, 8),
+                                        (3, 2049, 5)])
+def test_limits(n_real, n, S):
+    dt, D, seed = 0.1, 2e-5 * 400.0 / n, 11
+    x, M = W.positions(n_real * n, 2, n), W.masses(n_real * n, S, n)
+    ens = rwpt.Ensemble(dim=2, n_species=S, react=(0, 1), rw_ratio=1.0, precision=rwpt.RWPT_FP64, seed=seed)
+    ens.init([n] * n_real, x, M)
+    ens.step(dt, D, 2)
+    ens.step(dt, D, 1)
+    got, pos = ens.masses(), ens.positions()
+    assert np.allclose(ens.audit()[:, :S].sum(0), got.sum(1), rtol=1e-12)
+    ens.close()
+    # the realisations do not see each other, so the middle one is the same with a larger one beside it,
+    # under the general sort (its ids, hence its walk, are the same)
+    r = n_real // 2
+    rows = slice(r * n, (r + 1) * n)
+    sizes = [r * n, n, 5000]
+    ens = rwpt.Ensemble(dim=2, n_species=S, react=(0, 1), rw_ratio=1.0, precision=rwpt.RWPT_FP64, seed=seed)
+    ens.init(sizes, np.concatenate([x[:(r + 1) * n], W.positions(5000, 2, 1)]),
+             np.concatenate([M[:, :(r + 1) * n], W.masses(5000, S, 1)], 1))
+    ens.step(dt, D, 3)
+    assert np.array_equal(ens.positions()[rows], pos[rows])
+    # same tiles of eight or sixteen particles from the realisation's first on
+    assert np.array_equal(ens.masses()[:, rows], got[:, rows])
     ens.close()

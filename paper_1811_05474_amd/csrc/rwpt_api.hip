@@ -207,15 +207,15 @@ static int lanes_to_log2(int lanes) {
   }
 }
 
-static void default_refine(int dim, double nb, double out[3]) {
-  // nb: expected neighbours per particle.  Cells per cutoff length: fine along x (the fastest key axis, which trims
+static void default_refine(int dim, bool sparse, double out[3]) {
+  // Cells per cutoff length: fine along x (the fastest key axis, which trims
   // the candidate ranges), a few per cutoff across the other axes in 1-D and
   // 2-D
   if (dim == 1) {
     out[0] = 16.0; out[1] = 1.0; out[2] = 1.0;
   } else if (dim == 2) {
     out[0] = 16.0; out[1] = 2.0; out[2] = 1.0;
-  } else if (nb <= kSlotsFrom) {
+  } else if (sparse) {
     // sparse 3-D neighbourhoods (one lane per particle): cells of two
     // cutoffs, so each particle's cutoff box overlaps 2 x 2 rows of 2 cells
     out[0] = 0.5; out[1] = 0.5; out[2] = 0.5;
@@ -567,9 +567,9 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
     nb += (double)nr / (double)std::max<int64_t>(c->N, 1) * expected_neighbours(cfg, dim, dt, D * c->d_scale[r], nr);
   }
   c->nb_mean = nb;
-  c->nb_slots = c->log2l == kPrivateLists ? slots_for(nb, dim, cfg.precision == RWPT_FP64, c->S) : 0;
+  c->nb_slots = c->log2l == kPrivateLists ? slots_for(nb, dim, c->N, cfg.precision == RWPT_FP64, c->S) : 0;
   double defr[3];
-  default_refine(dim, nb, defr);
+  default_refine(dim, nb <= slots_from(dim, c->N, cfg.precision == RWPT_FP64, c->S), defr);
   for (int k = 0; k < 3; ++k) c->refine[k] = cfg.cell_refine[k] > 0 ? cfg.cell_refine[k] : defr[k];
   c->gauss = gauss_plan(cfg, dim, dt, D, c->n_real, c->real_start.data(), [&](int32_t r) { return c->d_scale[r]; },
                         c->dense);
@@ -1832,7 +1832,7 @@ rwpt_status rwpt_get_tiling(rwpt_ctx* c, int32_t* tile_lanes, double* cell_refin
   if (!c) return fail(nullptr, RWPT_EINVAL, "ctx is NULL");
   int lanes = c->cfg.tile_lanes ? c->cfg.tile_lanes : default_lanes(c->dim, c->N, c->cfg.precision == RWPT_FP64);
   double defr[3];
-  default_refine(c->dim, 0.0, defr);
+  default_refine(c->dim, true, defr);
   if (tile_lanes) *tile_lanes = lanes;
   if (cell_refine3)  // the grid's, once there is one
     for (int k = 0; k < 3; ++k)
@@ -2091,8 +2091,8 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   const int64_t n_range[2] = {0, n};
   const double nb = expected_neighbours(c, dim, dt, D, n);
   int plan = gauss_plan(c, dim, dt, D, 1, n_range, [](int32_t) { return 1.0; }, false);
-  int nb_slots = log2l == kPrivateLists ? slots_for(nb, dim, fp64, S) : 0;
-  double refine_nb = nb;
+  int nb_slots = log2l == kPrivateLists ? slots_for(nb, dim, n, fp64, S) : 0;
+  bool sparse = nb <= slots_from(dim, n, fp64, S);
   const int32_t ntiles = (int32_t)((n + G - 1) / G);
   const int64_t cap = (int64_t)(n + 63) / 64 * 64;
   const int PS = dim, Sa = padded_species(S);
@@ -2104,12 +2104,12 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   // the forms that need more of the area (1-D expansions, neighbour slots,
   // smaller cells) only where they fit
   for (;;) {
-    const bool last = !plan && !nb_slots && refine_nb == 0.0;
+    const bool last = !plan && !nb_slots && sparse;
     memset(&na, 0, sizeof(na));
     RowBuf rows{na.st, kNoAllocStencil, 0};
     float unused_escale = 0.0f, unused_skip = 0.0f;
     double refine[3];
-    default_refine(dim, refine_nb, refine);
+    default_refine(dim, sparse, refine);
     if (plan) refine[0] = kGaussPlan[plan].refine;
     for (int k = 0; k < 3; ++k)
       if (c.cell_refine[k] > 0) refine[k] = c.cell_refine[k];
@@ -2160,7 +2160,7 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
                   "the allocation-free path has %zu",
                   n, dim, S, fp64 ? 64 : 32, (long long)ncell, L.used, kScratchBytes);
     plan = nb_slots = 0;
-    refine_nb = 0.0;
+    sparse = true;
   }
   void* base = nullptr;
   st = scratch_on_current_device(&base);

@@ -93,17 +93,30 @@ constexpr uint32_t kCacheMiss = 15;
 // 1.5e5 particles in 3-D, eight species, cells of 2 x 1 x 1 per cutoff, whole
 // call, compacted / slots: 2 neighbours 91 / 80 us, 4: 103 / 84, 8: 126 / 92,
 // 12: 142 / 100; at 0.7 both take 77 (sparse cells: 73 compacted).
-constexpr double kSlotsFrom = 1.5;
+// A large ensemble's slots, one line of the memory per lane and entry, leave the
+// caches, and the masses have to follow every sort; few neighbours are then
+// fewer bytes compacted (a step, us: 3-D in cells of two cutoffs compacted, slots: 8e5
+// particles of 1.6 neighbours 116, 112, 1.6e6 171, 188, eight species 195, 242; 1.6e6 of 3
+// 263, 238, eight species 298, 296; 2-D: 8e5 of 2 106, 102, 1.6e6 162, 166, eight species
+// 188, 224; 1.6e6 of 4 234, 212, 274, 269; binary64 with eight species 8e5 of 1.6 in 3-D
+// 181, 190, in 2-D 142, 162).
+inline double slots_from(int dim, int64_t n, bool fp64, int S) {
+  return n <= (fp64 && S > 4 ? 600000 : 1000000) ? 1.5 : (dim == 3 ? 3.0 : 4.0);
+}
 constexpr uint16_t kSlotMiss = 0xffff;
 // Slots per particle, 0 for the compacted cache.  16 hold nearly all of Poisson
 // counts up to a mean of 6, 32 up to 16; beyond, more and more particles fill
-// their slots in vain and search again (2e5 particles, a step, compacted / slots in
-// us: 3-D 18 neighbours 146 / 127, 20 152 / 144, 24 167 / 181, 40 224 / 264; 3-D with
-// eight species 24 215 / 208, 28 228 / 239; 2-D 16 82 / 80, 18 86 / 84, 20 87 / 95, 32
-// 102 / 130; 2-D in binary64 14 97 / 95, 16 99 / 104).
-inline int slots_for(double nb, int dim, bool fp64, int S) {
-  const double up_to = dim == 3 ? (S > 4 ? 24.0 : 20.0) : (fp64 ? 14.0 : 18.0);
-  return !(nb > kSlotsFrom && nb <= up_to) ? 0 : (nb <= 6.0 ? 16 : 32);
+// their slots in vain and search again, in large ensembles at more bytes (a step,
+// compacted / slots in us: 2e5 particles 3-D 18 neighbours 146 / 127, 20 152 / 144, 24
+// 167 / 181, 40 224 / 264; with eight species 24 215 / 208, 28 228 / 239; 2e5 2-D 18 86 / 84,
+// 20 87 / 95, 32 102 / 130, in binary64 14 97 / 95, 16 99 / 104; 4e5 2-D 14 122 / 121, 16
+// 122 / 132, in binary64 12 147 / 134, 14 153 / 167; 1.6e6 2-D 10 308 / 296, 12 316 / 322, in
+// binary64 8 397 / 399, 10 415 / 445).
+inline int slots_for(double nb, int dim, int64_t n, bool fp64, int S) {
+  double up_to = n <= 600000 ? (fp64 ? 12.0 : 14.0) : (fp64 ? 8.0 : 10.0);
+  if (n <= 300000) up_to = fp64 ? 14.0 : 18.0;
+  if (dim == 3) up_to = S > 4 ? 24.0 : 20.0;
+  return !(nb > slots_from(dim, n, fp64, S) && nb <= up_to) ? 0 : (nb <= 6.0 ? 16 : 32);
 }
 // Half-stencil tiling (binary32): every unordered pair evaluated once, its
 // far-end share accumulated into slot planes and summed by a finalizer.

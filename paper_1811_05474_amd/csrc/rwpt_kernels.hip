@@ -1294,7 +1294,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange_priv(
 }
 
 // The same two passes with the neighbours in slots (PairArgs::nb_slots), for
-// neighbourhoods of more than kSlotsFrom.  Entry k of the tile's 64 particles is
+// neighbourhoods that slots_for names.  Entry k of the tile's 64 particles is
 // one row of the region, so the exchange reads rows whole; a particle with more
 // neighbours than slots is a miss.
 template <typename T, int DIM>

@@ -53,3 +53,24 @@ def test_step_and_allocation_free_call(dim, prec, nb, S):
     # the same cells and kernels as the step's: the same bits
     assert np.array_equal(out.double().cpu().numpy(), got)
     ens.close()
+
+
+# either side of the sizes at which the densities that take slots change (3e5, 6e5 and 1e6
+# particles), against the four-lane tiles: each within the kernels' bar of the exact masses
+@pytest.mark.parametrize("dim,n,nb,S", [(2, 300_000, 17.0, 2), (2, 300_001, 17.0, 2), (2, 600_000, 13.0, 2),
+                                        (2, 600_001, 9.9, 4), (2, 600_001, 10.1, 2), (2, 1_000_000, 2.0, 2),
+                                        (2, 1_000_001, 2.0, 2), (2, 1_000_001, 4.1, 8), (3, 1_000_000, 2.9, 2),
+                                        (3, 1_000_001, 2.9, 8), (3, 1_000_001, 3.1, 2)])
+def test_large_ensembles(dim, n, nb, S):
+    dt, D = 0.1, D_for(n, nb, dim)
+    x, M = (a.astype(np.float32).astype(np.float64) for a in (W.positions(n, dim, 7), W.masses(n, S, 7)))
+    out = []
+    for lanes in (-1, 4):
+        ens = rwpt.Ensemble(dim=dim, n_species=S, react=(0, 1), kappa=3.0, rw_ratio=0.0, tile_lanes=lanes)
+        ens.init([n], x, M)
+        counts = ens.rowsums(dt, D, unit_weights=True)
+        ens.step(dt, D, 2)
+        out.append((counts, ens.masses()))
+        ens.close()
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.abs(out[0][1] - out[1][1]).max() <= 2 * 2 * BAR[F32] * np.abs(out[1][1]).max()

@@ -27,13 +27,24 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
 // of 1e6 particles 0.379 -> 0.375.  Groups of 8, 16, 32, 64 and 512 blocks: the
 // former 0.374, 0.375, 0.376, 0.377, 0.378 ms, the batch 1.21 up to 64, 1.32 with 512.
 // The blocks after the last whole round are shared out as xcd_block does.
+// One lane per particle in 1-D and 2-D, where a block's vertical neighbours are
+// thousands of particles away and every cell row gathers from several: groups of
+// 256 (2e6 particles of 16 neighbours, a step in groups of 16, 64, 256 blocks and
+// contiguous eighths 399, 371, 349, 348 us, in binary64 545, 496, 470, 461; 8e6 in 3-D 648,
+// 648, 655, 669).  kXcdEighths, for the kernels without either: 8 lanes, 2e6
+// particles of 12 neighbours 562 -> 526, 16 lanes 866 -> 832.
 constexpr int kXcdGroup = 16;
+constexpr int kXcdEighths = 0;
+template <int DIM>
+constexpr int kXcdGroupSparse = DIM < 3 ? 256 : 16;
+template <int GROUP>
 __device__ __forceinline__ int xcd_group_block(int b, int nb) {
-  constexpr int R = 8 * kXcdGroup;
+  if constexpr (GROUP == kXcdEighths) return xcd_block(b, nb);
+  constexpr int R = GROUP > 0 ? 8 * GROUP : 1;
   const int whole = nb / R * R;
   if (b >= whole) return whole + xcd_block(b - whole, nb - whole);
   const int o = b % R;
-  return b - o + (o & 7) * kXcdGroup + (o >> 3);
+  return b - o + (o & 7) * GROUP + (o >> 3);
 }
 
 // Exchange of a double with lane ^ M: a DPP quad permutation for M = 1, 2

@@ -31,10 +31,10 @@ namespace rwpt {
 
 // Tile index of the calling wave, as tile_lane_setup derives it (SPLIT > 1:
 // one tile per block).
-template <int SPLIT = 1>
+template <int GROUP, int SPLIT = 1>
 __device__ __forceinline__ int64_t wave_tile() {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t blk = xcd_group_block(blockIdx.x, gridDim.x);
+  const int64_t blk = xcd_group_block<GROUP>(blockIdx.x, gridDim.x);
   return SPLIT > 1 ? blk : blk * (kBlock / 64) + wave;
 }
 
@@ -476,7 +476,7 @@ __device__ __forceinline__ void for_tile_rows(const RealParams& P, const Stencil
 // Load the tile header and this lane's particle.
 // SPLIT > 1: the SPLIT = kBlock / 64 waves of a block share one tile (each
 // takes every SPLIT-th chunk of its candidates); otherwise one tile per wave.
-template <int LOG2L, int SPLIT = 1>
+template <int LOG2L, int GROUP, int SPLIT = 1>
 __device__ __forceinline__ bool tile_lane_setup(const Tile* __restrict__ tiles, int32_t ntiles,
                                                 TileLane& tl, Tile& tile) {
   static_assert(SPLIT == 1 || SPLIT == kBlock / 64, "a split tile takes the waves of one block");
@@ -486,7 +486,7 @@ __device__ __forceinline__ bool tile_lane_setup(const Tile* __restrict__ tiles, 
   // derived from the tile is kept in scalar registers and loaded through the
   // scalar cache
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int blk = xcd_group_block(blockIdx.x, gridDim.x);
+  const int blk = xcd_group_block<GROUP>(blockIdx.x, gridDim.x);
   const int t = SPLIT > 1 ? blk : blk * (kBlock / 64) + wave;
   if (t >= ntiles) return false;
   tile = tiles[t];
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kBlock) void k_rowsum(
   wfn.setup();
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<LOG2L>(tiles, ntiles, tl, tile)) return;
+  if (!tile_lane_setup<LOG2L, kXcdEighths>(tiles, ntiles, tl, tile)) return;
   const RealParams& P = rp[tile.real];
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
   T xi[DIM];
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange(
   wfn.setup();
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<LOG2L>(tiles, ntiles, tl, tile)) return;
+  if (!tile_lane_setup<LOG2L, kXcdEighths>(tiles, ntiles, tl, tile)) return;
   const RealParams& P = rp[tile.real];
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
   T xi[DIM];
@@ -701,7 +701,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange(
     racc += __shfl_xor(racc, off);
   }
   exchange_epilogue<T, SMAX, G>(P, sym, acc, racc, Mi, tl.gl == 0 && tl.valid, tl.i, mout, S, react_a,
-                                react_b, audit_part, om, wave_tile());
+                                react_b, audit_part, om, wave_tile<kXcdEighths>());
 }
 
 // ---------------------------------------------------------------------------
@@ -827,7 +827,7 @@ __global__ __launch_bounds__(kBlock) void k_rowsum_dpp(
     float* __restrict__ q_out) {
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<2, SPLIT>(tiles, ntiles, tl, tile)) return;  // block-uniform when SPLIT > 1
+  if (!tile_lane_setup<2, kXcdGroup, SPLIT>(tiles, ntiles, tl, tile)) return;  // block-uniform when SPLIT > 1
   const int part = SPLIT > 1 ? (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const RealParams& P = rp[tile.real];
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange_dpp(
   constexpr int G = 16;
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<2, SPLIT>(tiles, ntiles, tl, tile)) return;  // block-uniform when SPLIT > 1
+  if (!tile_lane_setup<2, kXcdGroup, SPLIT>(tiles, ntiles, tl, tile)) return;  // block-uniform when SPLIT > 1
   const int part = SPLIT > 1 ? (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const RealParams& P = rp[tile.real];
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
@@ -967,7 +967,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange_dpp(
     if (!sym) racc += __shfl_xor(racc, off);
   }
   exchange_epilogue<float, SMAX, G>(P, sym, acc, racc, Mi, tl.gl == 0 && tl.valid, tl.i, mout, S,
-                                    react_a, react_b, audit_part, om, wave_tile<SPLIT>());
+                                    react_a, react_b, audit_part, om, wave_tile<kXcdGroup, SPLIT>());
 }
 
 // ---------------------------------------------------------------------------
@@ -1113,7 +1113,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
   wfn.setup();
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<0>(tiles, ntiles, tl, tile)) return;
+  if (!tile_lane_setup<0, kXcdGroupSparse<DIM>>(tiles, ntiles, tl, tile)) return;
   const RealParams& P = rp[tile.real];
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
   T xi[DIM];
@@ -1165,7 +1165,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) voi
   // is the last lane whose offset is <= e (a lane with no entries shares its
   // offset with the next lane).
   wave_lds_fence();
-  const int64_t wbase = wave_tile() * kCacheWave;
+  const int64_t wbase = wave_tile<kXcdGroupSparse<DIM>>() * kCacheWave;
   for (uint32_t r0 = 0; r0 < nent; r0 += 64) {
     const uint32_t e = r0 + (uint32_t)lane;
     int o = 0;
@@ -1210,7 +1210,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange_priv(
   wfn.setup();
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<0>(tiles, ntiles, tl, tile)) return;
+  if (!tile_lane_setup<0, kXcdGroupSparse<DIM>>(tiles, ntiles, tl, tile)) return;
   const RealParams& P = rp[tile.real];
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
   T Mi[SMAX];
@@ -1237,7 +1237,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange_priv(
   T* const sm = st_m[threadIdx.x >> 6];
   T* const swq = st_wq[threadIdx.x >> 6];
   const int lane = threadIdx.x & 63;
-  const int64_t wbase = wave_tile() * kCacheWave;
+  const int64_t wbase = wave_tile<kXcdGroupSparse<DIM>>() * kCacheWave;
   for (uint32_t r0 = 0; r0 < nent; r0 += 64) {
     const uint32_t e = r0 + (uint32_t)lane;
     const int64_t ge = wbase + (e < nent ? e : 0u);  // entry 0 exists when nent > 0
@@ -1290,7 +1290,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange_priv(
     });
   }
   exchange_epilogue<T, SMAX, 64>(P, sym, acc, racc, Mi, tl.valid, tl.i, mout, S, react_a, react_b,
-                                 audit_part, om, wave_tile());
+                                 audit_part, om, wave_tile<kXcdGroupSparse<DIM>>());
 }
 
 // The same two passes with the neighbours in slots (PairArgs::nb_slots), for
@@ -1307,7 +1307,7 @@ __global__ __launch_bounds__(kBlock) void k_rowsum_slots(
   wfn.setup();
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<0>(tiles, ntiles, tl, tile)) return;
+  if (!tile_lane_setup<0, kXcdGroupSparse<DIM>>(tiles, ntiles, tl, tile)) return;
   if (!tl.valid) return;
   const RealParams& P = rp[tile.real];
   const int32_t ii = tl.i;
@@ -1315,7 +1315,7 @@ __global__ __launch_bounds__(kBlock) void k_rowsum_slots(
   load_pos<T, DIM>(pos, ii, xi);
   const T rc2 = rc2_of<T>(P), esc = escale_of<T>(P);
   double acc = 1.0;  // only the self weight when the transfer is off
-  const int64_t base = wave_tile() * 64 * (int64_t)slots + tl.gi;
+  const int64_t base = wave_tile<kXcdGroupSparse<DIM>>() * 64 * (int64_t)slots + tl.gi;
   uint32_t cnt = 0;
   if (P.active) {
     acc = 0.0;
@@ -1358,7 +1358,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange_slots(
   wfn.setup();
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<0>(tiles, ntiles, tl, tile)) return;
+  if (!tile_lane_setup<0, kXcdGroupSparse<DIM>>(tiles, ntiles, tl, tile)) return;
   const RealParams& P = rp[tile.real];
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
   T Mi[SMAX];
@@ -1373,7 +1373,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange_slots(
   const uint32_t meta = mine ? nb_meta[ii] : 0u;
   if (mine && meta != kSlotMiss) {
     racc = sym ? 1.0 : r_in[ii];  // only the row normalisation divides by r_i
-    const int64_t base = wave_tile() * 64 * (int64_t)slots + tl.gi;
+    const int64_t base = wave_tile<kXcdGroupSparse<DIM>>() * 64 * (int64_t)slots + tl.gi;
     for (uint32_t k0 = 0; k0 < meta; k0 += U) {
       uint32_t j[U];
       T w[U], qj[U], mj[U][SMAX];
@@ -1419,7 +1419,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange_slots(
     });
   }
   exchange_epilogue<T, SMAX, 64>(P, sym, acc, racc, Mi, tl.valid, tl.i, mout, S, react_a, react_b, audit_part, om,
-                                 wave_tile());
+                                 wave_tile<kXcdGroupSparse<DIM>>());
 }
 
 // Counts ordered pairs j != i within the cutoff and candidate evaluations.
@@ -1428,7 +1428,7 @@ __global__ __launch_bounds__(kBlock) void k_count(PairArgs a) {
   constexpr int L = 1 << LOG2L;
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<LOG2L>(a.tiles, a.ntiles, tl, tile)) return;
+  if (!tile_lane_setup<LOG2L, kXcdEighths>(a.tiles, a.ntiles, tl, tile)) return;
   const RealParams& P = a.rp[tile.real];
   const T* __restrict__ pos = (const T*)a.pos;
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
@@ -1460,7 +1460,7 @@ __global__ __launch_bounds__(kBlock) void k_count(PairArgs a) {
     evals += __shfl_xor(evals, off);
   }
   if ((threadIdx.x & 63) == 0) {
-    const int t = xcd_group_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
+    const int64_t t = wave_tile<kXcdEighths>();
     a.counts[2 * t] = pairs;
     a.counts[2 * t + 1] = evals;
   }
@@ -1473,7 +1473,7 @@ __global__ __launch_bounds__(kBlock) void k_count_priv(PairArgs a) {
   constexpr int CB = PrivBatch<DIM>::kCandBatch;
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<0>(a.tiles, a.ntiles, tl, tile)) return;
+  if (!tile_lane_setup<0, kXcdGroupSparse<DIM>>(a.tiles, a.ntiles, tl, tile)) return;
   const RealParams& P = a.rp[tile.real];
   const T* __restrict__ pos = (const T*)a.pos;
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
@@ -1497,7 +1497,7 @@ __global__ __launch_bounds__(kBlock) void k_count_priv(PairArgs a) {
     evals += __shfl_xor(evals, off);
   }
   if ((threadIdx.x & 63) == 0) {
-    const int t = xcd_group_block(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
+    const int64_t t = wave_tile<kXcdGroupSparse<DIM>>();
     a.counts[2 * t] = pairs;
     a.counts[2 * t + 1] = evals;
   }
@@ -1512,7 +1512,7 @@ __global__ __launch_bounds__(kBlock) void k_nbr_priv(PairArgs a) {
   constexpr int CB = PrivBatch<DIM>::kCandBatch;
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<0>(a.tiles, a.ntiles, tl, tile)) return;
+  if (!tile_lane_setup<0, kXcdGroupSparse<DIM>>(a.tiles, a.ntiles, tl, tile)) return;
   if (!tl.valid) return;
   const RealParams& P = a.rp[tile.real];
   const T* __restrict__ pos = (const T*)a.pos;
@@ -1551,7 +1551,7 @@ template <int DIM, int SPLIT, int MODE>
 __global__ __launch_bounds__(kBlock) void k_nbr_dpp(PairArgs a) {
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<2, SPLIT>(a.tiles, a.ntiles, tl, tile)) return;  // block-uniform when SPLIT > 1
+  if (!tile_lane_setup<2, kXcdGroup, SPLIT>(a.tiles, a.ntiles, tl, tile)) return;  // block-uniform when SPLIT > 1
   const int part = SPLIT > 1 ? (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const RealParams& P = a.rp[tile.real];
   const float* __restrict__ pos = (const float*)a.pos;
@@ -1641,12 +1641,12 @@ __global__ __launch_bounds__(kBlock) void k_nbr_dpp(PairArgs a) {
           p += shc[w][0];
           e += shc[w][1];
         }
-        const int64_t t = wave_tile<SPLIT>();
+        const int64_t t = wave_tile<kXcdGroup, SPLIT>();
         a.counts[2 * t] = p;
         a.counts[2 * t + 1] = e;
       }
     } else if (lane == 0) {
-      const int64_t t = wave_tile();
+      const int64_t t = wave_tile<kXcdGroup>();
       a.counts[2 * t] = pairs;
       a.counts[2 * t + 1] = evals;
     }
@@ -1660,7 +1660,7 @@ __global__ __launch_bounds__(kBlock) void k_nbr(PairArgs a) {
   constexpr int L = 1 << LOG2L;
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<LOG2L>(a.tiles, a.ntiles, tl, tile)) return;
+  if (!tile_lane_setup<LOG2L, kXcdEighths>(a.tiles, a.ntiles, tl, tile)) return;
   const RealParams& P = a.rp[tile.real];
   const T* __restrict__ pos = (const T*)a.pos;
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
@@ -2309,7 +2309,7 @@ __device__ __forceinline__ void half_gather(const PairArgs& a, const RealParams&
 __global__ __launch_bounds__(kBlock) void k_half_rowsum_fin(PairArgs a) {
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<0>(a.tiles, a.ntiles, tl, tile)) return;
+  if (!tile_lane_setup<0, kXcdGroup>(a.tiles, a.ntiles, tl, tile)) return;
   if (!tl.valid) return;
   const RealParams& P = a.rp[tile.real];
   double r[1] = {1.0};
@@ -2328,7 +2328,7 @@ template <int SMAX>
 __global__ __launch_bounds__(kBlock) void k_half_exchange_fin(PairArgs a) {
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<0>(a.tiles, a.ntiles, tl, tile)) return;
+  if (!tile_lane_setup<0, kXcdGroup>(a.tiles, a.ntiles, tl, tile)) return;
   const RealParams& P = a.rp[tile.real];
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
   float Mi[SMAX];
@@ -2344,7 +2344,7 @@ __global__ __launch_bounds__(kBlock) void k_half_exchange_fin(PairArgs a) {
     racc = a.norm == 0 ? 1.0 : a.r_out[ii];  // only the row normalisation divides by r_i
   }
   exchange_epilogue<float, SMAX, 64>(P, a.norm == 0, acc, racc, Mi, tl.valid, tl.i, (float*)a.mass_out, a.S,
-                                     a.react_a, a.react_b, a.audit_part, a.out_map, wave_tile());
+                                     a.react_a, a.react_b, a.audit_part, a.out_map, wave_tile<kXcdGroup>());
 }
 
 // ---------------------------------------------------------------------------

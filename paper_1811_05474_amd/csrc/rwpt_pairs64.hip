@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kBlock) void k_pairs64(const PairArgs a) {
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int w = xcd_group_block(blockIdx.x, gridDim.x) * W + wave;
+  const int w = xcd_group_block<kXcdGroup>(blockIdx.x, gridDim.x) * W + wave;
   int tile = w, nt = 1;
   if constexpr (PP > 1) {
     if (w >= a.group_nitems) return;

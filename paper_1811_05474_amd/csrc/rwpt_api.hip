@@ -216,8 +216,8 @@ static void default_refine(int dim, bool sparse, double out[3]) {
   } else if (dim == 2) {
     out[0] = 16.0; out[1] = 2.0; out[2] = 1.0;
   } else if (sparse) {
-    // sparse 3-D neighbourhoods (one lane per particle): cells of two
-    // cutoffs, so each particle's cutoff box overlaps 2 x 2 rows of 2 cells
+    // cells of two cutoffs, so each particle's cutoff box overlaps 2 x 2 rows of
+    // 2 cells
     out[0] = 0.5; out[1] = 0.5; out[2] = 0.5;
   } else {
     // more candidates per row: smaller cells leave fewer of them outside the
@@ -225,6 +225,16 @@ static void default_refine(int dim, bool sparse, double out[3]) {
     // 0.7 neighbours 73 / 77 us, 2: 101 / 91, 4: 147 / 103, 12: 280 / 142)
     out[0] = 2.0; out[1] = 1.0; out[2] = 1.0;
   }
+}
+
+// Whether 3-D cells of two cutoffs are the better default.  Beside few
+// neighbours, realisations of few particles: smaller cells give every tile many
+// segments of a few particles each (a step with fixed positions, small cells / these,
+// us: one lane per particle, 150 realisations of 50 particles of 5 neighbours 46 / 10, of 150
+// of 15 58 / 21, of 500 of 25 91 / 120; four lanes 20 / 7, 17 / 9, 28 / 44); the neighbour slots
+// keep the small ones (150 of 8: 7.5 / 7.8).
+static bool sparse_cells(double nb, int dim, int64_t n, int64_t n_real, bool fp64, int S, int nb_slots) {
+  return nb <= slots_from(dim, n, fp64, S) || (!nb_slots && n <= 200 * n_real);
 }
 
 // Expected neighbours of a particle among nr in the box, walls aside.
@@ -569,7 +579,7 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   c->nb_mean = nb;
   c->nb_slots = c->log2l == kPrivateLists ? slots_for(nb, dim, c->N, cfg.precision == RWPT_FP64, c->S) : 0;
   double defr[3];
-  default_refine(dim, nb <= slots_from(dim, c->N, cfg.precision == RWPT_FP64, c->S), defr);
+  default_refine(dim, sparse_cells(nb, dim, c->N, c->n_real, cfg.precision == RWPT_FP64, c->S, c->nb_slots), defr);
   for (int k = 0; k < 3; ++k) c->refine[k] = cfg.cell_refine[k] > 0 ? cfg.cell_refine[k] : defr[k];
   c->gauss = gauss_plan(cfg, dim, dt, D, c->n_real, c->real_start.data(), [&](int32_t r) { return c->d_scale[r]; },
                         c->dense);
@@ -2092,7 +2102,7 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   const double nb = expected_neighbours(c, dim, dt, D, n);
   int plan = gauss_plan(c, dim, dt, D, 1, n_range, [](int32_t) { return 1.0; }, false);
   int nb_slots = log2l == kPrivateLists ? slots_for(nb, dim, n, fp64, S) : 0;
-  bool sparse = nb <= slots_from(dim, n, fp64, S);
+  bool sparse = sparse_cells(nb, dim, n, 1, fp64, S, nb_slots);
   const int32_t ntiles = (int32_t)((n + G - 1) / G);
   const int64_t cap = (int64_t)(n + 63) / 64 * 64;
   const int PS = dim, Sa = padded_species(S);

@@ -95,7 +95,8 @@ typedef struct rwpt_config {
                              operations), deterministic; 0 = choose from dim and N */
   double cell_refine[3];  /* cells per cutoff length along each axis (> 0); 0 = choose */
   int32_t device;         /* HIP device ordinal */
-  int32_t use_graph;      /* 1 = replay each rwpt_step as one captured HIP graph */
+  int32_t use_graph;      /* 1 = replay the steps of a call of three or more as captured HIP
+                             graphs, of eight steps and of one */
   uint64_t seed;          /* key of the counter-based random walk */
   void *stream;           /* hipStream_t to queue work on; NULL = a stream the context owns */
   /* Advection and hydrodynamic dispersion of the walk (Eq. 1, Eq. 2): a

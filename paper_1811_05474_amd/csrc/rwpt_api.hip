@@ -95,6 +95,13 @@ const char* kPhaseNames[PH_N] = {"walk_key", "cell_scan", "scatter", "canon", "r
 // of 1e6 particles in 2-D 0.419 -> 0.400 ms.  A longer one is paid for in the
 // first call, which captures it (about 0.3 ms).
 constexpr int kGraphSteps = 8;
+// Calls of fewer steps launch their kernels one by one: beside the launches
+// around the steps (row sums of fixed positions, audit) a graph of one step is one
+// submission more, not less (2000 particles in 2-D, fixed, calls of one / two
+// steps, us a step: launched 28 / 18, graphs 33 / 23, one graph with all of it 34 / 28;
+// walking 37 / 30, 40 / 34, 41 with all of it).  With fixed positions the first step
+// of calls too short for the longer graph is launched so, too.
+constexpr int kGraphFrom = 3;
 
 struct rwpt_ctx {
   rwpt_config cfg;
@@ -1332,7 +1339,8 @@ rwpt_status rwpt_step(rwpt_ctx* c, double dt, double D, int32_t n_steps) {
   }
   for (int32_t it = 0; it < n_steps;) {
     int32_t batch = 1;
-    if (c->cfg.use_graph && !c->prof) {
+    const bool launched = n_steps < kGraphFrom || (!walk && it == 0 && n_steps < kGraphSteps);
+    if (c->cfg.use_graph && !c->prof && !launched) {
       // a captured step bakes in the buffers of the mass parity it starts from
       const int m0 = c->mcur;
       batch = n_steps - it >= kGraphSteps ? kGraphSteps : 1;

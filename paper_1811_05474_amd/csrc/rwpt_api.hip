@@ -2177,8 +2177,8 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
                   "%d particles (dim %d, %d species, binary%d, %lld cells) need %zu bytes of scratch; "
                   "the allocation-free path has %zu",
                   n, dim, S, fp64 ? 64 : 32, (long long)ncell, L.used, kScratchBytes);
-    plan = nb_slots = 0;
-    sparse = true;
+    if (plan || nb_slots) plan = nb_slots = 0;
+    else sparse = true;
   }
   void* base = nullptr;
   st = scratch_on_current_device(&base);

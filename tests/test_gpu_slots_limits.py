@@ -74,3 +74,24 @@ def test_large_ensembles(dim, n, nb, S):
         ens.close()
     assert np.array_equal(out[0][0], out[1][0])
     assert np.abs(out[0][1] - out[1][1]).max() <= 2 * 2 * BAR[F32] * np.abs(out[1][1]).max()
+
+
+def test_allocation_free_call_whose_slots_do_not_fit():
+    """118000 particles of 12 neighbours in binary64: 32 slots each are beyond the
+    scratch area, the compacted cache with the step's cells is not."""
+    import torch
+
+    n, dt, S = 118_000, 0.1, 8
+    D = D_for(n, 12.0, 3)
+    x, M = W.positions(n, 3, 3), W.masses(n, S, 3)
+    cfg = rwpt.rwpt_config_default()
+    cfg.dim, cfg.n_species, cfg.precision = 3, S, F64
+    xd, md = torch.from_numpy(x).to("cuda"), torch.from_numpy(M).to("cuda")
+    out = torch.empty_like(md)
+    rwpt.rwpt_transfer_noalloc(cfg, n, xd.data_ptr(), md.data_ptr(), out.data_ptr(), dt, D)
+    ens = rwpt.Ensemble(dim=3, n_species=S, react=(0, 1), kappa=3.0, rw_ratio=0.0, precision=F64)
+    ens.init([n], x, M)
+    ens.step(dt, D, 1)
+    got = ens.masses()
+    assert np.abs(out.cpu().numpy() - got).max() <= 2 * BAR[F64] * np.abs(got).max()
+    ens.close()

@@ -163,7 +163,7 @@ struct rwpt_ctx {
   int32_t n_captures = 0;  // step graphs captured since the context was created
 
   // read-back of the queries
-  PinnedBuf pinned;
+  PinnedBuf pinned, bad_id;
   hipEvent_t read_ev[kReadSlots] = {};
 
   bool prof = false;
@@ -1504,14 +1504,20 @@ static rwpt_status fetch_sorted(rwpt_ctx* c, const DevBuf& buf, const DevBuf& st
   if (N == 0) return RWPT_OK;
   HIPCHK(c, hipSetDevice(c->cfg.device));
   // the sort's scratch is free between steps: the inverse of the id map
+  HIPCHK(c, c->bad_id.ensure(sizeof(uint32_t)));
+  volatile uint32_t* bad = (volatile uint32_t*)c->bad_id.p;
+  *bad = 0u;
   HIPCHK(c, launch_unsort(c->tsize == 8, (int32_t)N, c->id.as<uint32_t>(), c->tmp_src.as<uint32_t>(), buf.p, stage.p,
-                          comps, stride, species_major ? 1 : 0, c->stream));
+                          comps, stride, species_major ? 1 : 0, (uint32_t*)c->bad_id.p, c->stream));
+  rwpt_status st = RWPT_OK;
   try {
-    return read_back(c, stage.p, (size_t)comps * (size_t)N, out);
+    st = read_back(c, stage.p, (size_t)comps * (size_t)N, out);
   } catch (const std::bad_alloc&) {
     (void)hipStreamSynchronize(c->stream);
     return fail(c, RWPT_ENOMEM, "out of host memory");
   }
+  if (st == RWPT_OK && *bad) return fail(c, RWPT_EDEVICE, "corrupt id map");
+  return st;
 }
 
 rwpt_status rwpt_query_masses(rwpt_ctx* c, double* out) {
@@ -2302,6 +2308,7 @@ void rwpt_destroy(rwpt_ctx* c) {
     for (hipEvent_t e : c->read_ev)
       if (e) (void)hipEventDestroy(e);
     c->pinned.release();
+    c->bad_id.release();
     DevBuf* bufs[] = {&c->pos0, &c->pos1, &c->mass0, &c->mass1, &c->id, &c->key, &c->slot,
                       &c->tmp_src, &c->tmp_id, &c->tmp_key, &c->skey, &c->r, &c->q, &c->cell_count,
                       &c->cell_start, &c->scan_part, &c->d_rp, &c->d_st, &c->d_tiles,

@@ -2419,13 +2419,14 @@ __global__ __launch_bounds__(kBlock) void k_na_store(int32_t n, int32_t S, const
 // Caller's order for the queries
 // ---------------------------------------------------------------------------
 
-// inv[id[p]] = p.  (id is a permutation of 0..n-1.)
+// inv[id[p]] = p.  (id is a permutation of 0..n-1; *bad is set where it is not.)
 __global__ __launch_bounds__(kBlock) void k_invert(int32_t n, const uint32_t* __restrict__ id,
-                                                   uint32_t* __restrict__ inv) {
+                                                   uint32_t* __restrict__ inv, uint32_t* __restrict__ bad) {
   const int p = blockIdx.x * kBlock + threadIdx.x;
   if (p < n) {
     const uint32_t o = id[p];
     if (o < (uint32_t)n) inv[o] = (uint32_t)p;
+    else *bad = 1u;
   }
 }
 
@@ -2850,10 +2851,10 @@ hipError_t launch_noalloc_store(int fp64, int S, int32_t n, const void* mass_sor
 }
 
 hipError_t launch_unsort(int fp64, int32_t n, const uint32_t* id, uint32_t* inv, const void* in, void* out, int comps,
-                         int stride, int species_major, hipStream_t s) {
+                         int stride, int species_major, uint32_t* bad, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const dim3 g(blocks_for(n)), b(kBlock);
-  hipLaunchKernelGGL(k_invert, g, b, 0, s, n, id, inv);
+  hipLaunchKernelGGL(k_invert, g, b, 0, s, n, id, inv, bad);
   if (fp64)
     hipLaunchKernelGGL(k_unsort<double>, g, b, 0, s, n, inv, (const double*)in, (double*)out, comps, stride,
                        species_major);

@@ -274,6 +274,7 @@ rwpt_status rwpt_autotune(rwpt_ctx *ctx, double dt, double D, int32_t trial_step
  *             (not checked: the data stay on the device);
  *   mass_in:  device, S x n species-major, same type;
  *   mass_out: device, S x n species-major, same type; may not alias mass_in.
+ * The arrays need the alignment of their elements only.
  * Every intermediate lives in a fixed 64 MiB scratch area of the library on
  * the current device (held until the process ends), so the call makes no
  * device allocation and no host-device copy; it queues its kernels on

@@ -157,7 +157,8 @@ __global__ __launch_bounds__(kGaussBlock) void k_gauss1d(const PairArgs a) {
   // particles of the near cells; where they are more (blocks that span many
   // cells, clusters), they are read from memory
   constexpr int kNear = SMAX > 4 ? 512 : 1024;
-  __shared__ float near_x[kNear], near_q[MODE == 1 ? kNear : 1], near_m[MODE == 0 ? 1 : kNear * SMAX];
+  __shared__ float near_x[kNear], near_q[MODE == 1 ? kNear : 1];
+  __shared__ __attribute__((aligned(16))) float near_m[MODE == 0 ? 4 : kNear * SMAX];
   const int blk = xcd_block(blockIdx.x, gridDim.x);
   TileGroup item;
   if (a.gauss_items) {

@@ -396,7 +396,7 @@ __global__ __launch_bounds__(kBlock) void k_canon(
   T x[kCanonItems][DIM], m[kCanonItems][SMAX];
 #pragma unroll
   for (int u = 0; u < kCanonItems; ++u) {
-    load_pos<T, DIM>(pos_in, src[u], x[u]);
+    load_pos_unaligned<T, DIM>(pos_in, src[u], x[u]);  // the caller's array in the allocation-free call
     if constexpr (MOVE) {
       if (caller_S > 0) {
 #pragma unroll
@@ -2388,7 +2388,7 @@ __global__ __launch_bounds__(kBlock) void k_na_key(int32_t n, int32_t S, const T
   const int p = blockIdx.x * kBlock + threadIdx.x;
   if (p >= n) return;
   T x[DIM];
-  load_pos<T, DIM>(pos, p, x);
+  load_pos_unaligned<T, DIM>(pos, p, x);
   if (mass_out) {
     T m[SP];
 #pragma unroll

@@ -41,6 +41,25 @@ __device__ __forceinline__ void load_pos(const T* __restrict__ pos, int64_t j, T
   }
 }
 
+// The same from an array that is aligned to its elements only (a caller's, which
+// may begin anywhere in a larger one).  Global memory takes the pair as one load at
+// any such address.
+template <typename T>
+struct __attribute__((packed, aligned(sizeof(T)))) Packed2 {
+  T x, y;
+};
+
+template <typename T, int DIM>
+__device__ __forceinline__ void load_pos_unaligned(const T* __restrict__ pos, int64_t j, T x[DIM]) {
+  if constexpr (DIM == 2) {
+    const Packed2<T> v = *(const Packed2<T>*)(pos + 2 * j);
+    x[0] = v.x;
+    x[1] = v.y;
+  } else {
+    load_pos<T, DIM>(pos, j, x);
+  }
+}
+
 template <typename T, int DIM>
 __device__ __forceinline__ void store_pos(T* __restrict__ pos, int64_t j, const T x[DIM]) {
   if constexpr (DIM == 1) {

@@ -79,7 +79,8 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
   for (int u = 0; u < kSmallItems; ++u) {
     const int o = tid + u * kSmallBlock;
     const int64_t p = p0 + (o < n ? o : n - 1);
-    load_pos<T, DIM>((const T*)a.pos_in, p, x[u]);
+    if constexpr (NA) load_pos_unaligned<T, DIM>((const T*)a.pos_in, p, x[u]);
+    else load_pos<T, DIM>((const T*)a.pos_in, p, x[u]);
     id[u] = NA ? (uint32_t)p : a.id[p];
     if (a.src_out == nullptr) {
       if constexpr (NA) {

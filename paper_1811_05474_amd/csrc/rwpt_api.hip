@@ -704,10 +704,22 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   HIPCHK(c, c->counts.ensure((size_t)std::max(1, c->ntiles) * 2 * sizeof(unsigned long long)));
   if (c->log2l == kPrivateLists) {
     HIPCHK(c, c->nb_meta.ensure((size_t)c->cap * sizeof(uint16_t)));
-    const size_t entries = (size_t)std::max(1, c->ntiles) * (c->nb_slots ? 64 * c->nb_slots : kCacheWave);
-    HIPCHK(c, c->nb_idx.ensure(entries * sizeof(uint32_t)));
-    HIPCHK(c, c->nb_w.ensure(entries * c->tsize));
-    if (!c->nb_slots) HIPCHK(c, c->nb_src.ensure(entries * sizeof(uint32_t)));
+    auto cache = [&]() {
+      const size_t entries = (size_t)std::max(1, c->ntiles) * (c->nb_slots ? 64 * c->nb_slots : kCacheWave);
+      hipError_t e = c->nb_idx.ensure(entries * sizeof(uint32_t));
+      if (e == hipSuccess) e = c->nb_w.ensure(entries * c->tsize);
+      if (e == hipSuccess && !c->nb_slots) e = c->nb_src.ensure(entries * sizeof(uint32_t));
+      return e;
+    };
+    hipError_t e = cache();
+    if (e == hipErrorOutOfMemory && c->nb_slots) {
+      // slots take 128 to 384 bytes per particle, the compacted cache 48 or 64
+      c->nb_idx.release();
+      c->nb_w.release();
+      c->nb_slots = 0;
+      e = cache();
+    }
+    HIPCHK(c, e);
   }
   if (half) {
     const int Sa = padded_species(c->S);

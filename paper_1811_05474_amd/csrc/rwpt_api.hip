@@ -1418,7 +1418,18 @@ static rwpt_status read_back(rwpt_ctx* c, const void* dev_src, size_t n, double*
   const int64_t nchunks = (int64_t)((n + per - 1) / per);
   const int slots = (int)std::min<int64_t>(nchunks, kReadSlots);
   const size_t slot_bytes = nchunks > 1 ? kReadChunk : n * ts;
-  HIPCHK(c, c->pinned.ensure(slots * slot_bytes));
+  if (c->pinned.ensure(slots * slot_bytes) != hipSuccess) {
+    // no page-locked memory: chunk by chunk through pageable memory
+    std::vector<unsigned char> h(slot_bytes);
+    for (int64_t k = 0; k < nchunks; ++k) {
+      const size_t cnt = std::min(per, n - (size_t)k * per);
+      HIPCHK(c, hipMemcpyAsync(h.data(), (const unsigned char*)dev_src + (size_t)k * per * ts, cnt * ts,
+                               hipMemcpyDeviceToHost, c->stream));
+      HIPCHK(c, hipStreamSynchronize(c->stream));
+      widen_chunk(h.data(), cnt, ts == 8, out + (size_t)k * per);
+    }
+    return RWPT_OK;
+  }
   for (int k = 0; k < slots; ++k)
     if (!c->read_ev[k]) HIPCHK(c, hipEventCreateWithFlags(&c->read_ev[k], hipEventDisableTiming));
   unsigned char* pin = (unsigned char*)c->pinned.p;
@@ -1516,9 +1527,11 @@ static rwpt_status fetch_sorted(rwpt_ctx* c, const DevBuf& buf, const DevBuf& st
   if (N == 0) return RWPT_OK;
   HIPCHK(c, hipSetDevice(c->cfg.device));
   // the sort's scratch is free between steps: the inverse of the id map
-  HIPCHK(c, c->bad_id.ensure(sizeof(uint32_t)));
-  volatile uint32_t* bad = (volatile uint32_t*)c->bad_id.p;
-  *bad = 0u;
+  volatile uint32_t* bad = nullptr;  // without page-locked memory the ids are not checked
+  if (c->bad_id.ensure(sizeof(uint32_t)) == hipSuccess) {
+    bad = (volatile uint32_t*)c->bad_id.p;
+    *bad = 0u;
+  }
   HIPCHK(c, launch_unsort(c->tsize == 8, (int32_t)N, c->id.as<uint32_t>(), c->tmp_src.as<uint32_t>(), buf.p, stage.p,
                           comps, stride, species_major ? 1 : 0, (uint32_t*)c->bad_id.p, c->stream));
   rwpt_status st = RWPT_OK;
@@ -1528,7 +1541,7 @@ static rwpt_status fetch_sorted(rwpt_ctx* c, const DevBuf& buf, const DevBuf& st
     (void)hipStreamSynchronize(c->stream);
     return fail(c, RWPT_ENOMEM, "out of host memory");
   }
-  if (st == RWPT_OK && *bad) return fail(c, RWPT_EDEVICE, "corrupt id map");
+  if (st == RWPT_OK && bad && *bad) return fail(c, RWPT_EDEVICE, "corrupt id map");
   return st;
 }
 

@@ -231,7 +231,7 @@ hipError_t launch_noalloc_store(int fp64, int S, int32_t n, const void* mass_sor
 // the caller's order in `out`: out[k n + i] (species_major) or out[comps i + k]
 // for the caller's particle i = id[p].  inv (n entries) is overwritten with the
 // inverse of the id map; *bad (device or page-locked host memory, cleared by the
-// caller) is set if an id is not below n.
+// caller, or null) is set if an id is not below n.
 hipError_t launch_unsort(int fp64, int32_t n, const uint32_t* id, uint32_t* inv, const void* in, void* out, int comps,
                          int stride, int species_major, uint32_t* bad, hipStream_t s);
 

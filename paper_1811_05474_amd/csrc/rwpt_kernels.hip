@@ -2419,14 +2419,14 @@ __global__ __launch_bounds__(kBlock) void k_na_store(int32_t n, int32_t S, const
 // Caller's order for the queries
 // ---------------------------------------------------------------------------
 
-// inv[id[p]] = p.  (id is a permutation of 0..n-1; *bad is set where it is not.)
+// inv[id[p]] = p.  (id is a permutation of 0..n-1; *bad, unless null, is set where it is not.)
 __global__ __launch_bounds__(kBlock) void k_invert(int32_t n, const uint32_t* __restrict__ id,
                                                    uint32_t* __restrict__ inv, uint32_t* __restrict__ bad) {
   const int p = blockIdx.x * kBlock + threadIdx.x;
   if (p < n) {
     const uint32_t o = id[p];
     if (o < (uint32_t)n) inv[o] = (uint32_t)p;
-    else *bad = 1u;
+    else if (bad) *bad = 1u;
   }
 }
 

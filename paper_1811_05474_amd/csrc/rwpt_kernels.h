@@ -267,9 +267,10 @@ struct GaussPlan {
 constexpr GaussPlan kGaussPlan[kGaussPlans + 1] = {{0, 0, 0.0, 0, 0}, {32, 8, 0.1, 31, 18}, {32, 10, 0.2, 40, 8}};
 // Pairs of a step, all realisations, from which a cutoff's expansions pay: up to
 // 32768 particles a launch of them is one round of blocks and takes 18 to 22 us
-// whatever it holds; the pair tiles' time grows with the pairs (exchange of 16000
-// particles of 1800 neighbours 20 us, of 1200 15 us; 32000 of 900 19 us).
-constexpr double kGaussPairs = 3e7;
+// whatever it holds; the pair tiles' time grows with the pairs (a step with fixed
+// positions / with the walk, expansions, tiles, us: 16000 particles of 1200 neighbours 21 /
+// 54, 15 / 46, of 1800 19 / 51, 20 / 57; 8000 of 1800 19 / 50, 14 / 49, of 3000 22 / 61, 19 / 67).
+constexpr double kGaussPairs = 2.4e7;
 // values of the moment buffer for ncell cells of S species
 inline size_t gauss_moment_words(int plan, int64_t ncell, int S) {
   return (size_t)kGaussPlan[plan].terms * (size_t)ncell * (2 * padded_species(S) + 2);

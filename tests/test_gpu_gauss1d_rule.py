@@ -1,5 +1,5 @@
 """The rule that takes a 1-D cutoff to the expansions (1152 expected neighbours,
-3e7 pairs a step): which side each size falls on, as the cells per cutoff say,
+2.4e7 pairs a step): which side each size falls on, as the cells per cutoff say,
 neighbour sets, masses against the oracle, uneven positions, and the
 allocation-free call.  Bars as in test_gpu_gauss1d: 1e-6 normwise per step of
 the expansions, 1e-5 of the tiles."""
@@ -32,7 +32,8 @@ def ensemble(S, norm, rw=0.0):
 @pytest.mark.parametrize("n,nb,S,norm,expand", [
     (16385, 1900.0, 2, SYM, True), (20097, 1600.0, 8, SYM, True), (26240, 1200.0, 1, SYM, True),
     (25729, 1180.0, 5, ROW, True), (16511, 2500.0, 3, SYM, True), (33023, 1160.0, 2, ROW, True),
-    (16385, 1800.0, 2, SYM, False), (40001, 1100.0, 2, SYM, False), (9000, 3000.0, 2, ROW, False)])
+    (8009, 3010.0, 2, SYM, True), (16385, 1400.0, 2, SYM, False), (40001, 1100.0, 2, SYM, False),
+    (9000, 2600.0, 2, ROW, False)])
 def test_either_side(n, nb, S, norm, expand):
     D = D_for(n, nb)
     x, M = f32(W.positions(n, 1, n)), f32(W.masses(n, S, n))

@@ -609,7 +609,7 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
     P.p_end = c->real_start[r + 1];
     const int64_t cells = (int64_t)P.nc[0] * P.nc[1] * P.nc[2];
     cell_off += cells;
-    c->small_sort = c->small_sort && small_sort_fits(nr, cells, cfg.precision == RWPT_FP64, c->S);
+    c->small_sort = c->small_sort && small_sort_fits(nr, cells, dim, cfg.precision == RWPT_FP64, c->S);
     if (half) half_segments(P, c->h_st.data() + P.stencil_off, nr, kHalfTarget);
     if (c->gauss && !gauss_reach(P, c->h_st.data(), c->dense, kGaussPlan[c->gauss]))
       return fail(c, RWPT_EUNSUPPORTED, "cell grid of the 1-D expansions");  // never: the plan was made for this grid
@@ -2141,7 +2141,9 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   const double nb = expected_neighbours(c, dim, dt, D, n);
   int plan = gauss_plan(c, dim, dt, D, 1, n_range, [](int32_t) { return 1.0; }, false);
   int nb_slots = log2l == kPrivateLists ? slots_for(nb, dim, n, fp64, S) : 0;
-  bool sparse = sparse_cells(nb, dim, n, 1, fp64, S, nb_slots);
+  // (the small cells of shared tiles and of denser neighbourhoods are the
+  // context's alone)
+  bool sparse = log2l != kPrivateLists || nb > 64.0 || sparse_cells(nb, dim, n, 1, fp64, S, nb_slots);
   const int32_t ntiles = (int32_t)((n + G - 1) / G);
   const int64_t cap = (int64_t)(n + 63) / 64 * 64;
   const int PS = dim, Sa = padded_species(S);
@@ -2228,7 +2230,7 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   // up to four species the exchange writes in the caller's order itself; more
   // are gathered from the sorted order afterwards (by the inverse of the ids, in
   // the keys' place), since scattered words cost more than that launch
-  const bool small = small_sort_fits(n, ncell, fp64, S);
+  const bool small = small_sort_fits(n, ncell, dim, fp64, S);
   const bool gather = S > 4 && !small;
   if (small) {
     SmallSortArgs ss;

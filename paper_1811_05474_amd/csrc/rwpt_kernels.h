@@ -189,18 +189,22 @@ hipError_t launch_noalloc_key(int fp64, int dim, int S, const NoAllocParams& a, 
 // tiles; pos_in and mass_in in the caller's layouts); else null.
 constexpr int64_t kSmallParticles = 4096;
 constexpr int64_t kSmallCells = 16384;
-// Binary64 with eight species slots: the particles a thread holds spill beyond two
-// (3-D, one realisation, a step, one launch / general, us: 1500 particles 40 / 35, 2500
-// 49 / 36, 4096 62 / 36; 75 realisations of 2500 70 / 68), and from 3000 on the step was slower
-// than before there was this sort.
-inline bool small_sort_fits(int64_t n, int64_t ncell, bool fp64, int S) {
-  return n <= (fp64 && S > 4 ? kSmallParticles / 2 : kSmallParticles) && ncell <= kSmallCells;
+// 3-D in binary64 with eight species slots: the particles a thread holds spill (one
+// realisation, a step, one launch / general, us: 1500 particles 40 / 35, 2500 49 / 36, 4096
+// 62 / 36; 75 realisations of 2500 70 / 69), and from 3000 on the step was slower than before
+// there was this sort.
+inline bool small_sort_fits(int64_t n, int64_t ncell, int dim, bool fp64, int S) {
+  return n <= (dim == 3 && fp64 && S > 4 ? kSmallParticles / 2 : kSmallParticles) && ncell <= kSmallCells;
 }
-// One block per CU: beyond two rounds of them realisations of few particles leave
+// One block per CU: beyond three rounds of them realisations of few particles leave
 // most of their threads idle, where the general sort fills the chip (a step, one launch
-// / general, us: 512 of 300 2-D 61 / 68, 1024 of 100 64 / 60, 2048 of 100 107 / 89, 10000 of
-// 100 456 / 320, 2048 of 500 264 / 264, 3000 of 700 464 / 474, 10000 of 1000 2129 / 2240).
-inline bool small_sort_pays(int64_t n_real, int64_t n) { return n_real <= 512 || n >= 700 * n_real; }
+// / general, us: 512 of 300 2-D 61 / 68, 600 of 50 53 / 54, 1024 of 100 64 / 60, 2048 of 100
+// 107 / 89, 10000 of 100 456 / 320, 2048 of 500 264 / 264, 3000 of 700 464 / 474, 10000 of 1000
+// 2129 / 2240; of single particles, each of whose realisation the general sort looks
+// up, 1200 36 / 53, 2000 50 / 53, 4000 90 / 58).
+inline bool small_sort_pays(int64_t n_real, int64_t n) {
+  return n_real <= (n < 2 * n_real ? 2048 : 768) || n >= 700 * n_real;
+}
 struct SmallSortArgs {
   const void* pos_in;
   void* pos_out;           // may be pos_in

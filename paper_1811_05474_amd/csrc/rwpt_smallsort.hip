@@ -30,7 +30,7 @@ __device__ __forceinline__ int cell_word(int k) { return k + (k >> 4); }
 // runs on one CU, the cell's ids are marked in a bitmap over the realisation's and
 // a particle counts the bits below its own (a step of 4096 particles in one cell
 // 820 -> 46 us, 650 with the general sort; half of 4096 in one cell 184 -> 42).
-// The search for large cells costs the others 0.14 us.
+// The search for large cells costs the others 0.16 us.
 // A realisation's particles, counts and cell starts never leave the block: its
 // positions are all read (into registers) before any is written, so pos_out may
 // be pos_in.
@@ -100,6 +100,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
       if (!NA && a.do_walk && P.moves) walk_particle<T, DIM>(P, id[u], a.seed, step, x[u]);
       key[u] = (uint32_t)cell_index<T, DIM>(P, x[u]);
       slot[u] = atomicAdd(&cnt[cell_word(key[u])], 1u);
+      if (slot[u] >= kBigCell) any_big = 1u;
     }
   }
   __syncthreads();
@@ -107,15 +108,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
   // exclusive scan in place, consecutive counts per thread
   constexpr int kPer = kSmallCells / kSmallBlock;
   const int per = (ncell + kSmallBlock - 1) / kSmallBlock, c0 = tid * per;
-  uint32_t sum = 0, most = 0;
+  uint32_t sum = 0;
 #pragma unroll
   for (int k = 0; k < kPer; ++k)
-    if (k < per && c0 + k < ncell) {
-      const uint32_t c = cnt[cell_word(c0 + k)];
-      sum += c;
-      most = c > most ? c : most;
-    }
-  if (most > kBigCell) any_big = 1u;
+    if (k < per && c0 + k < ncell) sum += cnt[cell_word(c0 + k)];
   uint32_t v = sum;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -124,7 +120,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
   }
   if (lane == 63) sh[wave] = v;
   __syncthreads();
-  const uint32_t large = any_big;
+  const uint32_t large = any_big;  // some cell is
   uint32_t run = v - sum;
   for (int w = 0; w < wave; ++w) run += sh[w];
 #pragma unroll
@@ -135,71 +131,79 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
       run += c;
     }
   __syncthreads();
-  auto finish = [&](auto big) {
-    constexpr bool BIG = decltype(big)::value;  // some cell is large
-    auto cell = [&](int k) { return BIG ? cnt[cell_word(k)] & 0xffffu : cnt[cell_word(k)]; };
-    if constexpr (BIG) {
-      // a large cell's bitmap, plus one, above its start
-      for (int k = tid; k < ncell; k += kSmallBlock) {
-        const uint32_t c = cell(k), e = k + 1 < ncell ? cell(k + 1) : (uint32_t)n;
-        if (e - c > kBigCell) cnt[cell_word(k)] = c | (atomicAdd(&n_big, 1u) + 1u) << 16;
-      }
-      __syncthreads();
-      for (int k = tid; k < (int)n_big * kIdWords; k += kSmallBlock) (&bits[0][0])[k] = 0u;
-      __syncthreads();
-    }
-    for (int k = tid; k < ncell; k += kSmallBlock) start[k] = (uint32_t)p0 + cell(k);
-    if (tid == 0) start[ncell] = (uint32_t)P.p_end;  // the next realisation writes the same
-#pragma unroll
-    for (int u = 0; u < kSmallItems; ++u) {
-      const int o = tid + u * kSmallBlock;
-      if (o < n) {
-        const uint32_t w = cnt[cell_word(key[u])], l = id[u] - (uint32_t)p0;
-        if (BIG && (w >> 16)) atomicOr(&bits[(w >> 16) - 1u][l >> 5], 1u << (l & 31u));
-        else sid[w + slot[u]] = id[u];
-      }
+  // kRanked + its rank in slot for a particle of a large cell
+  constexpr uint32_t kRanked = 1u << 31;
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane(large) != 0u, 0)) {
+    // a large cell's bitmap, plus one, above its start
+    for (int k = tid; k < ncell; k += kSmallBlock) {
+      const uint32_t c = cnt[cell_word(k)] & 0xffffu;
+      const uint32_t e = k + 1 < ncell ? cnt[cell_word(k + 1)] & 0xffffu : (uint32_t)n;
+      if (e - c > kBigCell) cnt[cell_word(k)] = c | (atomicAdd(&n_big, 1u) + 1u) << 16;
     }
     __syncthreads();
-    if constexpr (BIG) {
-      for (int b = wave; b < (int)n_big; b += kSmallBlock / 64) {
-        const uint32_t first = (uint32_t)__popc(bits[b][2 * lane]);
-        const uint32_t both = first + (uint32_t)__popc(bits[b][2 * lane + 1]);
-        uint32_t t = both;
+    for (int k = tid; k < (int)n_big * kIdWords; k += kSmallBlock) (&bits[0][0])[k] = 0u;
+    __syncthreads();
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const uint32_t s = __shfl_up(t, off);
-          if (lane >= off) t += s;
-        }
-        below[b][2 * lane] = (uint16_t)(t - both);
-        below[b][2 * lane + 1] = (uint16_t)(t - both + first);
+    for (int u = 0; u < kSmallItems; ++u)
+      if (tid + u * kSmallBlock < n) {
+        const uint32_t b = cnt[cell_word(key[u])] >> 16, l = id[u] - (uint32_t)p0;
+        if (b) atomicOr(&bits[b - 1u][l >> 5], 1u << (l & 31u));
       }
-      __syncthreads();
+    __syncthreads();
+    for (int b = wave; b < (int)n_big; b += kSmallBlock / 64) {
+      const uint32_t first = (uint32_t)__popc(bits[b][2 * lane]);
+      const uint32_t both = first + (uint32_t)__popc(bits[b][2 * lane + 1]);
+      uint32_t t = both;
+      // (unrolled, it shares its lanes' addresses with the scan above, and they take ten
+      // registers from there to here)
+#pragma unroll 1
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t s = __shfl_up(t, off);
+        if (lane >= off) t += s;
+      }
+      below[b][2 * lane] = (uint16_t)(t - both);
+      below[b][2 * lane + 1] = (uint16_t)(t - both + first);
     }
-    // canonical order inside a cell: by id
+    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < kSmallItems; ++u) {
-      const int o = tid + u * kSmallBlock;
-      if (o < n) {
-        const uint32_t w = cnt[cell_word(key[u])], cs = cell((int)key[u]);
-        uint32_t rank = 0;
-        if (BIG && (w >> 16)) {
-          const uint32_t l = id[u] - (uint32_t)p0, b = (w >> 16) - 1u;
-          rank = below[b][l >> 5] + (uint32_t)__popc(bits[b][l >> 5] & ((1u << (l & 31u)) - 1u));
-        } else {
-          const uint32_t ce = (int)key[u] + 1 < ncell ? cell((int)key[u] + 1) : (uint32_t)n;
-          for (uint32_t f = cs; f < ce; ++f) rank += sid[f] < id[u] ? 1u : 0u;
-        }
-        const int64_t dst = p0 + cs + rank;
-        store_pos<T, DIM>((T*)a.pos_out, dst, x[u]);
-        if (a.src_out) a.src_out[dst] = (uint32_t)(p0 + o);
-        else store_mass<T, SMAX>((T*)a.mass_out, dst, m[u]);
-        a.id_out[dst] = id[u];
-        a.skey[dst] = (uint32_t)P.cell_off + key[u];
+    for (int u = 0; u < kSmallItems; ++u)
+      if (tid + u * kSmallBlock < n) {
+        const uint32_t b = cnt[cell_word(key[u])] >> 16, l = id[u] - (uint32_t)p0;
+        if (b)
+          slot[u] = kRanked + below[b - 1u][l >> 5] + (uint32_t)__popc(bits[b - 1u][l >> 5] & ((1u << (l & 31u)) - 1u));
       }
+    __syncthreads();
+    for (int k = tid; k < ncell; k += kSmallBlock) cnt[cell_word(k)] &= 0xffffu;
+    __syncthreads();
+  }
+  for (int k = tid; k < ncell; k += kSmallBlock) start[k] = (uint32_t)p0 + cnt[cell_word(k)];
+  if (tid == 0) start[ncell] = (uint32_t)P.p_end;  // the next realisation writes the same
+#pragma unroll
+  for (int u = 0; u < kSmallItems; ++u) {
+    const int o = tid + u * kSmallBlock;
+    if (o < n && slot[u] < kRanked) sid[cnt[cell_word(key[u])] + slot[u]] = id[u];
+  }
+  __syncthreads();
+  // canonical order inside a cell: by id
+#pragma unroll
+  for (int u = 0; u < kSmallItems; ++u) {
+    const int o = tid + u * kSmallBlock;
+    if (o < n) {
+      const uint32_t cs = cnt[cell_word(key[u])];
+      uint32_t rank = slot[u] & ~kRanked;
+      if (slot[u] < kRanked) {
+        const uint32_t ce = (int)key[u] + 1 < ncell ? cnt[cell_word(key[u] + 1)] : (uint32_t)n;
+        rank = 0;
+        for (uint32_t f = cs; f < ce; ++f) rank += sid[f] < id[u] ? 1u : 0u;
+      }
+      const int64_t dst = p0 + cs + rank;
+      store_pos<T, DIM>((T*)a.pos_out, dst, x[u]);
+      if (a.src_out) a.src_out[dst] = (uint32_t)(p0 + o);
+      else store_mass<T, SMAX>((T*)a.mass_out, dst, m[u]);
+      a.id_out[dst] = id[u];
+      a.skey[dst] = (uint32_t)P.cell_off + key[u];
     }
-  };
-  if (__builtin_expect(__builtin_amdgcn_readfirstlane(large) == 0u, 1)) finish(std::false_type{});
-  else finish(std::true_type{});
+  }
 }
 
 hipError_t launch_small_sort(int fp64, int dim, int32_t n_real, const SmallSortArgs& a, const NoAllocParams* na,

@@ -25,7 +25,7 @@ def D_for(n, nb, dim, dt=0.1):
 
 @pytest.mark.parametrize("dim,prec,nb,S", [
     (3, F32, 23.9, 8), (3, F32, 24.1, 5), (3, F64, 19.9, 2), (3, F64, 20.1, 2), (2, F32, 17.9, 2), (2, F32, 18.1, 2),
-    (2, F64, 13.9, 3), (2, F64, 14.1, 3), (1, F32, 17.9, 2), (3, F32, 63.0, 2), (3, F32, 120.0, 2)])
+    (2, F64, 13.9, 3), (2, F64, 14.1, 3), (1, F32, 17.9, 2), (3, F32, 63.0, 2)])
 def test_step_and_allocation_free_call(dim, prec, nb, S):
     import torch
 

@@ -66,14 +66,17 @@ def test_allocation_free_call_in_one_cell(n):
     ens.close()
 
 
-# (realisations, particles each, species): either side of 512 realisations, of 700 particles on
-# average beyond, and of 2048 particles with eight species slots in binary64
-@pytest.mark.parametrize("n_real,n,S", [(512, 20, 2), (513, 20, 2), (600, 699, 2), (600, 700, 2), (3, 2048, 8),
-                                        (3, 2049, 5)])
-def test_limits(n_real, n, S):
-    dt, D, seed = 0.1, 2e-5 * 400.0 / n, 11
-    x, M = W.positions(n_real * n, 2, n), W.masses(n_real * n, S, n)
-    ens = rwpt.Ensemble(dim=2, n_species=S, react=(0, 1), rw_ratio=1.0, precision=rwpt.RWPT_FP64, seed=seed)
+# (dimension, realisations, particles each, species): either side of 768 realisations, of 700
+# particles on average beyond, of 2048 single particles, and of 2048 particles in 3-D with eight
+# species slots in binary64
+@pytest.mark.parametrize("dim,n_real,n,S", [(2, 768, 20, 2), (2, 769, 20, 2), (2, 800, 699, 2), (2, 800, 700, 2),
+                                            (2, 2048, 1, 2), (2, 2049, 1, 2), (3, 3, 2048, 8), (3, 3, 2049, 5),
+                                            (2, 3, 2049, 8)])
+def test_limits(dim, n_real, n, S):
+    dt, seed = 0.1, 11
+    D = 2e-5 * 400.0 / n if dim == 2 else 1e-4
+    x, M = W.positions(n_real * n, dim, n), W.masses(n_real * n, S, n)
+    ens = rwpt.Ensemble(dim=dim, n_species=S, react=(0, 1), rw_ratio=1.0, precision=rwpt.RWPT_FP64, seed=seed)
     ens.init([n] * n_real, x, M)
     ens.step(dt, D, 2)
     ens.step(dt, D, 1)
@@ -84,12 +87,11 @@ def test_limits(n_real, n, S):
     # under the general sort (its ids, hence its walk, are the same)
     r = n_real // 2
     rows = slice(r * n, (r + 1) * n)
-    sizes = [r * n, n, 5000]
-    ens = rwpt.Ensemble(dim=2, n_species=S, react=(0, 1), rw_ratio=1.0, precision=rwpt.RWPT_FP64, seed=seed)
-    ens.init(sizes, np.concatenate([x[:(r + 1) * n], W.positions(5000, 2, 1)]),
+    bar = 1e-12 * np.abs(got).max() if dim == 3 else 0.0  # other cells, by the mean neighbours of all realisations
+    ens = rwpt.Ensemble(dim=dim, n_species=S, react=(0, 1), rw_ratio=1.0, precision=rwpt.RWPT_FP64, seed=seed)
+    ens.init([r * n, n, 5000], np.concatenate([x[:(r + 1) * n], W.positions(5000, dim, 1)]),
              np.concatenate([M[:, :(r + 1) * n], W.masses(5000, S, 1)], 1))
     ens.step(dt, D, 3)
     assert np.array_equal(ens.positions()[rows], pos[rows])
-    # same tiles of eight or sixteen particles from the realisation's first on
-    assert np.array_equal(ens.masses()[:, rows], got[:, rows])
+    assert np.abs(ens.masses()[:, rows] - got[:, rows]).max() <= bar
     ens.close()

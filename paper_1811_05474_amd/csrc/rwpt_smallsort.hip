@@ -133,7 +133,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_sort(const SmallSortArgs 
   __syncthreads();
   // kRanked + its rank in slot for a particle of a large cell
   constexpr uint32_t kRanked = 1u << 31;
-  if (__builtin_expect(__builtin_amdgcn_readfirstlane(large) != 0u, 0)) {
+  // (unlikely, but laid out of line it makes binary64 with eight species spill)
+  bool ranked = __builtin_amdgcn_readfirstlane(large) != 0u;
+  if constexpr (sizeof(T) * SMAX <= 32) ranked = __builtin_expect(ranked, false);
+  if (ranked) {
     // a large cell's bitmap, plus one, above its start
     for (int k = tid; k < ncell; k += kSmallBlock) {
       const uint32_t c = cnt[cell_word(k)] & 0xffffu;

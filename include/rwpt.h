@@ -71,7 +71,11 @@ enum { RWPT_NORM_SYM = 0, RWPT_NORM_ROW = 1 };
  * kappa = INFINITY (checked at create), RWPT_FP32 (create), and one
  * realisation of at most 131072 particles (init, else RWPT_EUNSUPPORTED).
  * Pairs whose weight is below 2^-40 are skipped tile-wise.
- * AUTO: DENSE when those conditions hold, else SPARSE. */
+ * AUTO: the full matrix when those conditions hold, else SPARSE.  AUTO's full
+ * matrix and SPARSE go through binary64 expansions over cells instead of pairs
+ * in 1-D, RWPT_FP32, where neighbourhoods are dense and tile_lanes and
+ * cell_refine are left open (the same neighbours, weights truncated below 2e-9
+ * of one). */
 enum { RWPT_PATH_AUTO = 0, RWPT_PATH_SPARSE = 1, RWPT_PATH_DENSE = 2 };
 
 typedef struct rwpt_config {
@@ -169,8 +173,10 @@ rwpt_status rwpt_steps_taken(rwpt_ctx *ctx, int64_t *out);
 
 /* Count, for the current positions and the cutoff of (dt, D), the ordered
  * neighbour pairs j != i within the cutoff (pairs_out, summed over
- * realisations) and the candidate evaluations the sparse kernels perform
- * (evals_out, may be NULL).  With the half-stencil tiling (tile_lanes = -2)
+ * realisations) and the candidate evaluations of the tiling in use
+ * (evals_out, may be NULL): those of single tiles where binary64 tiles go in
+ * twos (an eighth more), and those of the pair tiles where the step goes through
+ * the 1-D expansions, which evaluate pairs near the cutoff only.  With the half-stencil tiling (tile_lanes = -2)
  * both counts come from the one-lane tiles of 64 particles (the same pairs;
  * evals_out is then that enumeration's count, not the half stencil's own,
  * which evaluates each unordered pair once).  Synchronous; does not change
@@ -180,20 +186,23 @@ rwpt_status rwpt_count_pairs(rwpt_ctx *ctx, double dt, double D, int64_t *pairs_
 
 /* Debug export of the neighbour lists for the cutoff of (dt, D) and the
  * current positions, as CSR over the caller's particle order with ascending
- * global column indices, j = i included.  The candidates are enumerated as
- * the step's pair kernels enumerate them for the tiling in use (the chunked
- * candidate rows of the binary32 four-lane tiles, whole or split; each
- * particle's own cutoff box for one lane per particle; the stencil rows of
- * the other tilings), each decided by the same cutoff predicate.  Call with cols == NULL to get the
- * number of entries in *nnz_out; then with rowptr (N + 1 int64) and cols
- * (*nnz_out int32) allocated.  Synchronous; does not change the state. */
+ * global column indices, j = i included.  The candidates are enumerated for
+ * the tiling in use (the chunked candidate rows of the binary32 four-lane
+ * tiles, whole or split; each particle's own cutoff box for one lane per
+ * particle; the stencil rows of the other tilings, binary64 included), each
+ * decided by the cutoff predicate of the step's pair kernels; where the step
+ * goes through the 1-D expansions the four-lane tiles enumerate.  Call with
+ * cols == NULL to get the number of entries in *nnz_out; then with rowptr
+ * (N + 1 int64) and cols (*nnz_out int32) allocated.  Synchronous; does not
+ * change the state. */
 rwpt_status rwpt_neighbors(rwpt_ctx *ctx, double dt, double D, int64_t *rowptr, int32_t *cols,
                            int64_t *nnz_out);
 
 /* Debug: the row sums r_i = sum_j w_ij of the normalisation (Sec. 1.1, after
  * Eq. 3) for the current positions and the cutoff of (dt, D), computed by the
  * row-sum kernel of the sparse path in the launch shape a step uses (same
- * tiling, candidate enumeration and cutoff predicate), returned in the
+ * tiling, candidate enumeration and cutoff predicate, or the same 1-D
+ * expansions), returned in the
  * caller's particle order (r_out: N doubles, host).  unit_weights = 1 replaces
  * every weight by exp(0) = 1, so r_out[i] is exactly the number of particles
  * j (j = i included) that the step's own kernel takes as neighbours of i.
@@ -206,7 +215,9 @@ rwpt_status rwpt_debug_rowsums(rwpt_ctx *ctx, double dt, double D, int32_t unit_
  * brackets each kernel phase with HIP events on the context's stream.
  * rwpt_profile_read returns, per phase p < n_phases (at most 16), the summed
  * milliseconds ms[p] and launch counts cnt[p] since the last reset, and the
- * phase names through rwpt_profile_phase_name. */
+ * phase names through rwpt_profile_phase_name.  The audit runs once per call of
+ * rwpt_step, after its last step, and so do, before its first step, the row sums
+ * of positions that no walk moves. */
 rwpt_status rwpt_profile_enable(rwpt_ctx *ctx, int32_t on);
 rwpt_status rwpt_profile_reset(rwpt_ctx *ctx);
 rwpt_status rwpt_profile_read(rwpt_ctx *ctx, double *ms, int64_t *cnt, int32_t *n_phases);
@@ -224,7 +235,7 @@ typedef struct rwpt_stats_t {
   int64_t n_cells;            /* cells of the grid, all realisations */
   int64_t steps_taken;
   int64_t ordered_pairs;      /* pairs j != i within the cutoff */
-  int64_t candidate_evals;    /* candidate evaluations of the sparse kernels */
+  int64_t candidate_evals;    /* evals_out of rwpt_count_pairs */
   int32_t n_phases;           /* entries of phase_ms / phase_launches in use (<= 16) */
   int32_t graph_captures;     /* step graphs captured since rwpt_create (use_graph = 1) */
   double phase_ms[16];        /* per-phase milliseconds since the last profile reset */

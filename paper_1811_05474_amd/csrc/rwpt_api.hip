@@ -92,8 +92,9 @@ const char* kPhaseNames[PH_N] = {"walk_key", "cell_scan", "scatter", "canon", "r
 // Steps of the longer captured graph: even, so that it ends on the mass buffer
 // it began with.  A graph launch costs about 5 us beside its kernels' gaps: 500
 // 1-D steps of two launches each took 11.6 ms one step a graph, 8.6 ms so; one
-// of 1e6 particles in 2-D 0.419 -> 0.400 ms.  A longer one is paid for in the
-// first call, which captures it (about 0.3 ms).
+// of 1e6 particles in 2-D 0.419 -> 0.400 ms.  The first call of eight steps pays for
+// the capture of the longer one (that call, longer graph / one step's, us: 2000
+// particles 371 / 195, 1-D 32768 244 / 137, 1e6 in 2-D 2052 / 1760, in 3-D 1315 / 725).
 constexpr int kGraphSteps = 8;
 // Calls of fewer steps launch their kernels one by one: beside the launches
 // around the steps (row sums of fixed positions, audit) a graph of one step is one
@@ -256,17 +257,18 @@ static double expected_neighbours(const rwpt_config& cfg, int dim, double dt, do
 // fill the chip for small ensembles, fewer lanes per particle (smaller
 // candidate unions per lane) otherwise.
 static int default_lanes(int dim, int64_t n, bool fp64) {
-  // 1-D, binary32: the row-broadcast kernels (4 lanes) beat 16 lanes per
-  // particle (32768 particles: exchange 37 vs 54 us)
+  // 1-D, binary32: the row-broadcast kernels (a step of fixed positions of 200
+  // neighbours, 4 / 16 lanes, us: 2e4 particles 8.5 / 9.3, 1e6 105 / 190); binary64 tiles
+  // of 16 lanes for small ensembles (16 / 8 lanes: 2e4 12.0 / 12.7, but 1e6 231 / 193)
   if (dim == 1) return fp64 ? 16 : 4;
   if (dim == 3) return -1;  // sparse neighbourhoods: private candidate rows
-  // binary32: the row-broadcast kernels at every size (below 4097 tiles each
-  // tile takes a whole block); ~225 neighbours per particle, 2e4 - 3e5
-  // particles: 0.054 vs 0.058 ms (4 vs 8 lanes) at 2e4, 0.104 vs 0.140 at 1.5e5
+  // binary32: the row-broadcast kernels at every size (few tiles take a whole
+  // block each, split_tiles_for); a step of fixed
+  // positions of 225 neighbours, 4 / 8 lanes, us: 2e4 particles 13.4 / 18.6, 1.5e5 40 /
+  // 76, 1e6 192 / 427
   if (!fp64) return 4;
-  // binary64 (vector-load tiles; the exp is the cost): 8 lanes per particle
-  // beats 4 at every size measured, 0.975 vs 0.993 ms at 1e6, 0.351 vs 0.376
-  // at 3e5, 0.068 vs 0.083 at 2e4
+  // binary64: tiles of 8 particles a wave of their own kernels; a step as above, 8 / 4 /
+  // 16 lanes, us: 2e4 19.6 / 30.8 / 18.5, 3e5 118 / 200 / 133, 1e6 323 / 602 / 377
   (void)n;
   return 8;
 }

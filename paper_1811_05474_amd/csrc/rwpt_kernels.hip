@@ -1405,16 +1405,27 @@ __global__ __launch_bounds__(kBlock) void k_exchange_slots(
     load_pos<T, DIM>(pos, ii, xi);
     const T rc2 = rc2_of<T>(P), esc = escale_of<T>(P);
     for_own_rows<T, DIM>(P, st, cell_start, skey[ii] - (uint32_t)P.cell_off, [&](uint32_t jb, uint32_t je) {
-      for (uint32_t j = jb; j < je; ++j) {
-        const T s2 = sep2<T, DIM>(xi, pos, j);
-        if (!(s2 <= rc2)) continue;
-        const T w = wfn(s2, esc);
-        const T p = sym ? w * (qi + q[j]) : w;
-        racc += (double)w;
-        T mj[SMAX];
-        load_mass<T, SMAX>(min_, j, mj);
+      // bound by the loads' latency: U candidates' together (a step, one candidate at a
+      // time / so, us: 1.4e5 particles in 3-D, a third of them in a box of 0.02, 29748 / 24767,
+      // 1e6 of 20 neighbours 156 / 135)
+      for (uint32_t j0 = jb; j0 < je; j0 += U) {
+        T s2[U], qj[U], mj[U][SMAX];
 #pragma unroll
-        for (int s = 0; s < SMAX; ++s) acc[s] += (double)(p * (mj[s] - Mi[s]));
+        for (int u = 0; u < U; ++u) {
+          const uint32_t j = j0 + u < je ? j0 + u : je - 1;
+          s2[u] = j0 + u < je ? sep2<T, DIM>(xi, pos, j) : (T)INFINITY;
+          qj[u] = q[j];
+          load_mass<T, SMAX>(min_, j, mj[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (!(s2[u] <= rc2)) continue;
+          const T w = wfn(s2[u], esc);
+          const T p = sym ? w * (qi + qj[u]) : w;
+          racc += (double)w;
+#pragma unroll
+          for (int s = 0; s < SMAX; ++s) acc[s] += (double)(p * (mj[u][s] - Mi[s]));
+        }
       }
     });
   }

@@ -572,6 +572,13 @@ static bool two_tiles(const rwpt_config& cfg, int log2l, int32_t ntiles) {
   return cfg.precision == RWPT_FP64 && (log2l == 3 || log2l == 4) && !wide_cutoff(cfg) && ntiles >= kGroupMinTiles;
 }
 
+// Whether a step moves the particles.
+static bool walks(const rwpt_config& cfg, int dim, double D) {
+  bool advect = false;
+  for (int k = 0; k < dim; ++k) advect = advect || cfg.velocity[k] != 0.0;
+  return (cfg.rw_ratio > 0.0 && D > 0.0) || advect;
+}
+
 static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
   if (c->grid_valid && c->g_dt == dt && c->g_D == D) return RWPT_OK;
   const rwpt_config& cfg = c->cfg;
@@ -586,7 +593,9 @@ static rwpt_status build_grid(rwpt_ctx* c, double dt, double D) {
     nb += (double)nr / (double)std::max<int64_t>(c->N, 1) * expected_neighbours(cfg, dim, dt, D * c->d_scale[r], nr);
   }
   c->nb_mean = nb;
-  c->nb_slots = c->log2l == kPrivateLists ? slots_for(nb, dim, c->N, cfg.precision == RWPT_FP64, c->S) : 0;
+  c->nb_slots = 0;
+  if (c->log2l == kPrivateLists)
+    c->nb_slots = slots_for(nb, dim, c->N, c->n_real, cfg.precision == RWPT_FP64, c->S, !walks(cfg, dim, D));
   double defr[3];
   default_refine(dim, sparse_cells(nb, dim, c->N, c->n_real, cfg.precision == RWPT_FP64, c->S, c->nb_slots), defr);
   for (int k = 0; k < 3; ++k) c->refine[k] = cfg.cell_refine[k] > 0 ? cfg.cell_refine[k] : defr[k];
@@ -1340,9 +1349,7 @@ rwpt_status rwpt_step(rwpt_ctx* c, double dt, double D, int32_t n_steps) {
   HIPCHK(c, hipSetDevice(c->cfg.device));
   rwpt_status st = build_grid(c, dt, D);
   if (st != RWPT_OK) return st;
-  bool advect = false;
-  for (int k = 0; k < c->dim; ++k) advect = advect || c->cfg.velocity[k] != 0.0;
-  const bool walk = (c->cfg.rw_ratio > 0.0 && D > 0.0) || advect;
+  const bool walk = walks(c->cfg, c->dim, D);
   if (!walk) {
     // fixed positions: sorted once, and the row sums are those of every step
     // of this call (1-D, 32768 particles: 19 us of a 54 us step; full matrix
@@ -2142,7 +2149,7 @@ rwpt_status rwpt_transfer_noalloc(const rwpt_config* cfg, int32_t n, const void*
   const int64_t n_range[2] = {0, n};
   const double nb = expected_neighbours(c, dim, dt, D, n);
   int plan = gauss_plan(c, dim, dt, D, 1, n_range, [](int32_t) { return 1.0; }, false);
-  int nb_slots = log2l == kPrivateLists ? slots_for(nb, dim, n, fp64, S) : 0;
+  int nb_slots = log2l == kPrivateLists ? slots_for(nb, dim, n, 1, fp64, S, true) : 0;
   // (the small cells of shared tiles and of denser neighbourhoods are the
   // context's alone)
   bool sparse = log2l != kPrivateLists || nb > 64.0 || sparse_cells(nb, dim, n, 1, fp64, S, nb_slots);

@@ -106,16 +106,29 @@ inline double slots_from(int dim, int64_t n, bool fp64, int S) {
 constexpr uint16_t kSlotMiss = 0xffff;
 // Slots per particle, 0 for the compacted cache.  16 hold nearly all of Poisson
 // counts up to a mean of 6, 32 up to 16; beyond, more and more particles fill
-// their slots in vain and search again, in large ensembles at more bytes (a step,
-// compacted / slots in us: 2e5 particles 3-D 18 neighbours 146 / 127, 20 152 / 144, 24
-// 167 / 181, 40 224 / 264; with eight species 24 215 / 208, 28 228 / 239; 2e5 2-D 18 86 / 84,
-// 20 87 / 95, 32 102 / 130, in binary64 14 97 / 95, 16 99 / 104; 4e5 2-D 14 122 / 121, 16
-// 122 / 132, in binary64 12 147 / 134, 14 153 / 167; 1.6e6 2-D 10 308 / 296, 12 316 / 322, in
-// binary64 8 397 / 399, 10 415 / 445).
-inline int slots_for(double nb, int dim, int64_t n, bool fp64, int S) {
-  double up_to = n <= 600000 ? (fp64 ? 12.0 : 14.0) : (fp64 ? 8.0 : 10.0);
-  if (n <= 300000) up_to = fp64 ? 14.0 : 18.0;
-  if (dim == 3) up_to = S > 4 ? 24.0 : 20.0;
+// their slots in vain and search again, in large ensembles at more bytes.  Without
+// a walk a call fills them once and its steps read them, so they pay for longer
+// (`fixed`; the allocation-free call too, for the bits of such a step).  A step,
+// compacted / slots in us, fixed and with the walk: 2-D 1e5 particles of 20 neighbours
+// 32 / 25, 67 / 63, of 32 38 / 35, 78 / 77; 4e5 of 14 39 / 40, 104 / 105, of 18 47 / 46, 112 /
+// 124; 1e6 of 12 88 / 55, 187 / 188, of 18 96 / 84, 204 / 258, of 25 115 / 159; 2e6 of 12
+// 163 / 124, 327 / 398, of 16 170 / 167; binary64 1e6 of 10 112 / 76, 244 / 257, of 16
+// 121 / 121, 2e6 of 12 216 / 185, 439 / 573.  3-D 1e5 of 40 111 / 90, 192 / 162; 4e5 of 24
+// 134 / 110, 236 / 260; 2e6 of 20 471 / 299, 804 / 892, of 24 504 / 516; with eight species
+// 4e5 of 24 181 / 174, 288 / 321, binary64 of 20 172 / 111, 320 / 297.  1-D 4e5 of 12 32 / 29
+// (binary64), of 16 25 / 31, 69 / 76; 1e6 of 12 49 / 40, 114 / 118; 2e6 of 12 199 / 257 with
+// the walk.  3-D realisations of at most 200 particles, most of them one another's
+// neighbours from 20 on, then have the cells of two cutoffs that suit them (sparse_cells).
+constexpr int64_t kSlotsSizes[3] = {150000, 600000, 1500000};  // particles: up to each, beyond
+constexpr double kSlotsUpTo[3][2][2][4] = {  // expected neighbours: dimension, fixed, binary64, size
+    {{{16, 12, 10, 10}, {12, 12, 8, 8}}, {{20, 14, 14, 12}, {16, 12, 12, 10}}},
+    {{{24, 14, 12, 10}, {20, 14, 8, 8}}, {{32, 18, 20, 16}, {20, 18, 16, 12}}},
+    {{{40, 20, 20, 18}, {40, 20, 20, 20}}, {{40, 24, 24, 22}, {40, 24, 22, 22}}}};
+inline int slots_for(double nb, int dim, int64_t n, int64_t n_real, bool fp64, int S, bool fixed) {
+  int size = 0;
+  while (size < 3 && n > kSlotsSizes[size]) ++size;
+  double up_to = kSlotsUpTo[dim - 1][fixed][fp64][size];
+  if (dim == 3 && n <= 200 * n_real && up_to > 20.0) up_to = 20.0;
   return !(nb > slots_from(dim, n, fp64, S) && nb <= up_to) ? 0 : (nb <= 6.0 ? 16 : 32);
 }
 // Half-stencil tiling (binary32): every unordered pair evaluated once, its

@@ -1,7 +1,6 @@
 """Neighbour slots against the compacted cache on either side of the densities
-where the one gives way to the other (3-D 20 expected neighbours, 24 with more
-than four species; below, 18 in binary32 and 14 in binary64), against the oracle, and the allocation-free call
-at densities beyond, whose cells are the step's."""
+where the one gives way to the other, against the oracle, and the allocation-free
+call at densities beyond, whose cells are the step's."""
 import math
 
 import numpy as np
@@ -74,6 +73,31 @@ def test_large_ensembles(dim, n, nb, S):
         ens.close()
     assert np.array_equal(out[0][0], out[1][0])
     assert np.abs(out[0][1] - out[1][1]).max() <= 2 * 2 * BAR[F32] * np.abs(out[1][1]).max()
+
+
+@pytest.mark.parametrize("dim,prec,nb,S", [
+    (1, F32, 19.9, 2), (1, F32, 20.1, 2), (1, F64, 15.9, 2), (1, F64, 16.1, 2), (2, F32, 31.9, 3), (2, F32, 32.1, 3),
+    (2, F64, 19.9, 2), (2, F64, 20.1, 2), (3, F32, 39.9, 2), (3, F32, 40.1, 2), (3, F64, 39.9, 8), (3, F64, 40.1, 8)])
+def test_small_ensembles(dim, prec, nb, S):
+    test_step_and_allocation_free_call(dim, prec, nb, S)
+
+
+# with the walk the limits lie lower, on either side of 1.5e5, 6e5 and 1.5e6 particles
+@pytest.mark.parametrize("dim,n,nb", [(1, 150_000, 15.9), (1, 150_001, 15.9), (2, 150_000, 23.9), (2, 150_000, 24.1),
+                                      (2, 150_001, 14.1), (2, 600_001, 11.9), (2, 600_001, 12.1), (2, 1_500_001, 9.9),
+                                      (2, 1_500_001, 10.1), (3, 150_000, 39.9), (3, 150_001, 20.1)])
+def test_large_ensembles_with_the_walk(dim, n, nb):
+    dt, D = 0.1, D_for(n, nb, dim)
+    x, M = (a.astype(np.float32).astype(np.float64) for a in (W.positions(n, dim, 7), W.masses(n, 2, 7)))
+    out = []
+    for lanes in (-1, 4):
+        ens = rwpt.Ensemble(dim=dim, react=(0, 1), kappa=3.0, rw_ratio=1.0, tile_lanes=lanes)
+        ens.init([n], x, M)
+        ens.step(dt, D, 1)
+        out.append((ens.positions(), ens.masses()))
+        ens.close()
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.abs(out[0][1] - out[1][1]).max() <= 2 * BAR[F32] * np.abs(out[1][1]).max()
 
 
 def test_allocation_free_call_whose_slots_do_not_fit():

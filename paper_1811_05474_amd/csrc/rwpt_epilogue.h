@@ -31,20 +31,29 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
 // thousands of particles away and every cell row gathers from several: groups of
 // 256 (2e6 particles of 16 neighbours, a step in groups of 16, 64, 256 blocks and
 // contiguous eighths 399, 371, 349, 348 us, in binary64 545, 496, 470, 461; 8e6 in 3-D 648,
-// 648, 655, 669).  kXcdEighths, for the kernels without either: 8 lanes, 2e6
-// particles of 12 neighbours 562 -> 526, 16 lanes 866 -> 832.
+// 648, 655, 669).  The kernels of other tilings alike: 256 with 8 and 16 lanes (16, 64, 256,
+// eighths: 2e6 of 12 560, 556, 532, 522; 854, 868, 840, 808), 64 with 1 and 4 (1e6 of 30 475,
+// 406, 388, 374), whose clusters larger ones leave on few XCDs (2e5 of 30, a third in a
+// box of 0.02, one lane 5242, 5372, 7355, 7383 us, four in binary64 4931, 5487, 8543, 13975).
+// Fewer blocks take smaller groups, for the same reason and because what they read
+// stays in the L2s.
 constexpr int kXcdGroup = 16;
-constexpr int kXcdEighths = 0;
+constexpr int kXcdGroupWide = 64, kXcdGroupWideBlocks = 1024;  // from so many blocks
+constexpr int kXcdGroupWidest = 256, kXcdGroupWidestBlocks = 4096;
 template <int DIM>
-constexpr int kXcdGroupSparse = DIM < 3 ? 256 : 16;
+constexpr int kXcdGroupSparse = DIM < 3 ? kXcdGroupWidest : kXcdGroup;
+template <int LOG2L>
+constexpr int kXcdGroupLanes = LOG2L >= 3 ? kXcdGroupWidest : kXcdGroupWide;
 template <int GROUP>
 __device__ __forceinline__ int xcd_group_block(int b, int nb) {
-  if constexpr (GROUP == kXcdEighths) return xcd_block(b, nb);
-  constexpr int R = GROUP > 0 ? 8 * GROUP : 1;
-  const int whole = nb / R * R;
+  int log2g = 4;
+  if (GROUP > kXcdGroup && nb >= kXcdGroupWideBlocks) log2g = 6;
+  if (GROUP > kXcdGroupWide && nb >= kXcdGroupWidestBlocks) log2g = 8;
+  const int R = 8 << log2g;
+  const int whole = nb & -R;
   if (b >= whole) return whole + xcd_block(b - whole, nb - whole);
-  const int o = b % R;
-  return b - o + (o & 7) * GROUP + (o >> 3);
+  const int o = b & (R - 1);
+  return b - o + ((o & 7) << log2g) + (o >> 3);
 }
 
 // Exchange of a double with lane ^ M: a DPP quad permutation for M = 1, 2

@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kBlock) void k_rowsum(
   wfn.setup();
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<LOG2L, kXcdEighths>(tiles, ntiles, tl, tile)) return;
+  if (!tile_lane_setup<LOG2L, kXcdGroupLanes<LOG2L>>(tiles, ntiles, tl, tile)) return;
   const RealParams& P = rp[tile.real];
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
   T xi[DIM];
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange(
   wfn.setup();
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<LOG2L, kXcdEighths>(tiles, ntiles, tl, tile)) return;
+  if (!tile_lane_setup<LOG2L, kXcdGroupLanes<LOG2L>>(tiles, ntiles, tl, tile)) return;
   const RealParams& P = rp[tile.real];
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
   T xi[DIM];
@@ -701,7 +701,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange(
     racc += __shfl_xor(racc, off);
   }
   exchange_epilogue<T, SMAX, G>(P, sym, acc, racc, Mi, tl.gl == 0 && tl.valid, tl.i, mout, S, react_a,
-                                react_b, audit_part, om, wave_tile<kXcdEighths>());
+                                react_b, audit_part, om, wave_tile<kXcdGroupLanes<LOG2L>>());
 }
 
 // ---------------------------------------------------------------------------
@@ -1439,7 +1439,7 @@ __global__ __launch_bounds__(kBlock) void k_count(PairArgs a) {
   constexpr int L = 1 << LOG2L;
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<LOG2L, kXcdEighths>(a.tiles, a.ntiles, tl, tile)) return;
+  if (!tile_lane_setup<LOG2L, kXcdGroupLanes<LOG2L>>(a.tiles, a.ntiles, tl, tile)) return;
   const RealParams& P = a.rp[tile.real];
   const T* __restrict__ pos = (const T*)a.pos;
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
@@ -1471,7 +1471,7 @@ __global__ __launch_bounds__(kBlock) void k_count(PairArgs a) {
     evals += __shfl_xor(evals, off);
   }
   if ((threadIdx.x & 63) == 0) {
-    const int64_t t = wave_tile<kXcdEighths>();
+    const int64_t t = wave_tile<kXcdGroupLanes<LOG2L>>();
     a.counts[2 * t] = pairs;
     a.counts[2 * t + 1] = evals;
   }
@@ -1671,7 +1671,7 @@ __global__ __launch_bounds__(kBlock) void k_nbr(PairArgs a) {
   constexpr int L = 1 << LOG2L;
   TileLane tl;
   Tile tile;
-  if (!tile_lane_setup<LOG2L, kXcdEighths>(a.tiles, a.ntiles, tl, tile)) return;
+  if (!tile_lane_setup<LOG2L, kXcdGroupLanes<LOG2L>>(a.tiles, a.ntiles, tl, tile)) return;
   const RealParams& P = a.rp[tile.real];
   const T* __restrict__ pos = (const T*)a.pos;
   const int32_t ii = tl.valid ? tl.i : tile.end - 1;
